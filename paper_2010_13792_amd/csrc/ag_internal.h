@@ -279,15 +279,60 @@ template <class T> __device__ __forceinline__ T ag_wave_max(T v) {
     for (int o = 32; o > 0; o >>= 1) { T w = __shfl_xor(v, o, 64); v = w > v ? w : v; }
     return v;
 }
-// inclusive prefix sum over the wave
+// inclusive prefix sum over the wave, by DPP moves in the vector unit (rows of
+// 16 lanes, then the rows before): an LDS permute per step would take ten
+// times as long
+template <int C, int RowMask> __device__ __forceinline__ int ag_dpp_add(int v) {
+    return v + __builtin_amdgcn_update_dpp(0, v, C, RowMask, 0xF, false);
+}
 __device__ __forceinline__ int ag_wave_incl_scan(int v) {
-    const int lane = ag_lane();
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        int w = __shfl_up(v, o, 64);
-        if (lane >= o) v += w;
-    }
+    v = ag_dpp_add<0x111, 0xF>(v);   // row_shr 1, 2, 4, 8
+    v = ag_dpp_add<0x112, 0xF>(v);
+    v = ag_dpp_add<0x114, 0xF>(v);
+    v = ag_dpp_add<0x118, 0xF>(v);
+    v = ag_dpp_add<0x142, 0xA>(v);   // lane 15 of rows 0 and 2 into rows 1 and 3
+    v = ag_dpp_add<0x143, 0xC>(v);   // lane 31 into rows 2 and 3
     return v;
+}
+// minimum and maximum of a double over the wave (every lane gets it), by the
+// same moves; a lane without a partner keeps its own value
+template <int C, int RowMask> __device__ __forceinline__ double ag_dpp_f64(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp((int)b, (int)b, C, RowMask, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp((int)(b >> 32), (int)(b >> 32), C, RowMask, 0xF, false);
+    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+__device__ __forceinline__ double ag_last_lane_f64(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)b, 63);
+    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), 63);
+    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+template <int C, int RowMask> __device__ __forceinline__ double ag_dpp_min(double v) {
+    const double w = ag_dpp_f64<C, RowMask>(v);
+    return w < v ? w : v;
+}
+template <int C, int RowMask> __device__ __forceinline__ double ag_dpp_max(double v) {
+    const double w = ag_dpp_f64<C, RowMask>(v);
+    return w > v ? w : v;
+}
+__device__ __forceinline__ double ag_wave_min_f64(double v) {
+    v = ag_dpp_min<0x111, 0xF>(v);
+    v = ag_dpp_min<0x112, 0xF>(v);
+    v = ag_dpp_min<0x114, 0xF>(v);
+    v = ag_dpp_min<0x118, 0xF>(v);
+    v = ag_dpp_min<0x142, 0xA>(v);
+    v = ag_dpp_min<0x143, 0xC>(v);
+    return ag_last_lane_f64(v);
+}
+__device__ __forceinline__ double ag_wave_max_f64(double v) {
+    v = ag_dpp_max<0x111, 0xF>(v);
+    v = ag_dpp_max<0x112, 0xF>(v);
+    v = ag_dpp_max<0x114, 0xF>(v);
+    v = ag_dpp_max<0x118, 0xF>(v);
+    v = ag_dpp_max<0x142, 0xA>(v);
+    v = ag_dpp_max<0x143, 0xC>(v);
+    return ag_last_lane_f64(v);
 }
 
 // order-preserving map of doubles onto uint64 (for atomic min/max)

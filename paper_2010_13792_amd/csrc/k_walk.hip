@@ -2,8 +2,9 @@
 // active targets) and the adjoint walk (gradient of L = sum_k w_k . g_k).
 //
 // Work decomposition: the active targets, in key (Morton) order, are cut
-// into groups of at most 64 consecutive targets of one system; one wave64
-// (one workgroup) walks the tree once for its whole group.  Every lane owns
+// into groups of at most 64 consecutive targets of one system; one wave64,
+// or a team of waves where groups are few, walks the tree once for the whole
+// group.  Every lane owns
 // one target; in a group of fewer than 64 targets each target is given
 // several lanes, which share out the interaction list and add their parts
 // at the end, so the wave stays full.  The opening test is applied to the group's bounding box
@@ -22,6 +23,8 @@
 // group centre in LDS and all lanes evaluate the tile (LDS broadcast reads),
 // folding the FP32 tile sums into FP64 accumulators.
 #include <float.h>
+
+#include <algorithm>
 
 #include "ag_internal.h"
 #include "pair.h"
@@ -142,8 +145,8 @@ __device__ __forceinline__ float f_upr(double d) {
 __device__ __forceinline__ GroupBox group_box(double x, double y, double z) {
     double mnx = x, mny = y, mnz = z;
     double mxx = x, mxy = y, mxz = z;
-    mnx = ag_wave_min(mnx); mny = ag_wave_min(mny); mnz = ag_wave_min(mnz);
-    mxx = ag_wave_max(mxx); mxy = ag_wave_max(mxy); mxz = ag_wave_max(mxz);
+    mnx = ag_wave_min_f64(mnx); mny = ag_wave_min_f64(mny); mnz = ag_wave_min_f64(mnz);
+    mxx = ag_wave_max_f64(mxx); mxy = ag_wave_max_f64(mxy); mxz = ag_wave_max_f64(mxz);
     GroupBox g;
     g.cx = 0.5 * (mnx + mxx); g.cy = 0.5 * (mny + mxy); g.cz = 0.5 * (mnz + mxz);
     g.ox = g.cx; g.oy = g.cy; g.oz = g.cz;
@@ -306,15 +309,21 @@ __device__ __forceinline__ void fold(PairAcc<double>& D, const PairAcc<float>& F
     D.sxy += F.sxy; D.sxz += F.sxz; D.syz += F.syz;
 }
 
-// LDS of one wave
+// one staged tile of sources (layout set by the policy)
 template <int NT>
-struct WalkLds {
+struct TileLds {
+    float4 tile[NT * kW];
+    int tidx[kW];          // sorted index of each staged particle (self exclusion)
+};
+// lists of one traversal
+struct ListLds {
     int plist[kPCap];
     int nlist[kNCap];
     int2 stack[kSCap];
-    float4 tile[NT * kW];  // one staged tile of sources (layout set by the policy)
-    int tidx[kW];          // sorted index of each staged particle (self exclusion)
 };
+// LDS of a wave that walks a group on its own
+template <int NT>
+struct WalkLds : ListLds, TileLds<NT> {};
 
 struct Target {
     float tx, ty, tz;      // position relative to the group centre
@@ -344,9 +353,16 @@ struct ForwardPolicy {
     static constexpr bool kImageMac = false;
     static constexpr bool kGroupSum = false;
     static constexpr int kWaves = 4;   // launch bound: waves per SIMD (128 registers)
+    static constexpr int kTeamWaves = 16;   // largest team; with the relative opening test the middle one has kRelTeam
+    static constexpr int kRelTeam = 8;
+    using Tile = TileLds<5>;
     using Lds = WalkLds<5>;
+    using Sum = PairAcc<float>;   // one tile's sums
+    using Word = double;          // the walk's sums: kWords of them per lane
+    static constexpr int kWords = 12;
     struct Acc {
         PairAcc<double> a;
+        __device__ void fold(const Sum& f) { ::fold(a, f); }
         __device__ void zero() { a.zero(); }
         __device__ void add(const Acc& o) {
             a.ax += o.a.ax; a.ay += o.a.ay; a.az += o.a.az;
@@ -356,7 +372,7 @@ struct ForwardPolicy {
         }
     };
     template <int kPer>
-    __device__ static void stage_particle(Lds& S, const Tree& T, const GroupBox& gb, int lane, int pk,
+    __device__ static void stage_particle(Tile& S, const Tree& T, const GroupBox& gb, int lane, int pk,
                                           const WalkOut& O) {
         const double4 q = T.spos[pk];
         const float4 u = T.svf[pk];
@@ -376,9 +392,8 @@ struct ForwardPolicy {
     // so it always takes the softened branch, where it is dropped.  Periodic:
     // each pair is taken at its own nearest image.
     template <int kPer, bool kSoft>
-    __device__ static void particles(const Lds& S, int cnt, const Target& t, Acc& acc, float h2, float hinv,
+    __device__ static void particles(const Tile& S, int cnt, const Target& t, Sum& F, float h2, float hinv,
                                      int k0, int ks, const WalkOut& O) {
-        PairAcc<float> F;
         F.zero();
         float smf = 0.f;
         for (int k = k0; k < cnt; k += ks) {
@@ -450,10 +465,9 @@ struct ForwardPolicy {
         F.sxx += smf;
         F.syy += smf;
         F.szz += smf;
-        fold(acc.a, F);
     }
     template <int kPer>
-    __device__ static void stage_node(Lds& S, const Tree& T, const GroupBox& gb, int lane, int nk,
+    __device__ static void stage_node(Tile& S, const Tree& T, const GroupBox& gb, int lane, int nk,
                                       const WalkOut& O) {
         const double4 c = T.com[nk];
         const float4 m0 = T.mp[4 * nk], m1 = T.mp[4 * nk + 1], m2 = T.mp[4 * nk + 2], m3 = T.mp[4 * nk + 3];
@@ -470,8 +484,7 @@ struct ForwardPolicy {
         d[3 * kW + lane] = make_float4(m2.y, m2.z, m2.w, m3.x);   // Qyz, Qd xx yy zz
         d[4 * kW + lane] = make_float4(m3.y, m3.z, m3.w, 0.f);    // Qd xy xz yz
     }
-    __device__ static void nodes(const Lds& S, int cnt, const Target& t, Acc& acc, int k0, int ks, const WalkOut&) {
-        PairAcc<float> F;
+    __device__ static void nodes(const Tile& S, int cnt, const Target& t, Sum& F, int k0, int ks, const WalkOut&) {
         F.zero();
         float sca = 0.f;
         const float4* d = S.tile;
@@ -485,7 +498,6 @@ struct ForwardPolicy {
         F.sxx += sca;
         F.syy += sca;
         F.szz += sca;
-        fold(acc.a, F);
     }
     static __device__ void wave_sum(Acc&) {}
     __device__ static void finish(const Tree& T, const WalkOut& O, const Acc& A, int p, const Target&) {
@@ -521,15 +533,22 @@ struct AdjointPolicy {
     static constexpr bool kOpenAll = false;
     static constexpr bool kImageMac = false;
     static constexpr bool kGroupSum = false;
-    static constexpr int kWaves = 4;   // launch bound: waves per SIMD (128 registers)
+    static constexpr int kWaves = 3;   // launch bound: waves per SIMD (168 registers)
+    static constexpr int kTeamWaves = 12;
+    static constexpr int kRelTeam = 4;
+    using Tile = TileLds<9>;
     using Lds = WalkLds<9>;
+    using Sum = AdjAccF;
+    using Word = double;
+    static constexpr int kWords = 4;
     struct Acc {
         double vx, vy, vz, s;
+        __device__ void fold(const Sum& f) { vx += f.vx; vy += f.vy; vz += f.vz; s += f.s; }
         __device__ void zero() { vx = vy = vz = s = 0.0; }
         __device__ void add(const Acc& o) { vx += o.vx; vy += o.vy; vz += o.vz; s += o.s; }
     };
     template <int kPer>
-    __device__ static void stage_particle(Lds& S, const Tree& T, const GroupBox& gb, int lane, int pk,
+    __device__ static void stage_particle(Tile& S, const Tree& T, const GroupBox& gb, int lane, int pk,
                                           const WalkOut&) {
         static_assert(!kPer, "the adjoint walk has no periodic form");
         const double4 q = T.spos[pk];
@@ -539,10 +558,10 @@ struct AdjointPolicy {
         S.tidx[lane] = pk;
     }
     template <int kPer, bool kSoft>
-    __device__ static void particles(const Lds& S, int cnt, const Target& t, Acc& acc, float h2, float hinv,
+    __device__ static void particles(const Tile& S, int cnt, const Target& t, Sum& F, float h2, float hinv,
                                      int k0, int ks, const WalkOut&) {
         static_assert(!kSoft, "the adjoint walk has one softening length");
-        AdjAccF F{0.f, 0.f, 0.f, 0.f};
+        F = AdjAccF{0.f, 0.f, 0.f, 0.f};
         for (int k = k0; k < cnt; k += ks) {
             const float4 q = S.tile[k];
             const float4 w = S.tile[kW + k];
@@ -567,10 +586,9 @@ struct AdjointPolicy {
             F.vz += f * w.z + Ddw * dz;
             F.s += f * dw;
         }
-        acc.vx += F.vx; acc.vy += F.vy; acc.vz += F.vz; acc.s += F.s;
     }
     template <int kPer>
-    __device__ static void stage_node(Lds& S, const Tree& T, const GroupBox& gb, int lane, int nk, const WalkOut&) {
+    __device__ static void stage_node(Tile& S, const Tree& T, const GroupBox& gb, int lane, int nk, const WalkOut&) {
         const double4 c = T.com[nk];
         float4* d = S.tile;
         d[lane] = make_float4((float)(c.x - gb.cx), (float)(c.y - gb.cy), (float)(c.z - gb.cz), 0.f);
@@ -583,8 +601,8 @@ struct AdjointPolicy {
     //   s += 7.5 t/r^7 - 1.5 (d.trW + 2 d.trX)/r^5
     // u_b = W2_bce d_c d_e, s_e = W2_bce d_b d_c, t = d.u, trW_b = W2_bcc,
     // trX_c = W2_bbc.
-    __device__ static void nodes(const Lds& S, int cnt, const Target& t, Acc& acc, int k0, int ks, const WalkOut&) {
-        AdjAccF F{0.f, 0.f, 0.f, 0.f};
+    __device__ static void nodes(const Tile& S, int cnt, const Target& t, Sum& F, int k0, int ks, const WalkOut&) {
+        F = AdjAccF{0.f, 0.f, 0.f, 0.f};
         const float4* d = S.tile;
         for (int k = k0; k < cnt; k += ks) {
             const float4 c = d[k], a0 = d[kW + k], a1 = d[2 * kW + k], a2 = d[3 * kW + k], a3 = d[4 * kW + k];
@@ -638,7 +656,6 @@ struct AdjointPolicy {
             F.vz += f * a0.z + cd * dz + D * (Az + Bz) + 7.5f * ri7 * (2.f * sz + uz) - 1.5f * ri5 * (tWz + 2.f * tXz);
             F.s += f * (dW0 + tr) + D * dWd + 7.5f * tt * ri7 - 1.5f * dtr * ri5;
         }
-        acc.vx += F.vx; acc.vy += F.vy; acc.vz += F.vz; acc.s += F.s;
     }
     static __device__ void wave_sum(Acc&) {}
     __device__ static void finish(const Tree& T, const WalkOut& O, const Acc& A, int p, const Target&) {
@@ -768,11 +785,24 @@ struct EwaldPolicy {
     static constexpr bool kImageMac = true;
     static constexpr bool kGroupSum = true;
     static constexpr int kWaves = 4;   // launch bound: waves per SIMD (128 registers)
-    using Lds = WalkLds<8>;
+    static constexpr int kTeamWaves = 16;
+    static constexpr int kRelTeam = 4;
+    using Tile = TileLds<3>;
+    using Lds = WalkLds<3>;
+    // one tile's terms of a group sum (each lane holds at most one entry)
+    struct Sum {
+        float v[19];
+    };
+    using Word = float;
+    static constexpr int kWords = 19;
     struct Acc {
         // g 3, T 6, (group sums only) H 10; FP32 sums of at most a few
         // thousand terms per lane: rounding ~1e-6 relative, below the table's
         float v[19];
+        __device__ void fold(const Sum& f) {
+#pragma unroll
+            for (int k = 0; k < 19; ++k) v[k] += f.v[k];
+        }
         __device__ void zero() {
 #pragma unroll
             for (int k = 0; k < 19; ++k) v[k] = 0.f;
@@ -785,7 +815,7 @@ struct EwaldPolicy {
     // entry k: tile[k] = (position about the group centre, mass), tile[kW + k]
     // and tile[2 kW + k] = traceless quadrupole xx yy zz xy | xz yz (0 for particles)
     template <int kPer>
-    __device__ static void stage_particle(Lds& S, const Tree& T, const GroupBox& gb, int lane, int pk,
+    __device__ static void stage_particle(Tile& S, const Tree& T, const GroupBox& gb, int lane, int pk,
                                           const WalkOut& O) {
         const double4 q = T.spos[pk];
         S.tile[lane] = make_float4((float)near_img(q.x - gb.ox, O), (float)near_img(q.y - gb.oy, O),
@@ -794,7 +824,7 @@ struct EwaldPolicy {
         S.tile[2 * kW + lane] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
     template <int kPer>
-    __device__ static void stage_node(Lds& S, const Tree& T, const GroupBox& gb, int lane, int nk, const WalkOut& O) {
+    __device__ static void stage_node(Tile& S, const Tree& T, const GroupBox& gb, int lane, int nk, const WalkOut& O) {
         const double4 c = T.com[nk];
         const float4 m0 = T.mp[4 * nk], m1 = T.mp[4 * nk + 1], m2 = T.mp[4 * nk + 2];
         S.tile[lane] = make_float4((float)near_img(c.x - gb.ox, O), (float)near_img(c.y - gb.oy, O),
@@ -856,87 +886,90 @@ struct EwaldPolicy {
         g[1] -= c * (Qxx * H[1] + Qyy * H[6] + Qzz * H[8] + 2.f * (Qxy * H[3] + Qxz * H[4] + Qyz * H[7]));
         g[2] -= c * (Qxx * H[2] + Qyy * H[7] + Qzz * H[9] + 2.f * (Qxy * H[4] + Qxz * H[5] + Qyz * H[8]));
     }
-    __device__ static void entries(const Lds& S, int cnt, const Target& t, Acc& acc, int k0, int ks,
-                                   const WalkOut& O) {
+    // A compact group's terms about the group centre: c = entry - (group
+    // centre), at its image about the image origin; where that is not c's
+    // nearest image c', the field continues smoothly through
+    // dg(c) = dg(c') + g_single(c') - g_single(c) (likewise T and H).  Lane k
+    // takes entry k of the tile.
+    __device__ static void group_entry(const Tile& S, int cnt, const Target& t, Sum& F, const WalkOut& O) {
+        const int k = ag_lane();
+#pragma unroll
+        for (int c = 0; c < 19; ++c) F.v[c] = 0.f;
+        if (k >= cnt) return;
         EwaldVal E;
-        if (t.grp) {
-            // about the group centre: c = entry - (group centre), at its image
-            // about the image origin; where that is not c's nearest image c',
-            // the field continues smoothly through
-            // dg(c) = dg(c') + g_single(c') - g_single(c) (likewise T and H)
-            for (int k = threadIdx.x; k < cnt; k += kW) {
-                const float4 e = S.tile[k];
-                const float4 q0 = S.tile[kW + k], q1 = S.tile[2 * kW + k];
-                const float cx = e.x - t.g0x, cy = e.y - t.g0y, cz = e.z - t.g0z;
-                const float nx = near_imgf(cx, O), ny = near_imgf(cy, O), nz = near_imgf(cz, O);
-                ewald_lookup<true>(O, nx, ny, nz, E);
-                float gq[3] = {e.w * E.g[0], e.w * E.g[1], e.w * E.g[2]};
-                float tq[6], hq[10];
+        const float4 e = S.tile[k];
+        const float4 q0 = S.tile[kW + k], q1 = S.tile[2 * kW + k];
+        const float cx = e.x - t.g0x, cy = e.y - t.g0y, cz = e.z - t.g0z;
+        const float nx = near_imgf(cx, O), ny = near_imgf(cy, O), nz = near_imgf(cz, O);
+        ewald_lookup<true>(O, nx, ny, nz, E);
+        float gq[3] = {e.w * E.g[0], e.w * E.g[1], e.w * E.g[2]};
+        float tq[6], hq[10];
 #pragma unroll
-                for (int c = 0; c < 6; ++c) tq[c] = e.w * E.t[c];
+        for (int c = 0; c < 6; ++c) tq[c] = e.w * E.t[c];
 #pragma unroll
-                for (int c = 0; c < 10; ++c) hq[c] = e.w * E.h[c];
-                quad_g(q0, q1, E, gq);
-                if (nx != cx || ny != cy || nz != cz) {
-                    float g1[3], t1[6], g0[3], t0[6], h1[10], h0[10];
-                    newton_quad(nx, ny, nz, e.w, q0, q1, g1, t1);
-                    newton_quad(cx, cy, cz, e.w, q0, q1, g0, t0);
-                    newton_h(nx, ny, nz, e.w, h1);
-                    newton_h(cx, cy, cz, e.w, h0);
+        for (int c = 0; c < 10; ++c) hq[c] = e.w * E.h[c];
+        quad_g(q0, q1, E, gq);
+        if (nx != cx || ny != cy || nz != cz) {
+            float g1[3], t1[6], g0[3], t0[6], h1[10], h0[10];
+            newton_quad(nx, ny, nz, e.w, q0, q1, g1, t1);
+            newton_quad(cx, cy, cz, e.w, q0, q1, g0, t0);
+            newton_h(nx, ny, nz, e.w, h1);
+            newton_h(cx, cy, cz, e.w, h0);
 #pragma unroll
-                    for (int c = 0; c < 3; ++c) gq[c] += g1[c] - g0[c];
+            for (int c = 0; c < 3; ++c) gq[c] += g1[c] - g0[c];
 #pragma unroll
-                    for (int c = 0; c < 6; ++c) tq[c] += t1[c] - t0[c];
+            for (int c = 0; c < 6; ++c) tq[c] += t1[c] - t0[c];
 #pragma unroll
-                    for (int c = 0; c < 10; ++c) hq[c] += h1[c] - h0[c];
-                }
+            for (int c = 0; c < 10; ++c) hq[c] += h1[c] - h0[c];
+        }
 #pragma unroll
-                for (int c = 0; c < 3; ++c) acc.v[c] += gq[c];
+        for (int c = 0; c < 3; ++c) F.v[c] = gq[c];
 #pragma unroll
-                for (int c = 0; c < 6; ++c) acc.v[3 + c] += tq[c];
+        for (int c = 0; c < 6; ++c) F.v[3 + c] = tq[c];
 #pragma unroll
-                for (int c = 0; c < 10; ++c) acc.v[9 + c] += hq[c];
+        for (int c = 0; c < 10; ++c) F.v[9 + c] = hq[c];
+    }
+    // A wider group, per target: the forward walk took g and T at d, the image
+    // about the group centre; the periodic field is the same at the nearest
+    // image d', where the table is accurate, so add
+    // dg(d') + g_single(d') - g_single(d)  (the last two only when d' != d).
+    // The terms go straight into the walk's sums, entry by entry.
+    __device__ static void target_entries(const Tile& S, int cnt, const Target& t, Acc& acc, int k0, int ks,
+                                          const WalkOut& O) {
+        EwaldVal E;
+        for (int k = k0; k < cnt; k += ks) {
+            const float4 e = S.tile[k];
+            const float4 q0 = S.tile[kW + k], q1 = S.tile[2 * kW + k];
+            const float dx = e.x - t.tx, dy = e.y - t.ty, dz = e.z - t.tz;
+            const float nx = near_imgf(dx, O), ny = near_imgf(dy, O), nz = near_imgf(dz, O);
+            ewald_lookup<true>(O, nx, ny, nz, E);
+            float gq[3] = {e.w * E.g[0], e.w * E.g[1], e.w * E.g[2]};
+            float tq[6];
+#pragma unroll
+            for (int c = 0; c < 6; ++c) tq[c] = e.w * E.t[c];
+            quad_g(q0, q1, E, gq);
+            if (nx != dx || ny != dy || nz != dz) {
+                float g1[3], t1[6], g0[3], t0[6];
+                newton_quad(nx, ny, nz, e.w, q0, q1, g1, t1);
+                newton_quad(dx, dy, dz, e.w, q0, q1, g0, t0);
+#pragma unroll
+                for (int c = 0; c < 3; ++c) gq[c] += g1[c] - g0[c];
+#pragma unroll
+                for (int c = 0; c < 6; ++c) tq[c] += t1[c] - t0[c];
             }
-        } else {
-            // per target: the forward walk took g and T at d, the image about
-            // the group centre; the periodic field is the same at the nearest
-            // image d', where the table is accurate, so add
-            // dg(d') + g_single(d') - g_single(d)  (the last two only when d' != d)
-            for (int k = k0; k < cnt; k += ks) {
-                const float4 e = S.tile[k];
-                const float4 q0 = S.tile[kW + k], q1 = S.tile[2 * kW + k];
-                const float dx = e.x - t.tx, dy = e.y - t.ty, dz = e.z - t.tz;
-                const float nx = near_imgf(dx, O), ny = near_imgf(dy, O), nz = near_imgf(dz, O);
-                ewald_lookup<true>(O, nx, ny, nz, E);
-                float gq[3] = {e.w * E.g[0], e.w * E.g[1], e.w * E.g[2]};
-                float tq[6];
 #pragma unroll
-                for (int c = 0; c < 6; ++c) tq[c] = e.w * E.t[c];
-                quad_g(q0, q1, E, gq);
-                if (nx != dx || ny != dy || nz != dz) {
-                    float g1[3], t1[6], g0[3], t0[6];
-                    newton_quad(nx, ny, nz, e.w, q0, q1, g1, t1);
-                    newton_quad(dx, dy, dz, e.w, q0, q1, g0, t0);
+            for (int c = 0; c < 3; ++c) acc.v[c] += gq[c];
 #pragma unroll
-                    for (int c = 0; c < 3; ++c) gq[c] += g1[c] - g0[c];
-#pragma unroll
-                    for (int c = 0; c < 6; ++c) tq[c] += t1[c] - t0[c];
-                }
-#pragma unroll
-                for (int c = 0; c < 3; ++c) acc.v[c] += gq[c];
-#pragma unroll
-                for (int c = 0; c < 6; ++c) acc.v[3 + c] += tq[c];
-            }
+            for (int c = 0; c < 6; ++c) acc.v[3 + c] += tq[c];
         }
     }
     template <int kPer, bool kSoft>
-    __device__ static void particles(const Lds& S, int cnt, const Target& t, Acc& acc, float, float, int k0,
-                                     int ks, const WalkOut& O) {
-        entries(S, cnt, t, acc, k0, ks, O);
+    __device__ static void particles(const Tile& S, int cnt, const Target& t, Sum& F, float, float, int, int,
+                                     const WalkOut& O) {
+        group_entry(S, cnt, t, F, O);
     }
-    __device__ static void nodes(const Lds& S, int cnt, const Target& t, Acc& acc, int k0, int ks,
-                                 const WalkOut& O) {
-        entries(S, cnt, t, acc, k0, ks, O);
+    __device__ static void nodes(const Tile& S, int cnt, const Target& t, Sum& F, int, int, const WalkOut& O) {
+        group_entry(S, cnt, t, F, O);
     }
     static __device__ void wave_sum(Acc& A) {
 #pragma unroll
@@ -1051,6 +1084,7 @@ struct KnnPolicy {
     static constexpr bool kGroupSum = false;
     // the list's registers: 2 kCap of them
     static constexpr int kWaves = kCap <= 16 ? 4 : (kCap <= 32 ? 3 : 1);
+    using Tile = KnnLds;
     using Lds = KnnLds;
     struct Acc {
         double x, y, z;   // the target
@@ -1273,6 +1307,7 @@ struct PmPolicy {
     static constexpr bool kImageMac = false;
     static constexpr bool kGroupSum = false;
     static constexpr int kWaves = 4;
+    using Tile = PmLds;
     using Lds = PmLds;
     struct Acc {
         double x, y, z, m, h, zi;
@@ -1395,33 +1430,47 @@ struct PmPolicy {
 };
 
 template <class P, int kPer>
-__device__ __forceinline__ bool policy_skips(const typename P::Lds& S, const Tree& T, const GroupBox& g, int a,
+__device__ __forceinline__ bool policy_skips(const typename P::Lds* S, const Tree& T, const GroupBox& g, int a,
                                              const WalkOut& O) {
-    if constexpr (P::kOpenAll) return P::template skip_node<kPer>(S, T, g, a, O);
+    if constexpr (P::kOpenAll) return P::template skip_node<kPer>(*S, T, g, a, O);
     else if constexpr (P::kSkipEmpty) return T.wf[8 * a].w == 0.f;
     else return false;
 }
 
-template <class Pol, int kPer, bool kSoft>
-__device__ __forceinline__ void walk_group(typename Pol::Lds& S, const Tree& T, const Groups& Gr, const WalkOut& O,
-                                           const int4 gd, float theta2, float eps2, float h2, float hinv) {
-    const int lane = threadIdx.x;
-    const int count = gd.y;
-    if (count <= 0) return;
+// orders a wave's LDS accesses around it (LDS serves a wave's accesses in
+// order, so no wait is needed between its lanes)
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
-    // ---- targets ----
-    // A group of count < 64 targets gives each target sub = min(kMaxSub,
-    // 64 / count) lanes: lane = part * count + slot, and part k of a target
-    // takes every sub-th entry of each tile (lanes with part >= sub repeat
-    // work that is not used).  The parts are summed at the end.
-    const int sub = count * 2 > kW ? 1 : (kW / count < kMaxSub ? kW / count : kMaxSub);
-    const int slot = lane % count;
-    const int part = lane / count;
+// Targets of a group: a group of count < 64 targets gives each target
+// sub = min(kMaxSub, 64 / count) lanes: lane = part * count + slot, and part k
+// of a target takes every sub-th entry of each tile (lanes with part >= sub
+// repeat work that is not used).  The parts are summed at the end.
+struct GroupSetup {
+    GroupBox gb;
+    Target tg;
+    float gh2;                 // multipoles only beyond every softening length of the group and the node
+    int count, sub, slot, part;
+};
+
+template <class Pol, int kPer, bool kSoft>
+__device__ __forceinline__ GroupSetup group_setup(const Tree& T, const Groups& Gr, const WalkOut& O, const int4 gd,
+                                                  float eps2, int lane) {
+    GroupSetup U;
+    const int count = gd.y;
+    U.count = count;
+    U.sub = count * 2 > kW ? 1 : (kW / count < kMaxSub ? kW / count : kMaxSub);
+    U.slot = lane % count;
+    U.part = lane / count;
     // every lane holds some target of the group (no position list: all active)
-    const int p_i = Gr.act_pos ? Gr.act_pos[gd.x + slot] : gd.x + slot;
+    const int p_i = Gr.act_pos ? Gr.act_pos[gd.x + U.slot] : gd.x + U.slot;
     const double4 xi = T.spos[p_i];
     const float4 vi = T.svf[p_i];
-    GroupBox gb = group_box(xi.x, xi.y, xi.z);
+    GroupBox& gb = U.gb;
+    gb = group_box(xi.x, xi.y, xi.z);
     if (kPer == kEwald) {
         // images about a multiple of half the box: its cut lies on the faces
         // of the root's children (the root of a periodic tree is the box)
@@ -1430,7 +1479,7 @@ __device__ __forceinline__ void walk_group(typename Pol::Lds& S, const Tree& T, 
         gb.oy = hb * rint(gb.cy / hb);
         gb.oz = hb * rint(gb.cz / hb);
     }
-    Target tg;
+    Target& tg = U.tg;
     tg.tx = (float)(xi.x - gb.ox);
     tg.ty = (float)(xi.y - gb.oy);
     tg.tz = (float)(xi.z - gb.oz);
@@ -1439,22 +1488,24 @@ __device__ __forceinline__ void walk_group(typename Pol::Lds& S, const Tree& T, 
     tg.g0z = (float)(gb.cz - gb.oz);
     tg.h = kSoft ? T.sh[p_i] : 0.f;
     tg.hinv = kSoft ? 1.f / tg.h : 0.f;
-    // multipoles only beyond every softening length of the group and the node
-    const float gh2 = kSoft ? ag_wave_max(tg.h * tg.h) : eps2;
+    U.gh2 = kSoft ? ag_wave_max(tg.h * tg.h) : eps2;
     tg.vx = vi.x;
     tg.vy = vi.y;
     tg.vz = vi.z;
     tg.p = p_i;
     tg.grp = Pol::kGroupSum && fmaxf(fmaxf(gb.hx, gb.hy), gb.hz) <= O.ewald_grp;
     gb.amin = O.rel_a ? ag_wave_min(O.rel_a[T.perm[p_i]]) : 0.f;
-    typename Pol::Acc acc;
-    acc.zero();
-    if constexpr (Pol::kOpenAll) Pol::template start<kPer>(S, T, O, gd, tg, acc, part, slot, count);
+    return U;
+}
 
-    uint64_t n_pp = 0, n_pn = 0;
-
-    // ---- traversal state ----
-    const int root = T.sys_root[gd.z];
+// One wave walks the tree for a group and hands every full tile of accepted
+// nodes or of particles (64 list entries, the list's last ones first), and at
+// the end the two remainders, to tile(is_node, list, count).  The order of the
+// tiles and of the entries in them depends on the tree and the group alone.
+template <class Pol, int kPer, bool kSoft, class TileFn>
+__device__ __forceinline__ void traverse(ListLds& S, const typename Pol::Lds* P, const Tree& T, const WalkOut& O,
+                                         const GroupBox& gb, float gh2, int root, int lane, float theta2, float eps2,
+                                         TileFn tile) {
     int ca = 0, cb = 0;          // cursor range [ca, cb)
     int ps = 0, pc = 0;          // particles still to be listed from an opened leaf
     if (lane == 0 && root >= 0) {
@@ -1463,22 +1514,6 @@ __device__ __forceinline__ void walk_group(typename Pol::Lds& S, const Tree& T, 
     }
     int sp = 0;                  // stack depth (uniform)
     int npend = 0, ppend = 0;    // list fills (uniform)
-
-    auto flush_particles = [&](int base, int cnt) {
-        if (lane < cnt) Pol::template stage_particle<kPer>(S, T, gb, lane, S.plist[base + lane], O);
-        __syncthreads();
-        Pol::template particles<kPer, kSoft>(S, cnt, tg, acc, h2, hinv, part, sub, O);
-        n_pp += (uint64_t)cnt;
-        __syncthreads();
-    };
-    auto flush_nodes = [&](int base, int cnt) {
-        if (lane < cnt) Pol::template stage_node<kPer>(S, T, gb, lane, S.nlist[base + lane], O);
-        __syncthreads();
-        Pol::nodes(S, cnt, tg, acc, part, sub, O);
-        n_pn += (uint64_t)cnt;
-        __syncthreads();
-    };
-
     int64_t iters = 0;
     for (;;) {
         // every step tests a node or lists particles, so the loop ends within
@@ -1502,7 +1537,7 @@ __device__ __forceinline__ void walk_group(typename Pol::Lds& S, const Tree& T, 
                 }
                 sp -= take;
             }
-            __syncthreads();
+            wave_sync();
         }
         const bool walking = (ca < cb) && pc == 0;
         if (__ballot(walking || pc > 0) == 0) break;
@@ -1515,7 +1550,7 @@ __device__ __forceinline__ void walk_group(typename Pol::Lds& S, const Tree& T, 
             const int a = ca;
             const int4 L = T.link[a];
             const bool leaf = (L.w & 0x100) != 0;
-            if (policy_skips<Pol, kPer>(S, T, gb, a, O)) {
+            if (policy_skips<Pol, kPer>(P, T, gb, a, O)) {
                 ca = L.x;                  // nothing below this node matters
             } else {
                 const bool acc_ok =
@@ -1565,34 +1600,82 @@ __device__ __forceinline__ void walk_group(typename Pol::Lds& S, const Tree& T, 
             }
         }
         // 3c. particles of opened leaves -> particle list, as room allows
-        {
+        if (__ballot(pc > 0) != 0) {
             const int want = pc;
             const int incl = ag_wave_incl_scan(want);
             const int excl = incl - want;
-            const int total = __shfl(incl, 63, 64);
-            if (total > 0) {
-                const int room = kPCap - ppend;
-                int give = room - excl;
-                give = give < 0 ? 0 : (give > want ? want : give);
-                for (int k = 0; k < give; ++k) S.plist[ppend + excl + k] = ps + k;
-                ps += give;
-                pc -= give;
-                ppend += total < room ? total : room;
-            }
+            const int total = __builtin_amdgcn_readlane(incl, 63);
+            const int room = kPCap - ppend;
+            int give = room - excl;
+            give = give < 0 ? 0 : (give > want ? want : give);
+            for (int k = 0; k < give; ++k) S.plist[ppend + excl + k] = ps + k;
+            ps += give;
+            pc -= give;
+            ppend += total < room ? total : room;
         }
-        __syncthreads();
-        // 4. evaluate full tiles
+        wave_sync();
+        // 4. full tiles
         while (npend >= kW) {
             npend -= kW;
-            flush_nodes(npend, kW);
+            tile(true, S.nlist + npend, kW);
         }
         while (ppend >= kW) {
             ppend -= kW;
-            flush_particles(ppend, kW);
+            tile(false, S.plist + ppend, kW);
         }
     }
-    if (npend > 0) flush_nodes(0, npend);
-    if (ppend > 0) flush_particles(0, ppend);
+    if (npend > 0) tile(true, S.nlist, npend);
+    if (ppend > 0) tile(false, S.plist, ppend);
+}
+
+__device__ __forceinline__ void count_group(const WalkOut& O, uint64_t n_pp, uint64_t n_pn, int count) {
+    atomicAdd(&O.stats[0], (unsigned long long)(n_pp * (uint64_t)count));
+    atomicAdd(&O.stats[1], (unsigned long long)(n_pn * (uint64_t)count));
+    atomicAdd(&O.stats[2], (unsigned long long)count);
+    atomicAdd(&O.stats[3], 1ull);
+}
+
+// Walk the tree for one group of targets by one wave: every tile is staged
+// and evaluated as soon as it is full.
+template <class Pol, int kPer, bool kSoft>
+__device__ __forceinline__ void walk_group(typename Pol::Lds& S, const Tree& T, const Groups& Gr, const WalkOut& O,
+                                           const int4 gd, float theta2, float eps2, float h2, float hinv) {
+    const int lane = ag_lane();
+    if (gd.y <= 0) return;
+    const GroupSetup U = group_setup<Pol, kPer, kSoft>(T, Gr, O, gd, eps2, lane);
+    const Target tg = U.tg;
+    const int count = U.count, sub = U.sub, slot = U.slot, part = U.part;
+    typename Pol::Acc acc;
+    acc.zero();
+    if constexpr (Pol::kOpenAll) Pol::template start<kPer>(S, T, O, gd, tg, acc, part, slot, count);
+
+    uint64_t n_pp = 0, n_pn = 0;
+    traverse<Pol, kPer, kSoft>(S, &S, T, O, U.gb, U.gh2, T.sys_root[gd.z], lane, theta2, eps2,
+                               [&](bool node, const int* list, int cnt) {
+        if (lane < cnt) {
+            if (node) Pol::template stage_node<kPer>(S, T, U.gb, lane, list[lane], O);
+            else Pol::template stage_particle<kPer>(S, T, U.gb, lane, list[lane], O);
+        }
+        wave_sync();
+        if constexpr (Pol::kOpenAll) {
+            if (!node) Pol::template particles<kPer, kSoft>(S, cnt, tg, acc, h2, hinv, part, sub, O);
+        } else {
+            bool done = false;
+            if constexpr (Pol::kGroupSum) {
+                done = !tg.grp;
+                if (done) Pol::target_entries(S, cnt, tg, acc, part, sub, O);
+            }
+            if (!done) {
+                typename Pol::Sum F;
+                if (node) Pol::nodes(S, cnt, tg, F, part, sub, O);
+                else Pol::template particles<kPer, kSoft>(S, cnt, tg, F, h2, hinv, part, sub, O);
+                acc.fold(F);
+            }
+        }
+        if (node) n_pn += (uint64_t)cnt;
+        else n_pp += (uint64_t)cnt;
+        wave_sync();
+    });
 
     if (Pol::kGroupSum && tg.grp) {
         // every lane summed its own share of the entries: add all 64
@@ -1603,59 +1686,282 @@ __device__ __forceinline__ void walk_group(typename Pol::Lds& S, const Tree& T, 
         // sum the parts of every target in LDS (the walk lists are free now)
         static_assert(sizeof(typename Pol::Lds) >= sizeof(typename Pol::Acc) * kW, "LDS too small");
         typename Pol::Acc* red = reinterpret_cast<typename Pol::Acc*>(&S);
-        __syncthreads();
+        wave_sync();
         red[lane] = acc;
-        __syncthreads();
+        wave_sync();
         if (part == 0)
             for (int j = 1; j < sub; ++j) acc.add(red[slot + j * count]);
-        __syncthreads();
+        wave_sync();
     }
-    if (part == 0) Pol::finish(T, O, acc, p_i, tg);
-    if (lane == 0 && O.stats) {
-        atomicAdd(&O.stats[0], (unsigned long long)(n_pp * (uint64_t)count));
-        atomicAdd(&O.stats[1], (unsigned long long)(n_pn * (uint64_t)count));
-        atomicAdd(&O.stats[2], (unsigned long long)count);
-        atomicAdd(&O.stats[3], 1ull);
+    if (part == 0) Pol::finish(T, O, acc, tg.p, tg);
+    if (lane == 0 && O.stats) count_group(O, n_pp, n_pn, count);
+}
+
+// ---- one group walked by a team of waves ----
+// With fewer groups than the device has waves, a walk by single waves lasts as
+// long as its longest group (3000 particles: 70 groups on 1024 SIMDs, 0.74 ms).
+// A team (of 4 to 16 waves) walks one group: its first wave traverses the tree and queues the
+// full tiles in LDS, the others (and the first when the queue is full or the
+// traversal done) take tiles from the queue, stage and evaluate them, and fold
+// the tile sums into the group's sums in LDS in the order of the queue.  Tiles,
+// their order and every rounding are those of a single wave's walk, so the
+// results are the same bit for bit whichever way a group is walked.
+constexpr int kRing = 16;   // queued tiles
+constexpr int kMinTeam = 4; // waves of the smallest team
+template <class Pol>
+struct TeamLds {
+    ListLds lists;
+    typename Pol::Word acc[Pol::kWords][kW];   // the group's sums, one lane each
+    int ring[kRing][kW];    // queued tiles: list entries ...
+    int info[kRing];        // ... and their number, negative for nodes
+    int full[kRing];        // slot holds a tile that no wave has taken yet
+    int head, tail, done;   // next tile to take, tiles queued, traversal finished
+    int turn;               // next tile whose sums are folded
+    int g;                  // the team's group
+    int arrived;            // waves that have come to the team's barriers so far
+};
+
+// (a word that other waves of the team write: one lane's reading of it, so
+// that the whole wave takes the same branch)
+__device__ __forceinline__ int lds_get(const int* p) {
+    return __builtin_amdgcn_readfirstlane(__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+}
+__device__ __forceinline__ void lds_put(int* p, int v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void team_release() { __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local"); }
+__device__ __forceinline__ void team_acquire() { __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local"); }
+
+// barrier of the ts waves of a team, all resident on one CU; orders LDS
+__device__ __forceinline__ void team_barrier(int* arrived, int ts) {
+    team_release();
+    int a = 0;
+    if (ag_lane() == 0) a = __hip_atomic_fetch_add(arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    const int all = (__builtin_amdgcn_readfirstlane(a) / ts + 1) * ts;
+    while (lds_get(arrived) < all) __builtin_amdgcn_s_sleep(1);
+    team_acquire();
+}
+
+template <class Pol, int kPer, bool kSoft>
+__device__ __forceinline__ void walk_group_team(TeamLds<Pol>& S, typename Pol::Tile& st, int wave, int ts,
+                                                const Tree& T, const Groups& Gr, const WalkOut& O, const int4 gd,
+                                                float theta2, float eps2, float h2, float hinv) {
+    constexpr int kN = Pol::kWords;
+    const int lane = ag_lane();
+    if (gd.y <= 0) {   // uniform over the team
+        team_barrier(&S.arrived, ts);
+        return;
+    }
+    const GroupSetup U = group_setup<Pol, kPer, kSoft>(T, Gr, O, gd, eps2, lane);
+    const Target tg = U.tg;
+    const int count = U.count, sub = U.sub, slot = U.slot, part = U.part;
+    for (int k = wave; k < kN; k += ts) S.acc[k][lane] = 0;
+    if (wave == 0) {
+        if (lane < kRing) S.full[lane] = 0;
+        if (lane == 0) S.head = S.tail = S.done = S.turn = 0;
+    }
+    team_barrier(&S.arrived, ts);
+
+    // the queue's tile t: staged, evaluated and, in its turn, folded
+    auto evaluate = [&](int t) {
+        const int s = t % kRing;
+        const int info = lds_get(&S.info[s]);
+        const bool node = info < 0;
+        const int cnt = node ? -info : info;
+        const int id = S.ring[s][lane];
+        team_release();              // the slot is read ...
+        if (lane == 0) lds_put(&S.full[s], 0);   // ... before it is given back
+        if (lane < cnt) {
+            if (node) Pol::template stage_node<kPer>(st, T, U.gb, lane, id, O);
+            else Pol::template stage_particle<kPer>(st, T, U.gb, lane, id, O);
+        }
+        wave_sync();
+        typename Pol::Sum F;
+        const bool in_turn = Pol::kGroupSum && !tg.grp;   // terms go straight into the group's sums
+        if (!in_turn) {
+            if (node) Pol::nodes(st, cnt, tg, F, part, sub, O);
+            else Pol::template particles<kPer, kSoft>(st, cnt, tg, F, h2, hinv, part, sub, O);
+        }
+        // every earlier tile is held by a wave that does not wait for this one
+        while (lds_get(&S.turn) != t) __builtin_amdgcn_s_sleep(1);
+        team_acquire();
+        if constexpr (Pol::kGroupSum) {
+            if (in_turn) {
+                typename Pol::Acc a;
+#pragma unroll
+                for (int k = 0; k < kN; ++k) a.v[k] = S.acc[k][lane];
+                Pol::target_entries(st, cnt, tg, a, part, sub, O);
+#pragma unroll
+                for (int k = 0; k < kN; ++k) S.acc[k][lane] = a.v[k];
+            }
+        }
+        if (!in_turn) {
+            const float* f = reinterpret_cast<const float*>(&F);
+#pragma unroll
+            for (int k = 0; k < kN; ++k) S.acc[k][lane] += (typename Pol::Word)f[k];
+        }
+        team_release();
+        if (lane == 0) lds_put(&S.turn, t + 1);
+        wave_sync();
+    };
+
+    uint64_t n_pp = 0, n_pn = 0;
+    if (wave == 0) {
+        int tail = 0;
+        traverse<Pol, kPer, kSoft>(S.lists, (const typename Pol::Lds*)nullptr, T, O, U.gb, U.gh2, T.sys_root[gd.z],
+                                   lane, theta2, eps2, [&](bool node, const int* list, int cnt) {
+            const int s = tail % kRing;
+            // a full queue: take its oldest tile that no wave has asked for,
+            // or wait for the wave that has asked for the slot's
+            while (lds_get(&S.full[s]) != 0) {
+                int t = -1;
+                if (lane == 0) {
+                    int h = lds_get(&S.head);
+                    if (h < tail && __hip_atomic_compare_exchange_strong(&S.head, &h, h + 1, __ATOMIC_RELAXED,
+                                                                         __ATOMIC_RELAXED,
+                                                                         __HIP_MEMORY_SCOPE_WORKGROUP))
+                        t = h;
+                }
+                t = __builtin_amdgcn_readfirstlane(t);
+                if (t >= 0) {
+                    team_acquire();
+                    evaluate(t);
+                } else {
+                    __builtin_amdgcn_s_sleep(1);
+                }
+            }
+            if (lane < cnt) S.ring[s][lane] = list[lane];
+            if (lane == 0) {
+                lds_put(&S.info[s], node ? -cnt : cnt);
+                lds_put(&S.full[s], 1);
+            }
+            team_release();
+            ++tail;
+            if (lane == 0) lds_put(&S.tail, tail);
+            if (node) n_pn += (uint64_t)cnt;
+            else n_pp += (uint64_t)cnt;
+            wave_sync();
+        });
+        team_release();
+        if (lane == 0) lds_put(&S.done, 1);
+    }
+    // take tiles until the traversal is done and none is left
+    for (;;) {
+        int t = 0;
+        if (lane == 0) t = __hip_atomic_fetch_add(&S.head, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        t = __builtin_amdgcn_readfirstlane(t);
+        bool any = true;
+        while (lds_get(&S.tail) <= t) {   // the traversal goes on without this wave
+            if (lds_get(&S.done) != 0) {
+                team_acquire();
+                any = lds_get(&S.tail) > t;   // (the last tiles are queued before done is set)
+                break;
+            }
+            __builtin_amdgcn_s_sleep(2);
+        }
+        if (!any) break;
+        team_acquire();
+        evaluate(t);
+    }
+    team_barrier(&S.arrived, ts);
+    if (wave == 0) {
+        typename Pol::Acc acc;
+        typename Pol::Word* a = reinterpret_cast<typename Pol::Word*>(&acc);
+#pragma unroll
+        for (int k = 0; k < kN; ++k) a[k] = S.acc[k][lane];
+        if (Pol::kGroupSum && tg.grp) {
+            Pol::wave_sum(acc);
+        } else if (part == 0) {
+            for (int j = 1; j < sub; ++j)
+#pragma unroll
+                for (int k = 0; k < kN; ++k) a[k] += S.acc[k][slot + j * count];
+        }
+        if (part == 0) Pol::finish(T, O, acc, tg.p, tg);
+        if (lane == 0 && O.stats) count_group(O, n_pp, n_pn, count);
     }
 }
 
-// Persistent walk: each workgroup (one wave) pops groups from eight work
-// queues, one per contiguous eighth of the (Morton-ordered) group list.  A
-// workgroup starts on queue blockIdx % 8 -- the XCD the hardware dispatches
-// it to, so spatially neighbouring groups share that XCD's L2 -- and steals
-// from the other queues when its own runs dry.  The register budget is held
-// to 128 VGPRs (four waves per SIMD); the few values this spills live
-// outside the interaction loops.
+// Next group of a persistent walk: eight work queues, one per contiguous
+// eighth of the (Morton-ordered) group list.  A workgroup starts on queue
+// blockIdx % 8 -- the XCD the hardware dispatches it to, so spatially
+// neighbouring groups share that XCD's L2 -- and steals from the other queues
+// when its own runs dry (q counts the queues it has left).
+__device__ __forceinline__ int pop_group(int* __restrict__ qctr, int n_groups, int& q) {
+    const int home = blockIdx.x & 7;
+    while (q < 8) {
+        const int qq = (home + q) & 7;
+        const int lo = (int)((int64_t)n_groups * qq / 8);
+        const int hi = (int)((int64_t)n_groups * (qq + 1) / 8);
+        const int k = atomicAdd(&qctr[qq], 1);
+        if (lo + k < hi) return lo + k;
+        ++q;
+    }
+    return -1;
+}
+
+// Persistent walk by single waves, one per workgroup (the neighbour and Price
+// & Monaghan walks).
 template <class Pol, int kPer, bool kSoft = false>
 __global__ void __launch_bounds__(kW, Pol::kWaves) k_walk(Tree T, Groups Gr, WalkOut O, int* __restrict__ qctr,
                                              float theta2, float eps2, float h2, float hinv) {
     __shared__ typename Pol::Lds S;
-    __shared__ int s_g;
     const int n_groups = Gr.hdr[0];
-    const int home = blockIdx.x & 7;
     int q = 0;
     for (;;) {
-        if (threadIdx.x == 0) {
-            int g = -1;
-            while (q < 8) {
-                const int qq = (home + q) & 7;
-                const int lo = (int)((int64_t)n_groups * qq / 8);
-                const int hi = (int)((int64_t)n_groups * (qq + 1) / 8);
-                const int k = atomicAdd(&qctr[qq], 1);
-                if (lo + k < hi) {
-                    g = lo + k;
-                    break;
-                }
-                ++q;
-            }
-            s_g = g;
-        }
-        __syncthreads();
-        const int g = s_g;
-        __syncthreads();
+        int g = -1;
+        if (threadIdx.x == 0) g = pop_group(qctr, n_groups, q);
+        g = __builtin_amdgcn_readfirstlane(g);
         if (g < 0) break;
         walk_group<Pol, kPer, kSoft>(S, T, Gr, O, Gr.grp[g], theta2, eps2, h2, hinv);
+        wave_sync();
+    }
+}
+
+// Persistent walk by workgroups of W waves, which walk groups each on its own
+// or in teams, by the number of groups the device finds.  The register budget
+// is held to 128 VGPRs (four waves per SIMD); the few values this spills live
+// outside the interaction loops.
+struct TeamRule {
+    int solo_above, teams_above;   // more groups than this: single waves; teams of `mid` waves; else of W waves
+    int mid;
+};
+template <class Pol, int kPer, bool kSoft, int W>
+__global__ void __launch_bounds__(W * kW, Pol::kWaves) k_walk_team(Tree T, Groups Gr, WalkOut O,
+                                             int* __restrict__ qctr, TeamRule R,
+                                             float theta2, float eps2, float h2, float hinv) {
+    using Solo = typename Pol::Lds;
+    using Tile = typename Pol::Tile;
+    using Team = TeamLds<Pol>;
+    constexpr size_t kTeamBytes = W * sizeof(Tile) + W / kMinTeam * sizeof(Team);
+    constexpr size_t kBytes = W * sizeof(Solo) > kTeamBytes ? W * sizeof(Solo) : kTeamBytes;
+    __shared__ __align__(16) char s_mem[kBytes];   // one or the other, never both
+    const int n_groups = Gr.hdr[0];
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    int q = 0;
+    if (n_groups > R.solo_above) {
+        for (;;) {
+            int g = -1;
+            if (ag_lane() == 0) g = pop_group(qctr, n_groups, q);
+            g = __builtin_amdgcn_readfirstlane(g);
+            if (g < 0) break;
+            walk_group<Pol, kPer, kSoft>(reinterpret_cast<Solo*>(s_mem)[wave], T, Gr, O, Gr.grp[g], theta2, eps2, h2,
+                                         hinv);
+            wave_sync();
+        }
+    } else {
+        const int ts = n_groups > R.teams_above ? R.mid : W;
+        Team& S = reinterpret_cast<Team*>(s_mem + W * sizeof(Tile))[wave / ts];
+        Tile& st = reinterpret_cast<Tile*>(s_mem)[wave];
+        const int me = wave % ts;
+        if (me == 0 && ag_lane() == 0) S.arrived = 0;
         __syncthreads();
+        for (;;) {
+            if (me == 0 && ag_lane() == 0) S.g = pop_group(qctr, n_groups, q);
+            team_barrier(&S.arrived, ts);
+            const int g = lds_get(&S.g);
+            if (g < 0) break;
+            walk_group_team<Pol, kPer, kSoft>(S, st, me, ts, T, Gr, O, Gr.grp[g], theta2, eps2, h2, hinv);
+        }
     }
 }
 
@@ -2139,13 +2445,43 @@ static Tree make_tree(ag_ctx* c) {
     return T;
 }
 
+static int device_cus(ag_ctx* c) {
+    int cus = 256;
+    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device);
+    return cus;
+}
+
 static int walk_grid(ag_ctx* c, int64_t max_groups) {
-    int dev_cus = 256;
-    (void)hipDeviceGetAttribute(&dev_cus, hipDeviceAttributeMultiprocessorCount, c->device);
-    int64_t blocks = (int64_t)dev_cus * c->walk_waves_per_cu;
+    int64_t blocks = (int64_t)device_cus(c) * c->walk_waves_per_cu;
     if (blocks > max_groups) blocks = (max_groups + 7) / 8 * 8;
     if (blocks < 8) blocks = 8;
     return (int)blocks;
+}
+
+// A walk by workgroups of Pol::kTeamWaves waves, one workgroup resident per CU
+// (AG_OPT_WALK_WAVES_PER_CU in whole workgroups, at least one).  How the groups are walked
+// goes by how many there are for the P waves launched, read on the device:
+//   above 4 P   single waves: they keep every lane at interactions, and the
+//               last groups' tail is short (2^20 particles, 23 000 groups:
+//               2.99 ms per step, 3.7 ms in teams of 8)
+//   above P/4   teams of 4, whose traversing wave keeps three evaluating
+//               (200 000 particles, 4500 groups: 0.84 ms per step, 0.96 by
+//               single waves, 0.98 in teams of 8); of 8 with the relative
+//               opening test, where a group's cost goes by its smallest
+//               |a_old| and the longest ones set the time (180 000: 1.51 ms
+//               in teams of 8, 1.79 of 4, 4.1 by single waves)
+//   else        the whole workgroup (3000 particles, 70 groups: 0.30 ms per
+//               step, 0.34 in teams of 8, 0.43 of 4, 0.92 by single waves)
+template <class Pol, int kPer, bool kSoft = false>
+static void launch_walk(ag_ctx* c, int64_t max_groups, const Groups& Gr, const WalkOut& O, int32_t* qctr,
+                        float theta2, float eps2, float h2, float hinv) {
+    constexpr int W = Pol::kTeamWaves;
+    int64_t blocks = (int64_t)device_cus(c) * std::max(1, c->walk_waves_per_cu / W);
+    const int waves = (int)(blocks * W);
+    if (blocks > max_groups) blocks = (max_groups + 7) / 8 * 8;
+    const TeamRule R{4 * waves, waves / 4, O.rel_a ? Pol::kRelTeam : kMinTeam};
+    hipLaunchKernelGGL((k_walk_team<Pol, kPer, kSoft, W>), dim3((unsigned)blocks), dim3(W * kW), 0, c->stream,
+                       make_tree(c), Gr, O, qctr, R, theta2, eps2, h2, hinv);
 }
 
 // Ewald table: spacing box / 64 over the octant [0, box / 2]^3 of the cell
@@ -2310,32 +2646,20 @@ int ag_launch_eval(ag_ctx* c, const int32_t* idx, int64_t n_act, double theta, d
     }
     const float th = (float)theta;
     const float e2 = (float)(eps * eps);
-    const unsigned grid = (unsigned)walk_grid(c, mg);
     int32_t* qctr = c->grp_hdr.as<int32_t>() + 8;
     {
         PhaseScope phase(c, AG_PHASE_WALK);
-        const Tree T = make_tree(c);
-        const float h2 = e2, hi = (float)(1.0 / eps);
-        hipStream_t st = c->stream;
+        const float hi = (float)(1.0 / eps);
         if (c->tree_soft) {   // per-particle softening lengths
-            if (ewald)
-                hipLaunchKernelGGL((k_walk<ForwardPolicy, kEwald, true>), dim3(grid), dim3(kW), 0, st, T, Gr, O, qctr,
-                                   th * th, e2, h2, hi);
-            else if (c->box > 0.0)
-                hipLaunchKernelGGL((k_walk<ForwardPolicy, kNear, true>), dim3(grid), dim3(kW), 0, st, T, Gr, O, qctr,
-                                   th * th, e2, h2, hi);
-            else
-                hipLaunchKernelGGL((k_walk<ForwardPolicy, kOpen, true>), dim3(grid), dim3(kW), 0, st, T, Gr, O, qctr,
-                                   th * th, e2, h2, hi);
+            if (ewald) launch_walk<ForwardPolicy, kEwald, true>(c, mg, Gr, O, qctr, th * th, e2, e2, hi);
+            else if (c->box > 0.0) launch_walk<ForwardPolicy, kNear, true>(c, mg, Gr, O, qctr, th * th, e2, e2, hi);
+            else launch_walk<ForwardPolicy, kOpen, true>(c, mg, Gr, O, qctr, th * th, e2, e2, hi);
         } else if (ewald) {
-            hipLaunchKernelGGL((k_walk<ForwardPolicy, kEwald>), dim3(grid), dim3(kW), 0, st, T, Gr, O, qctr, th * th,
-                               e2, h2, hi);
+            launch_walk<ForwardPolicy, kEwald>(c, mg, Gr, O, qctr, th * th, e2, e2, hi);
         } else if (c->box > 0.0) {
-            hipLaunchKernelGGL((k_walk<ForwardPolicy, kNear>), dim3(grid), dim3(kW), 0, st, T, Gr, O, qctr, th * th,
-                               e2, h2, hi);
+            launch_walk<ForwardPolicy, kNear>(c, mg, Gr, O, qctr, th * th, e2, e2, hi);
         } else {
-            hipLaunchKernelGGL((k_walk<ForwardPolicy, kOpen>), dim3(grid), dim3(kW), 0, st, T, Gr, O, qctr, th * th,
-                               e2, h2, hi);
+            launch_walk<ForwardPolicy, kOpen>(c, mg, Gr, O, qctr, th * th, e2, e2, hi);
         }
     }
     if (ewald && (acc || tidal)) {
@@ -2346,8 +2670,7 @@ int ag_launch_eval(ag_ctx* c, const int32_t* idx, int64_t n_act, double theta, d
         WalkOut E = O;
         E.stats = nullptr;
         E.rel_a = nullptr;
-        hipLaunchKernelGGL((k_walk<EwaldPolicy, kEwald>), dim3(grid), dim3(kW), 0, c->stream, make_tree(c), Gr, E,
-                           c->ewald_q.as<int32_t>(), 0.f, 0.f, e2, (float)(1.0 / eps));
+        launch_walk<EwaldPolicy, kEwald>(c, mg, Gr, E, c->ewald_q.as<int32_t>(), 0.f, 0.f, e2, (float)(1.0 / eps));
     }
     return AG_OK;
 }
@@ -2414,8 +2737,7 @@ int ag_launch_backward(ag_ctx* c, const int32_t* idx, int64_t n_act, const doubl
     O.tin = tin;
     const float th = (float)theta;
     const float e2 = (float)(eps * eps);
-    hipLaunchKernelGGL((k_walk<AdjointPolicy, kOpen>), dim3((unsigned)walk_grid(c, mg)), dim3(kW), 0, st,
-                       make_tree(c), Gr,
-                       O, c->grp_hdr.as<int32_t>() + 8, th * th, e2, e2, (float)(1.0 / eps));
+    launch_walk<AdjointPolicy, kOpen>(c, mg, Gr, O, c->grp_hdr.as<int32_t>() + 8, th * th, e2, e2,
+                                      (float)(1.0 / eps));
     return AG_OK;
 }
