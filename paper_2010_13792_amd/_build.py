@@ -23,7 +23,7 @@ LIB = os.path.join(HERE, "libadaptgrav.so")
 PEAK_SRC = os.path.join(HERE, "peak", "fma_peak.hip")
 PEAK_EXE = os.path.join(HERE, "peak", "fma_peak")
 
-SOURCES = ["ag_api.hip", "k_direct.hip", "k_step.hip", "k_tree.hip", "k_walk.hip"]
+SOURCES = ["ag_api.hip", "k_direct.hip", "k_step.hip", "k_tree.hip", "k_near.hip", "k_walk.hip"]
 EXTRA = {"k_step.hip": ["-ffp-contract=off"]}
 
 ARCH = "gfx950"

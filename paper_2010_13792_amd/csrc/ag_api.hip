@@ -198,10 +198,10 @@ extern "C" int ag_destroy(ag_ctx* c) {
     (void)hipStreamSynchronize(c->stream);
     DevBuf* bufs[] = {&c->keys[0], &c->keys[1], &c->vals[0], &c->vals[1], &c->sort_hist, &c->perm,
                       &c->rank, &c->spos, &c->svf, &c->cdig, &c->cd_min, &c->pos_cnt, &c->pos_off,
-                      &c->scan_tmp, &c->nd_com, &c->nd_lo, &c->nd_hi, &c->nd_link, &c->nd_mp,
+                      &c->scan_tmp, &c->nd_com, &c->nd_lo, &c->nd_hi, &c->nd_slot, &c->nd_link, &c->nd_mp,
                       &c->nd_64, &c->nd_w, &c->nd_wf, &c->in_list, &c->in_cnt, &c->in_off,
                       &c->tree_hdr, &c->lvl_list, &c->leaf_list, &c->leaf_pos, &c->child, &c->sys_off, &c->sys_root, &c->sys_box, &c->act_flag,
-                      &c->act_pos, &c->act_off, &c->grp, &c->grp_hdr, &c->ewald_tab, &c->ewald_q, &c->soft_h, &c->soft_s, &c->rel_a, &c->pm_brk, &c->grp_cnt, &c->grp_off, &c->sys_act, &c->wsorted,
+                      &c->act_pos, &c->act_off, &c->grp, &c->grp_hdr, &c->ewald_tab, &c->soft_h, &c->soft_s, &c->rel_a, &c->grp_cnt, &c->grp_off, &c->sys_act, &c->wsorted,
                       &c->direct_part, &c->tmp_tidal, &c->sel_flag, &c->sel_off, &c->stats, &c->dflags};
     for (DevBuf* b : bufs) ag_release(*b);
     for (PhaseEvents& p : c->timing.pending) {
@@ -715,31 +715,8 @@ extern "C" int ag_pm_lengths(ag_ctx* c, double n_ngb, double* h, double* omega) 
     AG_TRY(check_pm(c, &n_ngb, true));
     if (!h || !omega) return ag_fail(AG_EINVAL, "h and omega must be non-null");
     DeviceGuard g(c->device);
-    AG_TRY(ag_ensure(c, c->pm_brk, (size_t)c->n * (3 * sizeof(double) + sizeof(int32_t)) + kPmSteps * sizeof(int)));
-    // each step counts in a slot of its own (slot 0: the rows the list pass
-    // leaves to the sum walk)
-    int* cnt = reinterpret_cast<int*>(c->pm_brk.as<double>() + 3 * c->n);
-    AG_HIP(hipMemsetAsync(cnt, 0, kPmSteps * sizeof(int), c->stream));
-    AG_TRY(ag_launch_pm_lengths(c, n_ngb, h, omega, 0, 0));
+    AG_TRY(ag_launch_pm_lengths(c, n_ngb, h, omega));
     AG_TRY(check_launch("Price & Monaghan lengths"));
-    int32_t f = 0, n_left = 0;
-    AG_HIP(hipMemcpyAsync(&f, c->dflags.p, sizeof(f), hipMemcpyDeviceToHost, c->stream));
-    AG_HIP(hipMemcpyAsync(&n_left, cnt, sizeof(int), hipMemcpyDeviceToHost, c->stream));
-    AG_HIP(hipStreamSynchronize(c->stream));
-    if ((f & AGF_PMSHORT) && n_left > 0) {
-        // Newton steps of the sum walk until no length moves
-        AG_HIP(hipMemsetAsync(c->dflags.p, 0, sizeof(int32_t), c->stream));
-        int step = 1, moving = 1;
-        for (; step < kPmSteps && moving; ++step) {
-            AG_TRY(ag_launch_pm_lengths(c, n_ngb, h, omega, step, n_left));
-            if (step % 4 == 0 || step == kPmSteps - 1) {
-                AG_HIP(hipMemcpyAsync(&moving, cnt + step, sizeof(int), hipMemcpyDeviceToHost, c->stream));
-                AG_HIP(hipStreamSynchronize(c->stream));
-            }
-        }
-        AG_TRY(check_launch("Price & Monaghan lengths"));
-        if (moving) return ag_fail(AG_EHIP, "Price & Monaghan lengths did not settle");
-    }
     return read_flags(c);
 }
 

@@ -38,11 +38,12 @@ struct DevBuf {
 };
 
 // device-side flag bits (ag_ctx::dflags)
-enum { AGF_BADINDEX = 1, AGF_NONFINITE = 2, AGF_INTERNAL = 4, AGF_PMSHORT = 8 };
+enum { AGF_BADINDEX = 1, AGF_NONFINITE = 2, AGF_INTERNAL = 4 };
 
 constexpr int AG_MAX_LEVEL = 21;   // Morton digits: 21 x 3 bits = 63-bit keys
 constexpr int AG_MAX_SYS = 512;    // batched systems: 3 octal digits of prefix
 constexpr int AG_GROUP = 64;       // targets per walk group = one wave64
+constexpr int kQueueStride = 32;   // i32 between work-queue counters: a cache line each
 
 // level table after the eight i64 header words of tree_hdr (as i32): inner
 // nodes per level, a scatter cursor per level, and the level offsets into
@@ -113,6 +114,7 @@ struct ag_ctx {
     // node arrays, depth-first (pre-order) numbering
     DevBuf nd_com;                // double4: centre of mass x y z, extent L
     DevBuf nd_lo, nd_hi;          // float4: bounding box (rounded outward)
+    DevBuf nd_slot;               // i32 [max_nodes]: inner nodes: their row of child (leaves: unwritten)
     DevBuf nd_link;               // int4: skip (next node after subtree), start, count, level|leafbit
     DevBuf nd_mp;                 // float4 x4: M ux uy uz | Q xx yy zz xy | Q xz yz, Qd xx yy | Qd zz xy xz yz
     DevBuf nd_64;                 // double [25]: FP64 moments (M, c, u, Q, Qd, lo, hi)
@@ -139,10 +141,8 @@ struct ag_ctx {
     DevBuf soft_h;                // f64 per-particle softening lengths, input order
     DevBuf soft_s;                // f32 the same in key order (rounded up)
     DevBuf rel_a;                 // f32 |a| of the previous evaluation, input order (rounded down)
-    DevBuf pm_brk;                // Price & Monaghan lengths: brackets and current lengths (3 n doubles), step counters, rows left to the sum walk (n)
     DevBuf ewald_tab;             // f32 Ewald correction table (5 float4 per point)
-    DevBuf ewald_q;               // i32 [8]: correction walk work-queue counters
-    DevBuf grp_hdr;               // i32: [0] number of groups, [8..15] walk work-queue counters
+    DevBuf grp_hdr;               // i32: [0] number of groups, then two walks' eight work-queue counters, kQueueStride apart
     DevBuf grp_cnt, grp_off;      // i32 [max_nodes (+1)]: groups owned per node, offsets
     DevBuf sys_act;               // i32 [n_sys + 1]
     DevBuf wsorted;               // double4 [n]: adjoint weights in sorted order
@@ -234,8 +234,7 @@ int ag_launch_eval(ag_ctx* c, const int32_t* idx, int64_t n_act, double theta, d
                    double G, double* acc, double* jerk, double* tidal, const int64_t* n_dev = nullptr,
                    int64_t* n_total = nullptr);
 int ag_launch_knn(ag_ctx* c, int32_t k, double scale, double* h_out);
-constexpr int kPmSteps = 257;   // sum walk steps of the lengths (slot 0 unused) and their counters
-int ag_launch_pm_lengths(ag_ctx* c, double n_ngb, double* h, double* omega, int step, int64_t n_left);
+int ag_launch_pm_lengths(ag_ctx* c, double n_ngb, double* h, double* omega);
 // mode 0: Z of every particle into z_out; mode 1: the correction, written to
 // acc for every row (idx null; added with `add`) or added to acc at rows
 // idx[0 .. *n_dev)
@@ -332,6 +331,23 @@ __device__ __forceinline__ double ag_wave_max_f64(double v) {
     v = ag_dpp_max<0x118, 0xF>(v);
     v = ag_dpp_max<0x142, 0xA>(v);
     v = ag_dpp_max<0x143, 0xC>(v);
+    return ag_last_lane_f64(v);
+}
+
+// sum of a double over the wave (every lane gets it), in a fixed order
+template <int C, int RowMask> __device__ __forceinline__ double ag_dpp_sum(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, C, RowMask, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), C, RowMask, 0xF, false);
+    return v + __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+__device__ __forceinline__ double ag_wave_sum_f64(double v) {
+    v = ag_dpp_sum<0x111, 0xF>(v);
+    v = ag_dpp_sum<0x112, 0xF>(v);
+    v = ag_dpp_sum<0x114, 0xF>(v);
+    v = ag_dpp_sum<0x118, 0xF>(v);
+    v = ag_dpp_sum<0x142, 0xA>(v);
+    v = ag_dpp_sum<0x143, 0xC>(v);
     return ag_last_lane_f64(v);
 }
 

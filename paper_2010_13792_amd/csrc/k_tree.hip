@@ -1317,7 +1317,8 @@ __global__ void __launch_bounds__(kThreads) k_level_lists(const int64_t* __restr
                                                           const uint64_t* __restrict__ keys,
                                                           int4* __restrict__ child,
                                                           int32_t* __restrict__ lvl,
-                                                          int32_t* __restrict__ lvl_list) {
+                                                          int32_t* __restrict__ lvl_list,
+                                                          int32_t* __restrict__ nslot) {
     __shared__ int s_off[AG_MAX_LEVEL + 2], s_cnt[AG_MAX_LEVEL + 1], s_base[AG_MAX_LEVEL + 1];
     const int64_t ni = hdr[2];
     if (threadIdx.x == 0) {
@@ -1356,6 +1357,7 @@ __global__ void __launch_bounds__(kThreads) k_level_lists(const int64_t* __restr
         if (node >= 0) {
             const int64_t slot = s_off[l] + s_base[l] + r;
             lvl_list[slot] = node;
+            nslot[node] = (int32_t)slot;
             child[2 * slot] = make_int4(c8[0], c8[1], c8[2], c8[3]);
             child[2 * slot + 1] = make_int4(c8[4], c8[5], c8[6], c8[7]);
         }
@@ -1558,6 +1560,7 @@ int ag_launch_build(ag_ctx* c, int64_t n, const double* x, const double* v, cons
     AG_TRY(ag_ensure(c, c->cd_min, (size_t)cd_tot * sizeof(int32_t)));
     AG_TRY(ag_ensure(c, c->nd_com, max_nodes * 32)); AG_TRY(ag_ensure(c, c->nd_lo, max_nodes * 16));
     AG_TRY(ag_ensure(c, c->nd_hi, max_nodes * 16)); AG_TRY(ag_ensure(c, c->nd_link, max_nodes * 16));
+    AG_TRY(ag_ensure(c, c->nd_slot, max_nodes * 4));
     AG_TRY(ag_ensure(c, c->nd_mp, max_nodes * 64)); AG_TRY(ag_ensure(c, c->nd_64, max_nodes * kM64 * 8));
     AG_TRY(ag_ensure(c, c->in_list, max_nodes * 4)); AG_TRY(ag_ensure(c, c->in_cnt, (n + 1) * 4));
     AG_TRY(ag_ensure(c, c->in_off, (n + 1) * 4));
@@ -1680,7 +1683,8 @@ int ag_launch_build(ag_ctx* c, int64_t n, const double* x, const double* v, cons
     }
     hipLaunchKernelGGL(k_level_lists, dim3(grid_for(inner_bound) < 1024 ? grid_for(inner_bound) : 1024),
                        dim3(kThreads), 0, st, hdr, c->in_list.as<int32_t>(), c->nd_link.as<int4>(), k0,
-                       c->child.as<int4>(), reinterpret_cast<int32_t*>(hdr + 8), c->lvl_list.as<int32_t>());
+                       c->child.as<int4>(), reinterpret_cast<int32_t*>(hdr + 8), c->lvl_list.as<int32_t>(),
+                       c->nd_slot.as<int32_t>());
 
     c->n = n;
     c->n_leaf = n_leaf;

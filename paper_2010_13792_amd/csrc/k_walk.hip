@@ -99,26 +99,6 @@ struct WalkOut {
     int etab_ne;
     float ewald_theta;  // correction walk: opening angle against the nearest image point
     float ewald_grp;    // groups of at most this half extent sum the correction once
-    double* knn_out;    // neighbour lengths (input order)
-    double knn_scale;   // ... each multiplied by this
-    int knn_k;          // which neighbour
-    int64_t knn_n;
-    // Price & Monaghan terms (input order arrays)
-    double pm_ngb;      // > 0: the neighbour walk solves the density condition
-    double pm_G;
-    double* pm_omega;
-    const double* pm_h;
-    double* pm_lo;      // bisection brackets of the lengths (input order)
-    double* pm_hi;
-    double* pm_cur;     // the length the next sum walk evaluates
-    int* pm_active;     // sum walk: lengths still moving after it (list pass: lengths left to it)
-    int32_t* pm_idx;    // list pass: the rows left to the sum walk
-    double pm_hiscale;  // upper end of a bracket: this times the root's diagonal
-    const double* pm_om;
-    const double* pm_z;
-    double* pm_zout;
-    double* pm_acc;
-    bool pm_add;        // correction: added to pm_acc (else written)
     double* dldx;       // adjoint outputs
     double* dldm;
     const double* tin;  // adjoint: tidal tensor rows of the charged targets
@@ -349,7 +329,6 @@ __device__ __forceinline__ void soft_fd(float r2, float h, float hinv, float& f,
 // ---- forward: g, j and S = -T from particle masses and node multipoles ----
 struct ForwardPolicy {
     static constexpr bool kSkipEmpty = false;
-    static constexpr bool kOpenAll = false;
     static constexpr bool kImageMac = false;
     static constexpr bool kGroupSum = false;
     static constexpr int kWaves = 4;   // launch bound: waves per SIMD (128 registers)
@@ -530,7 +509,6 @@ struct AdjAccF {
 };
 struct AdjointPolicy {
     static constexpr bool kSkipEmpty = true;   // nodes without charge add nothing
-    static constexpr bool kOpenAll = false;
     static constexpr bool kImageMac = false;
     static constexpr bool kGroupSum = false;
     static constexpr int kWaves = 3;   // launch bound: waves per SIMD (168 registers)
@@ -781,7 +759,6 @@ __device__ __forceinline__ bool ewald_accept(const GroupBox& g, const double4 c,
 // background that neutralises its own images).
 struct EwaldPolicy {
     static constexpr bool kSkipEmpty = false;
-    static constexpr bool kOpenAll = false;
     static constexpr bool kImageMac = true;
     static constexpr bool kGroupSum = true;
     static constexpr int kWaves = 4;   // launch bound: waves per SIMD (128 registers)
@@ -1010,433 +987,6 @@ struct EwaldPolicy {
     }
 };
 
-// ---- the cubic spline with support 1 for the Price & Monaghan terms ----
-// w(u) and w'(u) with W(r, h) = 8/(pi h^3) w(r/h); and -h^2 dphi/dh =
-// psi(u) + u^2 F(u), where phi(r, h) = psi(r/h)/h is the potential of the
-// spread unit mass and F = h^3 f its force kernel (the 1/u terms cancel):
-//   16 u^2 - 48 u^4 + 192/5 u^5 - 14/5               (u < 1/2)
-//   32 u^2 - 64 u^3 + 48 u^4 - 64/5 u^5 - 16/5        (1/2 <= u < 1), 0 beyond.
-__device__ __forceinline__ double m4_w(double u) {
-    return u < 0.5 ? 1.0 + u * u * (-6.0 + 6.0 * u) : (u < 1.0 ? 2.0 * (1.0 - u) * (1.0 - u) * (1.0 - u) : 0.0);
-}
-__device__ __forceinline__ double m4_wp(double u) {
-    return u < 0.5 ? u * (-12.0 + 18.0 * u) : (u < 1.0 ? -6.0 * (1.0 - u) * (1.0 - u) : 0.0);
-}
-__device__ __forceinline__ double m4_dphi(double u) {
-    const double u2 = u * u;
-    return u < 0.5 ? u2 * (16.0 + u2 * (-48.0 + u * (192.0 / 5.0))) - 14.0 / 5.0
-                   : (u < 1.0 ? u2 * (32.0 + u * (-64.0 + u * (48.0 - u * (64.0 / 5.0)))) - 16.0 / 5.0 : 0.0);
-}
-
-// One step of safeguarded Newton for S(h) = target with S increasing in h:
-// s = S(h), sd = sum u w'(u) (so dS/dh = -sd / h).  The bracket [lo, hi]
-// shrinks to the side of h the sign of S - target gives; the Newton point is
-// taken when it falls strictly inside the bracket (growing h at most
-// twofold), else twice h while h is below the root and the sum has no slope
-// there, else the bracket's midpoint.
-// Returns false once the length is settled, leaving hn = h: the step or the
-// bracket below 2e-14 h (above the rounding noise of a sum of many terms,
-// which keeps a tighter test from ever closing; Newton's last step had
-// already brought h to that noise).
-__device__ __forceinline__ bool pm_newton(double s, double sd, double target, double h, double& lo, double& hi,
-                                          double& hn) {
-    if (s < target) lo = h; else hi = h;
-    hn = h;
-    if (hi - lo <= 2e-14 * hi) return false;
-    double t = sd < 0.0 ? h + (s - target) * h / sd : -1.0;
-    // a settled Newton step is tested first: below an ulp it returns h
-    // itself, which the bracket test would take for a failed step
-    if (sd < 0.0 && fabs(t - h) <= 2e-14 * h) return false;
-    if (s < target && t > 2.0 * h) t = 2.0 * h;
-    if (!(t > lo && t < hi)) t = s < target && sd == 0.0 && 2.0 * h < hi ? 2.0 * h : 0.5 * (lo + hi);
-    hn = t;
-    return true;
-}
-
-// ---- k-th neighbour distance: the length fully adaptive softening follows ----
-// Every node is opened; a node whose box lies farther from the group's box
-// than the group's pruning radius is skipped.  Each target keeps its k
-// smallest squared distances so far in registers, as an ascending list of
-// kCap entries (16, 32 or 64, the smallest that holds k) whose first kCap - k
-// are -inf, so the k-th sits at the fixed last place.  A candidate below it
-// goes to a small buffer in LDS; when any buffer of the wave is full (and
-// after every tile) the buffered values are inserted one by one with the
-// branch-free network L'[i] = max(L[i-1], min(L[i], v)), whose entries are
-// independent of one another (a value not below the last entry leaves the
-// list as it is).  Before the walk the targets take the particles within k
-// sorted positions of the group, which fills every list; the pruning radius
-// is then the largest of the targets' k-th distances, and shrinks after
-// every tile.  Distances are d^2 = (dx^2 + dy^2) + dz^2 with d = x_j - x_i,
-// each operation rounded once.
-constexpr int kKnnBuf = 8;
-struct KnnLds : WalkLds<2> {
-    double buf[kW * kKnnBuf];   // entry b of lane l at [b * 64 + l]
-    double r2;
-    int win_lo, win_hi;   // sorted positions taken before the walk
-};
-// kDensity: the Price & Monaghan density mode of finish (its own kernel, so
-// that the plain lists keep their register budget)
-template <int kCap, bool kDensity = false>
-struct KnnPolicy {
-    static constexpr bool kSkipEmpty = false;
-    static constexpr bool kOpenAll = true;
-    static constexpr bool kImageMac = false;
-    static constexpr bool kGroupSum = false;
-    // the list's registers: 2 kCap of them
-    static constexpr int kWaves = kCap <= 16 ? 4 : (kCap <= 32 ? 3 : 1);
-    using Tile = KnnLds;
-    using Lds = KnnLds;
-    struct Acc {
-        double x, y, z;   // the target
-        double L[kCap];   // ascending; the last entry is the k-th so far
-        int nb;           // buffered candidates
-        __device__ void zero() { nb = 0; }
-        __device__ void add(const Acc&) {}
-    };
-    // hipcc contracts a * b + c into one fma by default: not here.  In a
-    // periodic tree every difference goes to its nearest image first,
-    // d - L rint(d / L) (the division correctly rounded).
-    template <int kPer>
-    __device__ static double dist2(const double4& p, const Acc& A, const WalkOut& O) {
-#pragma clang fp contract(off)
-        double dx = p.x - A.x, dy = p.y - A.y, dz = p.z - A.z;
-        if (kPer) {
-            const double L = O.box;
-            dx = dx - L * rint(dx / L);
-            dy = dy - L * rint(dy / L);
-            dz = dz - L * rint(dz / L);
-        }
-        return (dx * dx + dy * dy) + dz * dz;
-    }
-    __device__ static void insert(Acc& A, double v) {
-#pragma unroll
-        for (int i = kCap - 1; i > 0; --i) A.L[i] = fmax(A.L[i - 1], fmin(A.L[i], v));
-        A.L[0] = fmin(A.L[0], v);
-    }
-    __device__ static void offer(Lds& S, Acc& A, double d2) {
-        if (d2 < A.L[kCap - 1]) {
-            S.buf[A.nb * kW + threadIdx.x] = d2;
-            ++A.nb;
-        }
-    }
-    // every lane inserts its buffered values (called by the whole wave)
-    __device__ static void merge(Lds& S, Acc& A) {
-        const int nbmax = ag_wave_max(A.nb);
-        for (int b = 0; b < nbmax; ++b)
-            insert(A, b < A.nb ? S.buf[b * kW + threadIdx.x] : __builtin_huge_val());
-        A.nb = 0;
-    }
-    __device__ static void check_full(Lds& S, Acc& A) {
-        if (__ballot(A.nb == kKnnBuf) != 0) merge(S, A);
-    }
-    // merge every buffer; radius^2 no target's k-th neighbour lies beyond
-    __device__ static void flush(Lds& S, Acc& A, bool owner) {
-        merge(S, A);
-        const double r2 = ag_wave_max(owner ? A.L[kCap - 1] : 0.0);
-        if (threadIdx.x == 0) S.r2 = r2;
-    }
-    // Both boxes are rounded outward, their gaps are exact in FP64, and the
-    // relative margin covers the rounding of the squares: a skipped node
-    // holds no particle at a computed d^2 <= r2.
-    // Periodic: per axis the gap between two arcs of a circle of length L,
-    // the centres' distance taken the short way round less both half widths
-    // (every node lies inside the box, so no arc crosses the cut).
-    template <int kPer>
-    __device__ static double axis_gap(float lo, float hi, float glo, float ghi, const WalkOut& O) {
-        if (!kPer) return fmax(fmax((double)lo - ghi, (double)glo - hi), 0.0);
-        double c = fabs(0.5 * ((double)lo + hi) - 0.5 * ((double)glo + ghi));
-        c = fmin(c, O.box - c);
-        return fmax(c - 0.5 * (((double)hi - lo) + ((double)ghi - glo)), 0.0);
-    }
-    template <int kPer>
-    __device__ static bool skip_node(const Lds& S, const Tree& T, const GroupBox& g, int a, const WalkOut& O) {
-        const float4 lo = T.lo[a], hi = T.hi[a];
-        const double gx = axis_gap<kPer>(lo.x, hi.x, g.lox, g.hix, O);
-        const double gy = axis_gap<kPer>(lo.y, hi.y, g.loy, g.hiy, O);
-        const double gz = axis_gap<kPer>(lo.z, hi.z, g.loz, g.hiz, O);
-        return gx * gx + gy * gy + gz * gz > S.r2 * (1.0 + 1e-12);
-    }
-    template <int kPer>
-    __device__ static void start(Lds& S, const Tree& T, const WalkOut& O, int4 gd, const Target& t, Acc& A,
-                                 int part, int, int count) {
-        const bool owner = part == 0;
-        const double4 xi = T.spos[t.p];
-        A.x = xi.x;
-        A.y = xi.y;
-        A.z = xi.z;
-        const int k = O.knn_k;
-#pragma unroll
-        for (int i = 0; i < kCap; ++i) A.L[i] = i < kCap - k ? -__builtin_huge_val() : __builtin_huge_val();
-        const int64_t lo = gd.x - k > 0 ? gd.x - k : 0;
-        const int64_t hi = gd.x + count + k < O.knn_n ? gd.x + count + k : O.knn_n;
-        if (threadIdx.x == 0) {
-            S.win_lo = (int)lo;
-            S.win_hi = (int)hi;
-        }
-        double4* P = reinterpret_cast<double4*>(S.tile);
-        for (int64_t base = lo; base < hi; base += kW) {
-            const int cw = hi - base < kW ? (int)(hi - base) : kW;
-            __syncthreads();
-            if ((int)threadIdx.x < cw) {
-                P[threadIdx.x] = T.spos[base + threadIdx.x];
-                S.tidx[threadIdx.x] = (int)(base + threadIdx.x);
-            }
-            __syncthreads();
-            for (int q = 0; q < cw; ++q) {
-                if (owner && S.tidx[q] != t.p) offer(S, A, dist2<kPer>(P[q], A, O));
-                check_full(S, A);
-            }
-        }
-        flush(S, A, owner);
-        __syncthreads();
-    }
-    template <int kPer>
-    __device__ static void stage_particle(Lds& S, const Tree& T, const GroupBox&, int lane, int pk, const WalkOut&) {
-        reinterpret_cast<double4*>(S.tile)[lane] = T.spos[pk];
-        S.tidx[lane] = pk;
-    }
-    template <int kPer>
-    __device__ static void stage_node(Lds&, const Tree&, const GroupBox&, int, int, const WalkOut&) {}
-    template <int kPer, bool kSoft>
-    __device__ static void particles(Lds& S, int cnt, const Target& t, Acc& A, float, float, int k0, int,
-                                     const WalkOut& O) {
-        const bool owner = k0 == 0;   // the target's first lane keeps its list
-        const double4* P = reinterpret_cast<const double4*>(S.tile);
-        for (int q = 0; q < cnt; ++q) {
-            const int pk = S.tidx[q];
-            if (owner && pk != t.p && (pk < S.win_lo || pk >= S.win_hi))
-                offer(S, A, dist2<kPer>(P[q], A, O));
-            check_full(S, A);
-        }
-        flush(S, A, owner);
-    }
-    __device__ static void nodes(const Lds&, int, const Target&, Acc&, int, int, const WalkOut&) {}
-    static __device__ void wave_sum(Acc&) {}
-    // Density mode (Price & Monaghan lengths): h with S(h) = 1 + sum_i
-    // w(r_i / h) = 3 N / 32 over the listed neighbours (self counted as 1),
-    // by pm_newton; every particle within h is listed when the root lies
-    // inside the list's last distance or the list holds all the others.
-    // Also Omega = -(32 / (9 N)) sum_i u_i w'(u_i) at h.
-    __device__ static void finish(const Tree& T, const WalkOut& O, const Acc& A, int p, const Target&) {
-        const int64_t row = T.perm[p];
-        if constexpr (!kDensity) {
-            O.knn_out[row] = O.knn_scale * sqrt(A.L[kCap - 1]);
-            return;
-        }
-        // the distances once (-1 for the leading -inf dummies)
-        double r[kCap];
-#pragma unroll
-        for (int i = 0; i < kCap; ++i) r[i] = A.L[i] >= 0.0 ? sqrt(A.L[i]) : -1.0;
-        const double target = 3.0 * O.pm_ngb / 32.0;
-        auto sums = [&](double h, double& sd) {
-            const double hinv = 1.0 / h;
-            double sw = 1.0;
-            sd = 0.0;
-#pragma unroll
-            for (int i = 0; i < kCap; ++i) {
-                const double u = r[i] * hinv;
-                if (r[i] >= 0.0 && u < 1.0) {
-                    sw += m4_w(u);
-                    sd += u * m4_wp(u);
-                }
-            }
-            return sw;
-        };
-        const bool all = (int64_t)O.knn_k >= O.knn_n - 1;
-        const double rl = r[kCap - 1];
-        double hi = rl > 0.0 ? rl : 1.0, sd = 0.0;
-        double shi = sums(hi, sd);
-        if (all)
-            for (int g = 0; g < 64 && shi < target; ++g) shi = sums(hi *= 2.0, sd);
-        if (shi < target) {
-            // the root lies beyond the list: the sum walk takes over from the
-            // list's last distance with a bracket closed by any length at
-            // which every particle counts (h = D / u*, D the root's diagonal)
-            atomicOr(O.flags, AGF_PMSHORT);
-            O.pm_idx[atomicAdd(O.pm_active, 1)] = (int32_t)row;
-            const int root = T.sys_root[0];
-            const float4 lo4 = T.lo[root], hi4 = T.hi[root];
-            const double ex = (double)hi4.x - lo4.x, ey = (double)hi4.y - lo4.y, ez = (double)hi4.z - lo4.z;
-            O.pm_lo[row] = hi;
-            O.pm_hi[row] = O.pm_hiscale * sqrt(ex * ex + ey * ey + ez * ez);
-            O.pm_cur[row] = 2.0 * hi;
-            O.knn_out[row] = __builtin_nan("");
-            O.pm_omega[row] = __builtin_nan("");
-            return;
-        }
-        // start where S would meet the target if the listed neighbours filled
-        // the ball of radius hi uniformly (S - 1 growing as h^3)
-        double lo = 0.0, h = hi;
-        if (shi > target) h = fmin(hi, hi * cbrt((target - 1.0) / (shi - 1.0)));
-        for (int it = 0; it < 200; ++it) {
-            const double s = sums(h, sd);
-            double hn;
-            if (!pm_newton(s, sd, target, h, lo, hi, hn)) break;
-            h = hn;
-        }
-        sums(h, sd);
-        O.pm_lo[row] = h;   // a closed bracket: the sum walk leaves it alone
-        O.pm_hi[row] = h;
-        O.knn_out[row] = h;
-        O.pm_omega[row] = -(32.0 / (9.0 * O.pm_ngb)) * sd;
-    }
-};
-
-// ---- Price & Monaghan sums over the pairs inside a kernel support ----
-// kMode 0: Z_i = -(G m_i h_i^2 / (6 C Omega_i)) sum_{j != i, r < h_i} m_j
-//          (psi + u^2 F)(r / h_i), C = 3 N / (4 pi) (number density n h^3);
-// kMode 1: a_i = -(1 / m_i) sum_{j != i} [Z_i W'(r, h_i) + Z_j W'(r, h_j)] d / r
-//          over r < max(h_i, h_j), W'(r, h) = 8 / (pi h^4) w'(r / h), d = x_j - x_i.
-// kMode 2: one pm_newton step of a length whose support holds more
-//          particles than the neighbour list: sum_j w(r / h) (self included)
-//          and sum_j u w'(u) at the current h; h and Omega at h are written.
-//          Targets with a closed bracket take no part; a group with none
-//          left skips the whole tree.
-// The lengths are the per-particle softening lengths the tree was built
-// with (FP64, input order); each node's largest one (lo.w, a float) bounds
-// the sources' supports in mode 1.  Coincident pairs add nothing (w'(0) = 0).
-// Only the first lane of each target sums.
-struct PmLds : WalkLds<2> {
-    double hz[2 * kW];   // staged sources' h and Z
-    double r2;           // the group's largest h^2
-};
-template <int kMode>
-struct PmPolicy {
-    static constexpr bool kSkipEmpty = false;
-    static constexpr bool kOpenAll = true;
-    static constexpr bool kImageMac = false;
-    static constexpr bool kGroupSum = false;
-    static constexpr int kWaves = 4;
-    using Tile = PmLds;
-    using Lds = PmLds;
-    struct Acc {
-        double x, y, z, m, h, zi;
-        double s, ax, ay, az;
-        __device__ void zero() { s = ax = ay = az = 0.0; }
-        __device__ void add(const Acc&) {}
-    };
-    template <int kPer>
-    __device__ static bool skip_node(const Lds& S, const Tree& T, const GroupBox& g, int a, const WalkOut&) {
-        const float4 lo = T.lo[a], hi = T.hi[a];
-        const double gx = fmax(fmax((double)lo.x - g.hix, (double)g.lox - hi.x), 0.0);
-        const double gy = fmax(fmax((double)lo.y - g.hiy, (double)g.loy - hi.y), 0.0);
-        const double gz = fmax(fmax((double)lo.z - g.hiz, (double)g.loz - hi.z), 0.0);
-        double R2 = S.r2;
-        if (kMode == 1) {
-            const double hn = (double)lo.w * (1.0 + 1e-6);   // covers the float rounding of each length
-            R2 = fmax(R2, hn * hn);
-        }
-        return gx * gx + gy * gy + gz * gz > R2 * (1.0 + 1e-12);
-    }
-    template <int kPer>
-    __device__ static void start(Lds& S, const Tree& T, const WalkOut& O, int4, const Target& t, Acc& A, int part,
-                                 int, int) {
-        const double4 xi = T.spos[t.p];
-        A.x = xi.x;
-        A.y = xi.y;
-        A.z = xi.z;
-        A.m = xi.w;
-        const int64_t row = T.perm[t.p];
-        if (kMode == 2) {
-            A.h = O.pm_lo[row] < O.pm_hi[row] ? O.pm_cur[row] : 0.0;
-        } else {
-            A.h = O.pm_h[row];
-        }
-        A.zi = kMode == 1 ? O.pm_z[row] : 0.0;
-        const double r2 = ag_wave_max(part == 0 && A.h > 0.0 ? A.h * A.h : -1.0);
-        if (threadIdx.x == 0) S.r2 = r2;
-        __syncthreads();
-    }
-    template <int kPer>
-    __device__ static void stage_particle(Lds& S, const Tree& T, const GroupBox&, int lane, int pk, const WalkOut& O) {
-        reinterpret_cast<double4*>(S.tile)[lane] = T.spos[pk];
-        S.tidx[lane] = pk;
-        if (kMode == 1) {
-            const int64_t row = T.perm[pk];
-            S.hz[2 * lane] = O.pm_h[row];
-            S.hz[2 * lane + 1] = O.pm_z[row];
-        }
-    }
-    template <int kPer>
-    __device__ static void stage_node(Lds&, const Tree&, const GroupBox&, int, int, const WalkOut&) {}
-    template <int kPer, bool kSoft>
-    __device__ static void particles(Lds& S, int cnt, const Target& t, Acc& A, float, float, int k0, int,
-                                     const WalkOut&) {
-        if (k0 != 0) return;
-        const double4* P = reinterpret_cast<const double4*>(S.tile);
-        constexpr double k8pi = 8.0 / 3.14159265358979323846;
-        for (int q = 0; q < cnt; ++q) {
-            if (kMode == 2) {   // self included: w(0) = 1
-                const double4 pj = P[q];
-                const double dx = pj.x - A.x, dy = pj.y - A.y, dz = pj.z - A.z;
-                const double r2 = dx * dx + dy * dy + dz * dz;
-                if (r2 < A.h * A.h) {
-                    const double u = sqrt(r2) / A.h;
-                    A.s += m4_w(u);
-                    A.ax += u * m4_wp(u);
-                }
-                continue;
-            }
-            if (S.tidx[q] == t.p) continue;
-            const double4 pj = P[q];
-            const double dx = pj.x - A.x, dy = pj.y - A.y, dz = pj.z - A.z;
-            const double r2 = dx * dx + dy * dy + dz * dz;
-            if (kMode == 0) {
-                if (r2 < A.h * A.h) A.s += pj.w * m4_dphi(sqrt(r2) / A.h);
-            } else {
-                const double hj = S.hz[2 * q], zj = S.hz[2 * q + 1];
-                if (r2 > 0.0 && (r2 < A.h * A.h || r2 < hj * hj)) {
-                    const double r = sqrt(r2);
-                    const double hi4 = (A.h * A.h) * (A.h * A.h), hj4 = (hj * hj) * (hj * hj);
-                    const double c = k8pi * (A.zi * m4_wp(r / A.h) / hi4 + zj * m4_wp(r / hj) / hj4) / r;
-                    A.ax += c * dx;
-                    A.ay += c * dy;
-                    A.az += c * dz;
-                }
-            }
-        }
-    }
-    __device__ static void nodes(const Lds&, int, const Target&, Acc&, int, int, const WalkOut&) {}
-    static __device__ void wave_sum(Acc&) {}
-    __device__ static void finish(const Tree& T, const WalkOut& O, const Acc& A, int p, const Target&) {
-        const int64_t row = T.perm[p];
-        if (kMode == 2) {
-            if (!(A.h > 0.0)) return;
-            double lo = O.pm_lo[row], hi = O.pm_hi[row], hn;
-            if (pm_newton(A.s, A.ax, 3.0 * O.pm_ngb / 32.0, A.h, lo, hi, hn)) {
-                O.pm_lo[row] = lo;
-                O.pm_hi[row] = hi;
-                O.pm_cur[row] = hn;
-                atomicAdd(O.pm_active, 1);
-            } else {
-                O.pm_lo[row] = A.h;
-                O.pm_hi[row] = A.h;
-            }
-            O.knn_out[row] = A.h;
-            O.pm_omega[row] = -(32.0 / (9.0 * O.pm_ngb)) * A.ax;
-        } else if (kMode == 0) {
-            const double C = 3.0 * O.pm_ngb / (4.0 * 3.14159265358979323846);
-            O.pm_zout[row] = -(O.pm_G * A.m * A.h * A.h / (6.0 * C * O.pm_om[row])) * A.s;
-        } else if (O.pm_add) {
-            O.pm_acc[3 * row] += -A.ax / A.m;
-            O.pm_acc[3 * row + 1] += -A.ay / A.m;
-            O.pm_acc[3 * row + 2] += -A.az / A.m;
-        } else {
-            O.pm_acc[3 * row] = -A.ax / A.m;
-            O.pm_acc[3 * row + 1] = -A.ay / A.m;
-            O.pm_acc[3 * row + 2] = -A.az / A.m;
-        }
-    }
-};
-
-template <class P, int kPer>
-__device__ __forceinline__ bool policy_skips(const typename P::Lds* S, const Tree& T, const GroupBox& g, int a,
-                                             const WalkOut& O) {
-    if constexpr (P::kOpenAll) return P::template skip_node<kPer>(*S, T, g, a, O);
-    else if constexpr (P::kSkipEmpty) return T.wf[8 * a].w == 0.f;
-    else return false;
-}
-
 // orders a wave's LDS accesses around it (LDS serves a wave's accesses in
 // order, so no wait is needed between its lanes)
 __device__ __forceinline__ void wave_sync() {
@@ -1503,8 +1053,8 @@ __device__ __forceinline__ GroupSetup group_setup(const Tree& T, const Groups& G
 // the end the two remainders, to tile(is_node, list, count).  The order of the
 // tiles and of the entries in them depends on the tree and the group alone.
 template <class Pol, int kPer, bool kSoft, class TileFn>
-__device__ __forceinline__ void traverse(ListLds& S, const typename Pol::Lds* P, const Tree& T, const WalkOut& O,
-                                         const GroupBox& gb, float gh2, int root, int lane, float theta2, float eps2,
+__device__ __forceinline__ void traverse(ListLds& S, const Tree& T, const WalkOut& O, const GroupBox& gb, float gh2,
+                                         int root, int lane, float theta2, float eps2,
                                          TileFn tile) {
     int ca = 0, cb = 0;          // cursor range [ca, cb)
     int ps = 0, pc = 0;          // particles still to be listed from an opened leaf
@@ -1550,12 +1100,11 @@ __device__ __forceinline__ void traverse(ListLds& S, const typename Pol::Lds* P,
             const int a = ca;
             const int4 L = T.link[a];
             const bool leaf = (L.w & 0x100) != 0;
-            if (policy_skips<Pol, kPer>(P, T, gb, a, O)) {
+            if (Pol::kSkipEmpty && T.wf[8 * a].w == 0.f) {
                 ca = L.x;                  // nothing below this node matters
             } else {
                 const bool acc_ok =
-                    Pol::kOpenAll ? false
-                    : Pol::kImageMac ? ewald_accept(gb, T.com[a], T.lo[a], T.hi[a], O)
+                    Pol::kImageMac ? ewald_accept(gb, T.com[a], T.lo[a], T.hi[a], O)
                                    : mac_accept<kPer>(gb, T.com[a], T.lo[a], T.hi[a], theta2,
                                                       kSoft ? fmaxf(gh2, T.lo[a].w * T.lo[a].w) : eps2,
                                                       O.mac_offset, O);
@@ -1628,18 +1177,32 @@ __device__ __forceinline__ void traverse(ListLds& S, const typename Pol::Lds* P,
     if (ppend > 0) tile(false, S.plist, ppend);
 }
 
-__device__ __forceinline__ void count_group(const WalkOut& O, uint64_t n_pp, uint64_t n_pn, int count) {
-    atomicAdd(&O.stats[0], (unsigned long long)(n_pp * (uint64_t)count));
-    atomicAdd(&O.stats[1], (unsigned long long)(n_pn * (uint64_t)count));
-    atomicAdd(&O.stats[2], (unsigned long long)count);
-    atomicAdd(&O.stats[3], 1ull);
-}
+// What a wave's groups add to the context's counters: kept by the wave and
+// added once when it ends (four atomics per group, all on one line that the
+// XCDs' L2s then pass around, take as long as a short group's walk).
+struct WalkCount {
+    uint64_t pp = 0, pn = 0, targets = 0, groups = 0;
+    __device__ __forceinline__ void group(uint64_t n_pp, uint64_t n_pn, int count) {
+        pp += n_pp * (uint64_t)count;
+        pn += n_pn * (uint64_t)count;
+        targets += (uint64_t)count;
+        groups += 1;
+    }
+    __device__ __forceinline__ void add_to(unsigned long long* stats) const {
+        if (!stats || groups == 0 || ag_lane() != 0) return;
+        atomicAdd(&stats[0], (unsigned long long)pp);
+        atomicAdd(&stats[1], (unsigned long long)pn);
+        atomicAdd(&stats[2], (unsigned long long)targets);
+        atomicAdd(&stats[3], (unsigned long long)groups);
+    }
+};
 
 // Walk the tree for one group of targets by one wave: every tile is staged
 // and evaluated as soon as it is full.
 template <class Pol, int kPer, bool kSoft>
 __device__ __forceinline__ void walk_group(typename Pol::Lds& S, const Tree& T, const Groups& Gr, const WalkOut& O,
-                                           const int4 gd, float theta2, float eps2, float h2, float hinv) {
+                                           const int4 gd, float theta2, float eps2, float h2, float hinv,
+                                           WalkCount& C) {
     const int lane = ag_lane();
     if (gd.y <= 0) return;
     const GroupSetup U = group_setup<Pol, kPer, kSoft>(T, Gr, O, gd, eps2, lane);
@@ -1647,30 +1210,25 @@ __device__ __forceinline__ void walk_group(typename Pol::Lds& S, const Tree& T, 
     const int count = U.count, sub = U.sub, slot = U.slot, part = U.part;
     typename Pol::Acc acc;
     acc.zero();
-    if constexpr (Pol::kOpenAll) Pol::template start<kPer>(S, T, O, gd, tg, acc, part, slot, count);
 
     uint64_t n_pp = 0, n_pn = 0;
-    traverse<Pol, kPer, kSoft>(S, &S, T, O, U.gb, U.gh2, T.sys_root[gd.z], lane, theta2, eps2,
+    traverse<Pol, kPer, kSoft>(S, T, O, U.gb, U.gh2, T.sys_root[gd.z], lane, theta2, eps2,
                                [&](bool node, const int* list, int cnt) {
         if (lane < cnt) {
             if (node) Pol::template stage_node<kPer>(S, T, U.gb, lane, list[lane], O);
             else Pol::template stage_particle<kPer>(S, T, U.gb, lane, list[lane], O);
         }
         wave_sync();
-        if constexpr (Pol::kOpenAll) {
-            if (!node) Pol::template particles<kPer, kSoft>(S, cnt, tg, acc, h2, hinv, part, sub, O);
-        } else {
-            bool done = false;
-            if constexpr (Pol::kGroupSum) {
-                done = !tg.grp;
-                if (done) Pol::target_entries(S, cnt, tg, acc, part, sub, O);
-            }
-            if (!done) {
-                typename Pol::Sum F;
-                if (node) Pol::nodes(S, cnt, tg, F, part, sub, O);
-                else Pol::template particles<kPer, kSoft>(S, cnt, tg, F, h2, hinv, part, sub, O);
-                acc.fold(F);
-            }
+        bool done = false;
+        if constexpr (Pol::kGroupSum) {
+            done = !tg.grp;
+            if (done) Pol::target_entries(S, cnt, tg, acc, part, sub, O);
+        }
+        if (!done) {
+            typename Pol::Sum F;
+            if (node) Pol::nodes(S, cnt, tg, F, part, sub, O);
+            else Pol::template particles<kPer, kSoft>(S, cnt, tg, F, h2, hinv, part, sub, O);
+            acc.fold(F);
         }
         if (node) n_pn += (uint64_t)cnt;
         else n_pp += (uint64_t)cnt;
@@ -1680,8 +1238,6 @@ __device__ __forceinline__ void walk_group(typename Pol::Lds& S, const Tree& T, 
     if (Pol::kGroupSum && tg.grp) {
         // every lane summed its own share of the entries: add all 64
         Pol::wave_sum(acc);
-    } else if constexpr (Pol::kOpenAll) {
-        // (the neighbour walk's parts other than the first keep nothing)
     } else if (sub > 1) {
         // sum the parts of every target in LDS (the walk lists are free now)
         static_assert(sizeof(typename Pol::Lds) >= sizeof(typename Pol::Acc) * kW, "LDS too small");
@@ -1694,7 +1250,7 @@ __device__ __forceinline__ void walk_group(typename Pol::Lds& S, const Tree& T, 
         wave_sync();
     }
     if (part == 0) Pol::finish(T, O, acc, tg.p, tg);
-    if (lane == 0 && O.stats) count_group(O, n_pp, n_pn, count);
+    C.group(n_pp, n_pn, count);
 }
 
 // ---- one group walked by a team of waves ----
@@ -1745,7 +1301,7 @@ __device__ __forceinline__ void team_barrier(int* arrived, int ts) {
 template <class Pol, int kPer, bool kSoft>
 __device__ __forceinline__ void walk_group_team(TeamLds<Pol>& S, typename Pol::Tile& st, int wave, int ts,
                                                 const Tree& T, const Groups& Gr, const WalkOut& O, const int4 gd,
-                                                float theta2, float eps2, float h2, float hinv) {
+                                                float theta2, float eps2, float h2, float hinv, WalkCount& C) {
     constexpr int kN = Pol::kWords;
     const int lane = ag_lane();
     if (gd.y <= 0) {   // uniform over the team
@@ -1808,8 +1364,8 @@ __device__ __forceinline__ void walk_group_team(TeamLds<Pol>& S, typename Pol::T
     uint64_t n_pp = 0, n_pn = 0;
     if (wave == 0) {
         int tail = 0;
-        traverse<Pol, kPer, kSoft>(S.lists, (const typename Pol::Lds*)nullptr, T, O, U.gb, U.gh2, T.sys_root[gd.z],
-                                   lane, theta2, eps2, [&](bool node, const int* list, int cnt) {
+        traverse<Pol, kPer, kSoft>(S.lists, T, O, U.gb, U.gh2, T.sys_root[gd.z], lane,
+                                   theta2, eps2, [&](bool node, const int* list, int cnt) {
             const int s = tail % kRing;
             // a full queue: take its oldest tile that no wave has asked for,
             // or wait for the wave that has asked for the slot's
@@ -1877,7 +1433,7 @@ __device__ __forceinline__ void walk_group_team(TeamLds<Pol>& S, typename Pol::T
                 for (int k = 0; k < kN; ++k) a[k] += S.acc[k][slot + j * count];
         }
         if (part == 0) Pol::finish(T, O, acc, tg.p, tg);
-        if (lane == 0 && O.stats) count_group(O, n_pp, n_pn, count);
+        C.group(n_pp, n_pn, count);
     }
 }
 
@@ -1885,36 +1441,19 @@ __device__ __forceinline__ void walk_group_team(TeamLds<Pol>& S, typename Pol::T
 // eighth of the (Morton-ordered) group list.  A workgroup starts on queue
 // blockIdx % 8 -- the XCD the hardware dispatches it to, so spatially
 // neighbouring groups share that XCD's L2 -- and steals from the other queues
-// when its own runs dry (q counts the queues it has left).
+// when its own runs dry (q counts the queues it has left).  Each queue's counter
+// has a cache line of its own, which stays in its XCD's L2.
 __device__ __forceinline__ int pop_group(int* __restrict__ qctr, int n_groups, int& q) {
     const int home = blockIdx.x & 7;
     while (q < 8) {
         const int qq = (home + q) & 7;
         const int lo = (int)((int64_t)n_groups * qq / 8);
         const int hi = (int)((int64_t)n_groups * (qq + 1) / 8);
-        const int k = atomicAdd(&qctr[qq], 1);
+        const int k = atomicAdd(&qctr[qq * kQueueStride], 1);
         if (lo + k < hi) return lo + k;
         ++q;
     }
     return -1;
-}
-
-// Persistent walk by single waves, one per workgroup (the neighbour and Price
-// & Monaghan walks).
-template <class Pol, int kPer, bool kSoft = false>
-__global__ void __launch_bounds__(kW, Pol::kWaves) k_walk(Tree T, Groups Gr, WalkOut O, int* __restrict__ qctr,
-                                             float theta2, float eps2, float h2, float hinv) {
-    __shared__ typename Pol::Lds S;
-    const int n_groups = Gr.hdr[0];
-    int q = 0;
-    for (;;) {
-        int g = -1;
-        if (threadIdx.x == 0) g = pop_group(qctr, n_groups, q);
-        g = __builtin_amdgcn_readfirstlane(g);
-        if (g < 0) break;
-        walk_group<Pol, kPer, kSoft>(S, T, Gr, O, Gr.grp[g], theta2, eps2, h2, hinv);
-        wave_sync();
-    }
 }
 
 // Persistent walk by workgroups of W waves, which walk groups each on its own
@@ -1938,6 +1477,7 @@ __global__ void __launch_bounds__(W * kW, Pol::kWaves) k_walk_team(Tree T, Group
     const int n_groups = Gr.hdr[0];
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     int q = 0;
+    WalkCount C;
     if (n_groups > R.solo_above) {
         for (;;) {
             int g = -1;
@@ -1945,7 +1485,7 @@ __global__ void __launch_bounds__(W * kW, Pol::kWaves) k_walk_team(Tree T, Group
             g = __builtin_amdgcn_readfirstlane(g);
             if (g < 0) break;
             walk_group<Pol, kPer, kSoft>(reinterpret_cast<Solo*>(s_mem)[wave], T, Gr, O, Gr.grp[g], theta2, eps2, h2,
-                                         hinv);
+                                         hinv, C);
             wave_sync();
         }
     } else {
@@ -1960,9 +1500,10 @@ __global__ void __launch_bounds__(W * kW, Pol::kWaves) k_walk_team(Tree T, Group
             team_barrier(&S.arrived, ts);
             const int g = lds_get(&S.g);
             if (g < 0) break;
-            walk_group_team<Pol, kPer, kSoft>(S, st, me, ts, T, Gr, O, Gr.grp[g], theta2, eps2, h2, hinv);
+            walk_group_team<Pol, kPer, kSoft>(S, st, me, ts, T, Gr, O, Gr.grp[g], theta2, eps2, h2, hinv, C);
         }
     }
+    C.add_to(O.stats);
 }
 
 // ---------------------------------------------------------------------------
@@ -2253,7 +1794,7 @@ __global__ void k_group_emit(GroupCtx C, const int64_t* __restrict__ hdr, const 
          id += (int64_t)gridDim.x * blockDim.x) {
         if (goff[id + 1] > goff[id]) node_groups(C, (int)id, grp + goff[id]);
     }
-    if (blockIdx.x == 0 && threadIdx.x < 8) qctr[threadIdx.x] = 0;
+    if (blockIdx.x == 0 && threadIdx.x < 2 * 8) qctr[threadIdx.x * kQueueStride] = 0;   // two walks' queues
     if (blockIdx.x == 0 && threadIdx.x == 0) ghdr[0] = goff[nn];
 }
 
@@ -2273,7 +1814,7 @@ int ag_prepare_groups(ag_ctx* c, const int32_t* idx, int64_t n_act, int64_t* max
     AG_TRY(ag_ensure(c, c->act_off, (n + 1) * 4));
     AG_TRY(ag_ensure(c, c->act_pos, n * 4));
     AG_TRY(ag_ensure(c, c->grp, mg * 16));
-    AG_TRY(ag_ensure(c, c->grp_hdr, (16 + AG_MAX_SYS + 1) * 4));
+    AG_TRY(ag_ensure(c, c->grp_hdr, (1 + 2 * 8) * kQueueStride * sizeof(int32_t)));
     AG_TRY(ag_ensure(c, c->grp_cnt, (c->max_nodes + 1) * 4));
     AG_TRY(ag_ensure(c, c->grp_off, (c->max_nodes + 1) * 4));
     PhaseScope phase(c, AG_PHASE_GROUPS);
@@ -2303,7 +1844,7 @@ int ag_prepare_groups(ag_ctx* c, const int32_t* idx, int64_t n_act, int64_t* max
     AG_TRY(ag_scan_i32(c, gcnt, goff, c->max_nodes));
     int32_t* ghdr = c->grp_hdr.as<int32_t>();
     hipLaunchKernelGGL(k_group_emit, dim3(grid_for(c->max_nodes)), dim3(256), 0, st, C, hdr, goff,
-                       c->grp.as<int4>(), ghdr, ghdr + 8);
+                       c->grp.as<int4>(), ghdr, ghdr + kQueueStride);
     *max_groups = mg;
     return AG_OK;
 }
@@ -2451,13 +1992,6 @@ static int device_cus(ag_ctx* c) {
     return cus;
 }
 
-static int walk_grid(ag_ctx* c, int64_t max_groups) {
-    int64_t blocks = (int64_t)device_cus(c) * c->walk_waves_per_cu;
-    if (blocks > max_groups) blocks = (max_groups + 7) / 8 * 8;
-    if (blocks < 8) blocks = 8;
-    return (int)blocks;
-}
-
 // A walk by workgroups of Pol::kTeamWaves waves, one workgroup resident per CU
 // (AG_OPT_WALK_WAVES_PER_CU in whole workgroups, at least one).  How the groups are walked
 // goes by how many there are for the P waves launched, read on the device:
@@ -2505,7 +2039,6 @@ static WalkOut make_out(ag_ctx* c, double G) {
     O.G = G;
     O.flags = c->dflags.as<int32_t>();
     O.iter_cap = c->max_nodes + c->n + 1024;
-    O.knn_scale = 1.0;
     O.small_node = c->small_node;
     O.mac_offset = c->mac_offset != 0;
     O.box = c->box;
@@ -2522,109 +2055,6 @@ static WalkOut make_out(ag_ctx* c, double G) {
     O.etab_hinv = (float)(kEwaldPerBox / c->box);
     O.etab_range = (float)(c->box * kEwaldNE / kEwaldPerBox * (1.0 + 1e-4));   // a few ulps of slack
     return O;
-}
-
-// distance of every particle to its k-th nearest other particle, by a walk
-// that opens every node and prunes by distance
-int ag_launch_knn(ag_ctx* c, int32_t k, double scale, double* h_out) {
-    int64_t mg = 0;
-    AG_TRY(ag_prepare_groups(c, nullptr, c->n, &mg, nullptr, nullptr));
-    Groups Gr{nullptr, c->grp.as<int4>(), c->grp_hdr.as<int32_t>()};
-    WalkOut O = make_out(c, 1.0);
-    O.stats = nullptr;
-    O.knn_out = h_out;
-    O.knn_scale = scale;
-    O.knn_k = k;
-    O.knn_n = c->n;
-    O.box = c->tree_box;   // nearest images in the box the tree was built in
-    PhaseScope phase(c, AG_PHASE_NEIGHBOUR);
-    const unsigned grid = (unsigned)walk_grid(c, mg);
-    int32_t* qctr = c->grp_hdr.as<int32_t>() + 8;
-    const Tree T = make_tree(c);
-    hipStream_t st = c->stream;
-#define AG_KNN(CAP, PER) \
-    hipLaunchKernelGGL((k_walk<KnnPolicy<CAP>, PER>), dim3(grid), dim3(kW), 0, st, T, Gr, O, qctr, 0.f, 0.f, 0.f, 0.f)
-    const bool per = c->tree_box > 0.0;
-    if (k <= 16) {
-        if (per) AG_KNN(16, kNear); else AG_KNN(16, kOpen);
-    } else if (k <= 32) {
-        if (per) AG_KNN(32, kNear); else AG_KNN(32, kOpen);
-    } else {
-        if (per) AG_KNN(64, kNear); else AG_KNN(64, kOpen);
-    }
-#undef AG_KNN
-    return AG_OK;
-}
-
-// Price & Monaghan lengths and Omega: the 64-neighbour walk in density mode
-// (step 0), then the sum walk's Newton steps for the lengths the list
-// cannot reach (step > 0; each launch re-arms the walk's work queues), run
-// over the n_left rows the list pass left, grouped on their own)
-int ag_launch_pm_lengths(ag_ctx* c, double n_ngb, double* h, double* omega, int step, int64_t n_left) {
-    int64_t mg = 0;
-    int32_t* left = reinterpret_cast<int32_t*>(reinterpret_cast<int*>(c->pm_brk.as<double>() + 3 * c->n) + kPmSteps);
-    AG_TRY(ag_prepare_groups(c, step == 0 ? nullptr : left, step == 0 ? c->n : n_left, &mg, nullptr, nullptr));
-    Groups Gr{c->all_active ? (const int32_t*)nullptr : c->act_pos.as<int32_t>(), c->grp.as<int4>(),
-              c->grp_hdr.as<int32_t>()};
-    WalkOut O = make_out(c, 1.0);
-    O.stats = nullptr;
-    O.knn_out = h;
-    O.knn_k = c->n - 1 < 64 ? (int)(c->n - 1) : 64;
-    O.knn_n = c->n;
-    O.pm_ngb = n_ngb;
-    O.pm_omega = omega;
-    O.pm_lo = c->pm_brk.as<double>();
-    O.pm_hi = O.pm_lo + c->n;
-    O.pm_cur = O.pm_hi + c->n;
-    O.pm_active = reinterpret_cast<int*>(O.pm_cur + c->n) + step;
-    O.pm_idx = left;
-    // every particle lies within the root's diagonal D of every other, so
-    // at h = D / u* the sum is at least n (1 - 6 u*^2) >= 3 N / 32 (w(u) >=
-    // 1 - 6 u^2 for u < 1/2)
-    const double f = 3.0 * n_ngb / 32.0 / (double)c->n;
-    const double us = std::min(0.5, std::sqrt((1.0 - f) / 6.0));
-    O.pm_hiscale = 1.01 / us;
-    PhaseScope phase(c, AG_PHASE_NEIGHBOUR);
-    const unsigned grid = (unsigned)walk_grid(c, mg);
-    int32_t* qctr = c->grp_hdr.as<int32_t>() + 8;
-    if (step == 0) {
-        hipLaunchKernelGGL((k_walk<KnnPolicy<64, true>, kOpen>), dim3(grid), dim3(kW), 0, c->stream, make_tree(c), Gr,
-                           O, qctr, 0.f, 0.f, 0.f, 0.f);
-    } else {
-        hipLaunchKernelGGL((k_walk<PmPolicy<2>, kOpen>), dim3(grid), dim3(kW), 0, c->stream, make_tree(c), Gr, O,
-                           qctr, 0.f, 0.f, 0.f, 0.f);
-    }
-    return AG_OK;
-}
-
-// Price & Monaghan sums: Z (mode 0, z_out) or the correction (mode 1, acc)
-int ag_launch_pm_sum(ag_ctx* c, int mode, double n_ngb, double G, const double* omega, const double* z,
-                     double* z_out, double* acc, const int32_t* idx, const int64_t* n_dev, bool add) {
-    int64_t mg = 0;
-    AG_TRY(ag_prepare_groups(c, idx, c->n, &mg, idx ? n_dev : nullptr, nullptr));
-    Groups Gr{c->all_active ? (const int32_t*)nullptr : c->act_pos.as<int32_t>(), c->grp.as<int4>(),
-              c->grp_hdr.as<int32_t>()};
-    WalkOut O = make_out(c, G);
-    O.stats = nullptr;
-    O.pm_ngb = n_ngb;
-    O.pm_G = G;
-    O.pm_h = c->soft_h.as<double>();
-    O.pm_om = omega;
-    O.pm_z = z;
-    O.pm_zout = z_out;
-    O.pm_acc = acc;
-    O.pm_add = add || idx != nullptr;
-    PhaseScope phase(c, AG_PHASE_NEIGHBOUR);
-    const unsigned grid = (unsigned)walk_grid(c, mg);
-    const Tree T = make_tree(c);
-    int32_t* qctr = c->grp_hdr.as<int32_t>() + 8;
-    if (mode == 0)
-        hipLaunchKernelGGL((k_walk<PmPolicy<0>, kOpen>), dim3(grid), dim3(kW), 0, c->stream, T, Gr, O, qctr, 0.f, 0.f,
-                           0.f, 0.f);
-    else
-        hipLaunchKernelGGL((k_walk<PmPolicy<1>, kOpen>), dim3(grid), dim3(kW), 0, c->stream, T, Gr, O, qctr, 0.f, 0.f,
-                           0.f, 0.f);
-    return AG_OK;
 }
 
 int ag_launch_eval(ag_ctx* c, const int32_t* idx, int64_t n_act, double theta, double eps, double G, double* acc,
@@ -2646,7 +2076,7 @@ int ag_launch_eval(ag_ctx* c, const int32_t* idx, int64_t n_act, double theta, d
     }
     const float th = (float)theta;
     const float e2 = (float)(eps * eps);
-    int32_t* qctr = c->grp_hdr.as<int32_t>() + 8;
+    int32_t* qctr = c->grp_hdr.as<int32_t>() + kQueueStride;
     {
         PhaseScope phase(c, AG_PHASE_WALK);
         const float hi = (float)(1.0 / eps);
@@ -2664,13 +2094,11 @@ int ag_launch_eval(ag_ctx* c, const int32_t* idx, int64_t n_act, double theta, d
     }
     if (ewald && (acc || tidal)) {
         // what the periodic images add to g and T, at the same images
-        AG_TRY(ag_ensure(c, c->ewald_q, 8 * sizeof(int32_t)));
         PhaseScope phase(c, AG_PHASE_EWALD);
-        hipLaunchKernelGGL(k_fill0, dim3(1), dim3(64), 0, c->stream, c->ewald_q.as<int32_t>(), (int64_t)8);
         WalkOut E = O;
         E.stats = nullptr;
         E.rel_a = nullptr;
-        launch_walk<EwaldPolicy, kEwald>(c, mg, Gr, E, c->ewald_q.as<int32_t>(), 0.f, 0.f, e2, (float)(1.0 / eps));
+        launch_walk<EwaldPolicy, kEwald>(c, mg, Gr, E, qctr + 8 * kQueueStride, 0.f, 0.f, e2, (float)(1.0 / eps));
     }
     return AG_OK;
 }
@@ -2737,7 +2165,7 @@ int ag_launch_backward(ag_ctx* c, const int32_t* idx, int64_t n_act, const doubl
     O.tin = tin;
     const float th = (float)theta;
     const float e2 = (float)(eps * eps);
-    launch_walk<AdjointPolicy, kOpen>(c, mg, Gr, O, c->grp_hdr.as<int32_t>() + 8, th * th, e2, e2,
+    launch_walk<AdjointPolicy, kOpen>(c, mg, Gr, O, c->grp_hdr.as<int32_t>() + kQueueStride, th * th, e2, e2,
                                       (float)(1.0 / eps));
     return AG_OK;
 }
