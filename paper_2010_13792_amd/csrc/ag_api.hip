@@ -176,12 +176,12 @@ extern "C" int ag_create(ag_ctx** out, int device, void* stream) {
         ag_destroy(c);
         return r;
     }
-    if (hipHostMalloc(reinterpret_cast<void**>(&c->depth_host), sizeof(int64_t), hipHostMallocDefault) != hipSuccess ||
-        hipEventCreateWithFlags(&c->depth_ev, hipEventDisableTiming) != hipSuccess) {
+    if (hipHostMalloc(reinterpret_cast<void**>(&c->depth_host), sizeof(int64_t), hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
         ag_destroy(c);
         return ag_fail(AG_EHIP, "context initialisation failed (pinned depth word)");
     }
+    *c->depth_host = -1;
     if (hipMemsetAsync(c->stats.p, 0, 4 * sizeof(uint64_t), c->stream) != hipSuccess ||
         hipMemsetAsync(c->dflags.p, 0, 4 * sizeof(int32_t), c->stream) != hipSuccess ||
         hipStreamSynchronize(c->stream) != hipSuccess) {
@@ -196,13 +196,13 @@ extern "C" int ag_destroy(ag_ctx* c) {
     if (!c) return AG_OK;
     DeviceGuard g(c->device);
     (void)hipStreamSynchronize(c->stream);
-    DevBuf* bufs[] = {&c->keys[0], &c->keys[1], &c->vals[0], &c->vals[1], &c->sort_hist, &c->perm,
+    DevBuf* bufs[] = {&c->keys[0], &c->keys[1], &c->vals[0], &c->vals[1], &c->box_part, &c->sort_hist, &c->perm,
                       &c->rank, &c->spos, &c->svf, &c->cdig, &c->cd_min, &c->pos_cnt, &c->pos_off,
                       &c->scan_tmp, &c->nd_com, &c->nd_lo, &c->nd_hi, &c->nd_slot, &c->nd_link, &c->nd_mp,
                       &c->nd_64, &c->nd_w, &c->nd_wf, &c->in_list, &c->in_cnt, &c->in_off,
                       &c->tree_hdr, &c->lvl_list, &c->leaf_list, &c->leaf_pos, &c->child, &c->sys_off, &c->sys_root, &c->sys_box, &c->act_flag,
-                      &c->act_pos, &c->act_off, &c->grp, &c->grp_hdr, &c->ewald_tab, &c->soft_h, &c->soft_s, &c->rel_a, &c->grp_cnt, &c->grp_off, &c->sys_act, &c->wsorted,
-                      &c->direct_part, &c->tmp_tidal, &c->sel_flag, &c->sel_off, &c->stats, &c->dflags};
+                      &c->act_pos, &c->act_off, &c->grp, &c->grp_hdr, &c->ewald_tab, &c->soft_h, &c->soft_s, &c->rel_a, &c->grp_cnt, &c->grp_tile, &c->act_stamp, &c->sys_act, &c->wsorted,
+                      &c->direct_part, &c->tmp_tidal, &c->sel_flag, &c->sel_tile, &c->stats, &c->dflags};
     for (DevBuf* b : bufs) ag_release(*b);
     for (PhaseEvents& p : c->timing.pending) {
         (void)hipEventDestroy(p.a);
@@ -211,7 +211,6 @@ extern "C" int ag_destroy(ag_ctx* c) {
     for (hipEvent_t e : c->timing.pool) (void)hipEventDestroy(e);
     if (c->graph_exec) (void)hipGraphExecDestroy(c->graph_exec);
     if (c->graph) (void)hipGraphDestroy(c->graph);
-    if (c->depth_ev) (void)hipEventDestroy(c->depth_ev);
     if (c->depth_host) (void)hipHostFree(c->depth_host);
     delete c;
     return AG_OK;

@@ -101,6 +101,7 @@ struct ag_ctx {
     int64_t max_nodes = 0;
 
     DevBuf keys[2], vals[2];      // radix-sort ping-pong (u64 keys, i32 values)
+    DevBuf box_part;              // u64 [6 per workgroup]: partial bounding boxes
     DevBuf sort_hist;             // per-block digit counts (u32)
     DevBuf perm;                  // i32 [n]: sorted position -> input row
     DevBuf rank;                  // i32 [n]: input row -> sorted position
@@ -109,7 +110,7 @@ struct ag_ctx {
     DevBuf cdig;                  // i32 [n]: octal digits shared with the previous key
     DevBuf cd_min;                // i32: their minima over runs of 16, 256, ... 2^24 positions
     DevBuf pos_cnt, pos_off;      // i32 [n+1]: nodes starting at each position, offsets
-    DevBuf scan_tmp;              // scan block partials
+    DevBuf scan_tmp;              // int2: totals of the node counts per tile; i32: of the active flags
 
     // node arrays, depth-first (pre-order) numbering
     DevBuf nd_com;                // double4: centre of mass x y z, extent L
@@ -134,6 +135,7 @@ struct ag_ctx {
 
     // --- evaluation scratch ---
     bool all_active = false;      // the last grouping listed every particle (no flag, offset or position arrays)
+    DevBuf act_stamp;             // i32 [n]: last list entry that named the position, + 1 (stale where none does)
     DevBuf act_flag;              // i32 [n]
     DevBuf act_pos;               // i32 [n]: active sorted positions, ascending
     DevBuf act_off;               // i32 [n+1]: exclusive scan of act_flag
@@ -143,13 +145,14 @@ struct ag_ctx {
     DevBuf rel_a;                 // f32 |a| of the previous evaluation, input order (rounded down)
     DevBuf ewald_tab;             // f32 Ewald correction table (5 float4 per point)
     DevBuf grp_hdr;               // i32: [0] number of groups, then two walks' eight work-queue counters, kQueueStride apart
-    DevBuf grp_cnt, grp_off;      // i32 [max_nodes (+1)]: groups owned per node, offsets
+    DevBuf grp_cnt;               // i32 [max_nodes]: groups owned per node
+    DevBuf grp_tile;              // i32: their totals per tile
     DevBuf sys_act;               // i32 [n_sys + 1]
     DevBuf wsorted;               // double4 [n]: adjoint weights in sorted order
     DevBuf direct_part;           // direct sum: FP64 per-split sums of a small target set
     DevBuf tmp_tidal;             // double [n*6]
     DevBuf sel_flag;              // i32 [n]: due flags of the last select
-    DevBuf sel_off;               // i32 [n+1]: their exclusive scan
+    DevBuf sel_tile;              // i32: their totals per tile
 
     // --- counters and flags (device) ---
     DevBuf stats;                 // u64 [4]: n_pp, n_pn, n_targets
@@ -158,11 +161,10 @@ struct ag_ctx {
     int64_t host_n_nodes = -1;    // cached after a synchronising read
     size_t dev_bytes = 0;         // bytes held by the buffers above
     size_t mem_limit = 0;         // AG_OPT_MEM_LIMIT (0: none)
-    // depth of the last tree seen by the host (pinned copy + event, read when
-    // the next build starts without waiting): plans the moments' launches
+    // depth of the last finished build (-1: none), written by it to this pinned
+    // host word and read when a build starts, without waiting: plans the
+    // moments' launches
     int64_t* depth_host = nullptr;
-    hipEvent_t depth_ev = nullptr;
-    bool depth_pending = false;
     int seen_max_level = -1;
 };
 
@@ -243,8 +245,6 @@ int ag_launch_pm_sum(ag_ctx* c, int mode, double n_ngb, double G, const double* 
                      bool add = false);
 int ag_launch_backward(ag_ctx* c, const int32_t* idx, int64_t n_act, const double* w,
                        double theta, double eps, double G, double* dLdx, double* dLdm);
-// exclusive scan of n int32 counts into out (n+1 entries; out[n] = total) on c->stream
-int ag_scan_i32(ag_ctx* c, const int32_t* in, int32_t* out, int64_t n);
 // active rows -> ascending sorted positions and walk groups; returns upper bound of groups.
 // With n_dev set the list's length is read on the device (n_act is then its
 // capacity) and, with n_total set, added to *n_total on the device.
@@ -349,6 +349,34 @@ __device__ __forceinline__ double ag_wave_sum_f64(double v) {
     v = ag_dpp_sum<0x142, 0xA>(v);
     v = ag_dpp_sum<0x143, 0xC>(v);
     return ag_last_lane_f64(v);
+}
+
+// exclusive scan of one value per thread over a 256-thread block; *total
+// receives the block's sum
+__device__ __forceinline__ int ag_block_scan256(int v, int* s_tmp, int* total) {
+    const int lane = ag_lane(), w = threadIdx.x >> 6;
+    const int inc = ag_wave_incl_scan(v);
+    if (lane == 63) s_tmp[w] = inc;
+    __syncthreads();
+    int pre = 0, all = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        pre += q < w ? s_tmp[q] : 0;
+        all += s_tmp[q];
+    }
+    __syncthreads();
+    *total = all;
+    return pre + inc - v;
+}
+
+// sum of the totals of the tiles before this one (256 threads, all of them
+// read together): the scans here are a pass that writes each tile's total and
+// one that adds up the totals before its own, with no launch between them
+__device__ __forceinline__ int ag_tiles_before256(const int32_t* __restrict__ tile_sum, int tile, int* s_tmp) {
+    int v = 0, total;
+    for (int t = threadIdx.x; t < tile; t += 256) v += tile_sum[t];
+    ag_block_scan256(v, s_tmp, &total);
+    return total;
 }
 
 // order-preserving map of doubles onto uint64 (for atomic min/max)

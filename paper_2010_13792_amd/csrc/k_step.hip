@@ -75,11 +75,18 @@ __global__ void k_timestep(int64_t n_rows, const int64_t* __restrict__ n_dev, co
 // ---------------------------------------------------------------------------
 // Eq. 3 / Eq. 4 bookkeeping: flag due particles, reset their counters
 // ---------------------------------------------------------------------------
-__global__ void k_select(int64_t n, int64_t* __restrict__ tf, const int8_t* __restrict__ bin,
-                         int64_t step_ticks, int tick_bin, double q_f,
-                         int32_t* __restrict__ flag) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x) {
+// A workgroup takes a tile of rows and leaves the number due in it.
+constexpr int kSelTile = 2048;
+__global__ void __launch_bounds__(kThreads) k_select(int64_t n, int64_t* __restrict__ tf,
+                                                     const int8_t* __restrict__ bin, int64_t step_ticks,
+                                                     int tick_bin, double q_f, int32_t* __restrict__ flag,
+                                                     int32_t* __restrict__ tile_sum) {
+    __shared__ int s_sum[kThreads / 64];
+    int sum = 0;
+#pragma unroll
+    for (int r = 0; r < kSelTile / kThreads; ++r) {
+        const int64_t i = (int64_t)blockIdx.x * kSelTile + r * kThreads + threadIdx.x;
+        if (i >= n) continue;
         int k = bin[i];
         k = k < 0 ? 0 : (k > tick_bin ? tick_bin : k);
         int64_t span = (int64_t)1 << (tick_bin - k);
@@ -88,20 +95,36 @@ __global__ void k_select(int64_t n, int64_t* __restrict__ tf, const int8_t* __re
         int due = ((double)t >= thresh) ? 1 : 0;   // Eq. 4, inclusive
         tf[i] = due ? 0 : t;
         flag[i] = due;
+        sum += due;
+    }
+    sum = ag_wave_sum(sum);
+    if (ag_lane() == 0) s_sum[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int v = 0;
+        for (int w = 0; w < kThreads / 64; ++w) v += s_sum[w];
+        tile_sum[blockIdx.x] = v;
     }
 }
 
-__global__ void k_compact(int64_t n, const int32_t* __restrict__ flag,
-                          const int32_t* __restrict__ off, int32_t* __restrict__ out,
-                          int64_t* __restrict__ count, double* __restrict__ t0, double t) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        if (flag[i]) {
-            out[off[i]] = (int32_t)i;
+__global__ void __launch_bounds__(kThreads) k_compact(int64_t n, const int32_t* __restrict__ flag,
+                                                      const int32_t* __restrict__ tile_sum,
+                                                      int32_t* __restrict__ out, int64_t* __restrict__ count,
+                                                      double* __restrict__ t0, double t) {
+    __shared__ int s_tmp[kThreads / 64];
+    int run = ag_tiles_before256(tile_sum, (int)blockIdx.x, s_tmp);
+    for (int r = 0; r < kSelTile / kThreads; ++r) {
+        const int64_t i = (int64_t)blockIdx.x * kSelTile + r * kThreads + threadIdx.x;
+        const int f = i < n ? flag[i] : 0;
+        int tot;
+        const int e = run + ag_block_scan256(f, s_tmp, &tot);
+        if (f) {
+            out[e] = (int32_t)i;
             if (t0) t0[i] = t;
         }
+        run += tot;
     }
-    if (count && blockIdx.x == 0 && threadIdx.x == 0) *count = (int64_t)off[n];
+    if (count && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *count = (int64_t)run;
 }
 
 // leapfrog kick then drift: v += a dt_kick; x += v dt_drift
@@ -234,136 +257,7 @@ __global__ void k_predict_poly(int64_t n, const uint8_t* __restrict__ mask, int 
     }
 }
 
-// ---------------------------------------------------------------------------
-// device-wide exclusive scan of int32 (three passes: tile sums, scan of the
-// tile sums in one block, tile scans plus offsets)
-// ---------------------------------------------------------------------------
-constexpr int kScanThreads = 1024;
-constexpr int kScanItems = 4;
-constexpr int kScanTile = kScanThreads * kScanItems;
-
-// exclusive scan of `v` across the block; returns the block total in *total
-__device__ __forceinline__ int block_excl_scan(int v, int* s_w, int* total) {
-    const int lane = ag_lane();
-    const int wid = threadIdx.x >> 6;
-    const int nw = blockDim.x >> 6;
-    int inc = ag_wave_incl_scan(v);
-    if (lane == 63) s_w[wid] = inc;
-    __syncthreads();
-    if (wid == 0) {
-        int w = lane < nw ? s_w[lane] : 0;
-        int wi = ag_wave_incl_scan(w);
-        if (lane < nw) s_w[lane] = wi - w;
-        if (lane == nw - 1) s_w[nw] = wi;
-    }
-    __syncthreads();
-    int r = s_w[wid] + inc - v;
-    *total = s_w[nw];
-    __syncthreads();
-    return r;
-}
-
-__global__ void __launch_bounds__(kScanThreads) k_scan_tiles(const int32_t* __restrict__ in, int64_t n,
-                                                             int32_t* __restrict__ tile_sum) {
-    __shared__ int s_w[17];
-    int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-    int s = 0;
-#pragma unroll
-    for (int k = 0; k < kScanItems; ++k)
-        if (base + k < n) s += in[base + k];
-    int tot;
-    block_excl_scan(s, s_w, &tot);
-    if (threadIdx.x == 0) tile_sum[blockIdx.x] = tot;
-}
-
-__global__ void __launch_bounds__(kScanThreads) k_scan_top(int32_t* __restrict__ tile_sum, int64_t ntiles,
-                                                           int32_t* __restrict__ total_out) {
-    __shared__ int s_w[17];
-    // each thread owns a contiguous run of tiles
-    int64_t per = (ntiles + kScanThreads - 1) / kScanThreads;
-    int64_t lo = (int64_t)threadIdx.x * per;
-    int64_t hi = lo + per < ntiles ? lo + per : ntiles;
-    int s = 0;
-    for (int64_t t = lo; t < hi; ++t) s += tile_sum[t];
-    int tot;
-    int off = block_excl_scan(s, s_w, &tot);
-    for (int64_t t = lo; t < hi; ++t) {
-        int v = tile_sum[t];
-        tile_sum[t] = off;
-        off += v;
-    }
-    if (threadIdx.x == 0) *total_out = tot;
-}
-
-__global__ void __launch_bounds__(kScanThreads) k_scan_apply(const int32_t* __restrict__ in, int64_t n,
-                                                             const int32_t* __restrict__ tile_off,
-                                                             int32_t* __restrict__ out) {
-    __shared__ int s_w[17];
-    int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-    int v[kScanItems];
-    int s = 0;
-#pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
-        v[k] = (base + k < n) ? in[base + k] : 0;
-        s += v[k];
-    }
-    int tot;
-    int off = block_excl_scan(s, s_w, &tot) + tile_off[blockIdx.x];
-#pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
-        if (base + k < n) out[base + k] = off;
-        off += v[k];
-    }
-}
-
-// Second pass of the two-launch scan: every tile first sums the totals of
-// the tiles before it (at most kScanThreads * kScanTopItems of them), then
-// scans its own items; the last tile writes the grand total.
-constexpr int kScanTopItems = 4;
-
-__global__ void __launch_bounds__(kScanThreads) k_scan_apply2(const int32_t* __restrict__ in, int64_t n,
-                                                              const int32_t* __restrict__ tile_sum,
-                                                              int32_t* __restrict__ out) {
-    __shared__ int s_w[17];
-    int pre = 0;
-    for (int t = threadIdx.x; t < (int)blockIdx.x; t += kScanThreads) pre += tile_sum[t];
-    int pre_tot;
-    block_excl_scan(pre, s_w, &pre_tot);
-    int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-    int v[kScanItems];
-    int s = 0;
-#pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
-        v[k] = (base + k < n) ? in[base + k] : 0;
-        s += v[k];
-    }
-    int tot;
-    int off = block_excl_scan(s, s_w, &tot) + pre_tot;
-#pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
-        if (base + k < n) out[base + k] = off;
-        off += v[k];
-    }
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[n] = pre_tot + tot;
-}
-
 }  // namespace
-
-int ag_scan_i32(ag_ctx* c, const int32_t* in, int32_t* out, int64_t n) {
-    int64_t ntiles = (n + kScanTile - 1) / kScanTile;
-    if (ntiles < 1) ntiles = 1;
-    AG_TRY(ag_ensure(c, c->scan_tmp, (size_t)ntiles * sizeof(int32_t)));
-    int32_t* ts = c->scan_tmp.as<int32_t>();
-    hipLaunchKernelGGL(k_scan_tiles, dim3((unsigned)ntiles), dim3(kScanThreads), 0, c->stream, in, n, ts);
-    if (ntiles <= (int64_t)kScanThreads * kScanTopItems) {
-        hipLaunchKernelGGL(k_scan_apply2, dim3((unsigned)ntiles), dim3(kScanThreads), 0, c->stream, in, n, ts,
-                           out);
-        return AG_OK;
-    }
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kScanThreads), 0, c->stream, ts, ntiles, out + n);
-    hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)ntiles), dim3(kScanThreads), 0, c->stream, in, n, ts, out);
-    return AG_OK;
-}
 
 int ag_launch_timestep(ag_ctx* c, int64_t n, const int32_t* idx, int64_t n_idx, const double* tidal,
                        double eta, double dt_max, int32_t k_max, double* dt, int8_t* bin, const int64_t* n_dev) {
@@ -401,15 +295,15 @@ int ag_launch_select(ag_ctx* c, int64_t n, int64_t* tf, const int8_t* bin, int64
                      int32_t tick_bin, double q_f, int32_t* active_idx, int64_t* n_active_dev,
                      double* t0, double t) {
     PhaseScope phase(c, AG_PHASE_STEP);
+    const int64_t tiles = (n + kSelTile - 1) / kSelTile;
     AG_TRY(ag_ensure(c, c->sel_flag, (size_t)n * sizeof(int32_t)));
-    AG_TRY(ag_ensure(c, c->sel_off, (size_t)(n + 1) * sizeof(int32_t)));
+    AG_TRY(ag_ensure(c, c->sel_tile, (size_t)tiles * sizeof(int32_t)));
     int32_t* flag = c->sel_flag.as<int32_t>();
-    int32_t* off = c->sel_off.as<int32_t>();
-    hipLaunchKernelGGL(k_select, dim3(grid_for(n)), dim3(kThreads), 0, c->stream, n, tf, bin, step_ticks,
-                       (int)tick_bin, q_f, flag);
-    AG_TRY(ag_scan_i32(c, flag, off, n));
-    hipLaunchKernelGGL(k_compact, dim3(grid_for(n)), dim3(kThreads), 0, c->stream, n, flag, off,
-                       active_idx, n_active_dev, t0, t);
+    int32_t* sum = c->sel_tile.as<int32_t>();
+    hipLaunchKernelGGL(k_select, dim3((unsigned)tiles), dim3(kThreads), 0, c->stream, n, tf, bin, step_ticks,
+                       (int)tick_bin, q_f, flag, sum);
+    hipLaunchKernelGGL(k_compact, dim3((unsigned)tiles), dim3(kThreads), 0, c->stream, n, flag, sum, active_idx,
+                       n_active_dev, t0, t);
     return AG_OK;
 }
 

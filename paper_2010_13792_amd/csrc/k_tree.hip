@@ -57,7 +57,7 @@ __device__ __forceinline__ int sys_of(const int64_t* __restrict__ off, int n_sys
 // ---------------------------------------------------------------------------
 constexpr int64_t kBoxChunk = 2048;
 
-// One block opens a build: system offsets (checked; NULL = one system), the
+// One block opens a build over several systems: system offsets (checked; NULL = one system), the
 // empty bounding boxes, the first box workgroup of each system (exclusive
 // scan of their chunk counts) and a zeroed tree header.
 __global__ void k_build_init(int n_sys, int64_t n, const int64_t* __restrict__ in, int64_t* __restrict__ off,
@@ -108,21 +108,32 @@ __device__ __forceinline__ double in_box(double q, double pbox) {
 // system.  Non-finite coordinates raise the flag and are left out.
 constexpr int kBoxThreads = 384;
 
-__global__ void __launch_bounds__(kBoxThreads) k_box(const double* __restrict__ x, const int64_t* __restrict__ off,
+__global__ void __launch_bounds__(kBoxThreads) k_box(const double* __restrict__ x, int64_t n,
+                                                     int64_t* __restrict__ off,
                                                      int n_sys, const int32_t* __restrict__ blk_off,
                                                      uint64_t* __restrict__ part, int32_t* __restrict__ flags,
-                                                     double pbox) {
+                                                     double pbox, int64_t* __restrict__ hdr, int hdr_words) {
     __shared__ uint64_t s_red[6][kBoxThreads / 64];
     const int b = blockIdx.x;
-    if (b >= blk_off[n_sys]) return;
-    int lo = 0, hi = n_sys;
-    while (hi - lo > 1) {
-        int mid = (lo + hi) >> 1;
-        if (blk_off[mid] <= b) lo = mid; else hi = mid;
+    int64_t i0, i1;
+    if (!blk_off) {   // one system: this launch opens the build
+        i0 = (int64_t)b * kBoxChunk;
+        i1 = i0 + kBoxChunk < n ? i0 + kBoxChunk : n;
+        if (b == 0) {
+            for (int i = threadIdx.x; i < hdr_words; i += blockDim.x) hdr[i] = 0;
+            if (threadIdx.x < 2) off[threadIdx.x] = threadIdx.x ? n : 0;
+        }
+    } else {
+        if (b >= blk_off[n_sys]) return;
+        int lo = 0, hi = n_sys;
+        while (hi - lo > 1) {
+            int mid = (lo + hi) >> 1;
+            if (blk_off[mid] <= b) lo = mid; else hi = mid;
+        }
+        const int s = lo;
+        i0 = off[s] + (int64_t)(b - blk_off[s]) * kBoxChunk;
+        i1 = i0 + kBoxChunk < off[s + 1] ? i0 + kBoxChunk : off[s + 1];
     }
-    const int s = lo;
-    const int64_t i0 = off[s] + (int64_t)(b - blk_off[s]) * kBoxChunk;
-    const int64_t i1 = i0 + kBoxChunk < off[s + 1] ? i0 + kBoxChunk : off[s + 1];
     const int c = threadIdx.x % 3;   // kBoxThreads is a multiple of 3
     double mn = DBL_MAX, mx = -DBL_MAX;
     bool bad = false;
@@ -172,13 +183,14 @@ __global__ void __launch_bounds__(kBoxThreads) k_box(const double* __restrict__ 
 }
 
 // one workgroup per system: its box from the partial boxes of its workgroups
-__global__ void k_box_reduce(int n_sys, const int32_t* __restrict__ blk_off, const uint64_t* __restrict__ part,
-                             uint64_t* __restrict__ box) {
+__global__ void k_box_reduce(int n_sys, const int32_t* __restrict__ blk_off, int nparts,
+                             const uint64_t* __restrict__ part, uint64_t* __restrict__ box) {
     __shared__ uint64_t s_red[6][4];
     const int s = blockIdx.x;
     if (s >= n_sys) return;
     uint64_t v[6] = {~0ull, ~0ull, ~0ull, 0ull, 0ull, 0ull};
-    for (int b = blk_off[s] + threadIdx.x; b < blk_off[s + 1]; b += blockDim.x)
+    const int b0 = blk_off ? blk_off[s] : 0, b1 = blk_off ? blk_off[s + 1] : nparts;
+    for (int b = b0 + threadIdx.x; b < b1; b += blockDim.x)
 #pragma unroll
         for (int k = 0; k < 6; ++k) {
             const uint64_t q = part[6 * (int64_t)b + k];
@@ -214,39 +226,83 @@ __device__ __forceinline__ uint64_t spread3(uint64_t v) {
     return v;
 }
 
-__global__ void k_keys(int64_t n, const double* __restrict__ x, const int64_t* __restrict__ off, int n_sys,
-                       int bits, const uint64_t* __restrict__ box, uint64_t* __restrict__ keys,
-                       int32_t* __restrict__ vals, double pbox) {
+// Key of a position in a system's box (lo, ext: its corner and longest side).
+// A periodic tree's root cell is the box itself, split exactly at half of it:
+// no cell below it crosses the planes where sources change image about a
+// multiple of half the box.
+struct KeyBox {
+    double lo[3], inv;
+};
+__device__ __forceinline__ KeyBox key_box(const uint64_t* __restrict__ box, double scale_cells, double pbox) {
+    KeyBox B;
+    double ext = 0.0;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        B.lo[c] = ag_unord(box[c]);
+        double e = ag_unord(box[3 + c]) - B.lo[c];
+        ext = e > ext ? e : ext;
+    }
+    if (!(ext > 0.0) || !isfinite(ext)) ext = 1.0;
+    if (pbox > 0.0) B.lo[0] = B.lo[1] = B.lo[2] = 0.0;
+    B.inv = pbox > 0.0 ? scale_cells / pbox : scale_cells / (ext * (1.0 + 1e-12));
+    return B;
+}
+__device__ __forceinline__ uint64_t morton_key(const double* __restrict__ x, const KeyBox& B, int64_t maxc,
+                                               double pbox) {
+    uint64_t code = 0;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        double q = (in_box(x[c], pbox) - B.lo[c]) * B.inv;
+        int64_t k = isfinite(q) ? (int64_t)q : 0;
+        k = k < 0 ? 0 : (k > maxc ? maxc : k);
+        code |= spread3((uint64_t)k) << (2 - c);
+    }
+    return code;
+}
+
+// box of one system from its workgroups' partial boxes, by a whole workgroup
+__device__ __forceinline__ void reduce_box(const uint64_t* __restrict__ part, int nparts, uint64_t (*s_red)[16],
+                                           uint64_t* s_box) {
+    uint64_t v[6] = {~0ull, ~0ull, ~0ull, 0ull, 0ull, 0ull};
+    for (int b = threadIdx.x; b < nparts; b += blockDim.x)
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            const uint64_t q = part[6 * (int64_t)b + k];
+            v[k] = k < 3 ? (q < v[k] ? q : v[k]) : (q > v[k] ? q : v[k]);
+        }
+    const int lane = ag_lane(), w = threadIdx.x >> 6;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        const uint64_t r = k < 3 ? ag_wave_min(v[k]) : ag_wave_max(v[k]);
+        if (lane == 0) s_red[k][w] = r;
+    }
+    __syncthreads();
+    if (threadIdx.x < 6) {
+        const int k = threadIdx.x;
+        uint64_t r = s_red[k][0];
+        for (int q = 1; q < (int)(blockDim.x >> 6); ++q) r = k < 3 ? (s_red[k][q] < r ? s_red[k][q] : r)
+                                                                  : (s_red[k][q] > r ? s_red[k][q] : r);
+        s_box[k] = r;
+    }
+    __syncthreads();
+}
+
+// nparts > 0: one system, whose box every workgroup reduces for itself from
+// the nparts partial boxes at `box` (no launch of its own: 4.7 us)
+__global__ void __launch_bounds__(kThreads) k_keys(int64_t n, const double* __restrict__ x,
+                                                   const int64_t* __restrict__ off, int n_sys, int bits,
+                                                   const uint64_t* __restrict__ box, int nparts,
+                                                   uint64_t* __restrict__ keys, int32_t* __restrict__ vals,
+                                                   double pbox) {
+    __shared__ uint64_t s_red[6][16], s_box[6];
     const double scale_cells = (double)(1u << bits);
     const int64_t maxc = ((int64_t)1 << bits) - 1;
+    if (nparts > 0) reduce_box(box, nparts, s_red, s_box);
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x) {
         const int s = n_sys > 1 ? sys_of(off, n_sys, i) : 0;
-        double lo[3], ext = 0.0;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            lo[c] = ag_unord(box[6 * s + c]);
-            double e = ag_unord(box[6 * s + 3 + c]) - lo[c];
-            ext = e > ext ? e : ext;
-        }
-        if (!(ext > 0.0) || !isfinite(ext)) ext = 1.0;
-        if (pbox > 0.0) {   // a periodic tree's root cell is the box itself
-            lo[0] = lo[1] = lo[2] = 0.0;
-            ext = pbox;
-        }
-        // (a periodic root is split exactly at half the box: no cell below it
-        // crosses the planes where sources change image about a multiple of
-        // half the box)
-        const double inv = pbox > 0.0 ? scale_cells / pbox : scale_cells / (ext * (1.0 + 1e-12));
-        uint64_t code = 0;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            double q = (in_box(x[3 * i + c], pbox) - lo[c]) * inv;
-            int64_t k = isfinite(q) ? (int64_t)q : 0;
-            k = k < 0 ? 0 : (k > maxc ? maxc : k);
-            code |= spread3((uint64_t)k) << (2 - c);
-        }
-        keys[i] = ((uint64_t)s << (3 * bits)) | code;
+        const KeyBox B = key_box(nparts > 0 ? s_box : box + 6 * s, scale_cells, pbox);
+        keys[i] = ((uint64_t)s << (3 * bits)) | morton_key(x + 3 * i, B, maxc, pbox);
         vals[i] = (int32_t)i;
     }
 }
@@ -256,9 +312,10 @@ __global__ void k_keys(int64_t n, const double* __restrict__ x, const int64_t* _
 // ---------------------------------------------------------------------------
 constexpr int kRsItems = 16;
 constexpr int kRsTile = kThreads * kRsItems;
+constexpr int kRsFew = 64;
 
 __global__ void __launch_bounds__(kThreads) k_rs_hist(const uint64_t* __restrict__ keys, int64_t n, int shift,
-                                                      int nblocks, int32_t* __restrict__ hist) {
+                                                      int nblocks, int by_tile, int32_t* __restrict__ hist) {
     __shared__ int s_h[4][256];
     for (int w = 0; w < 4; ++w) s_h[w][threadIdx.x] = 0;
     __syncthreads();
@@ -271,25 +328,7 @@ __global__ void __launch_bounds__(kThreads) k_rs_hist(const uint64_t* __restrict
     }
     __syncthreads();
     int t = s_h[0][threadIdx.x] + s_h[1][threadIdx.x] + s_h[2][threadIdx.x] + s_h[3][threadIdx.x];
-    hist[(int64_t)threadIdx.x * nblocks + blockIdx.x] = t;
-}
-
-// exclusive scan of one value per thread over a 256-thread block; *total
-// receives the block's sum
-__device__ __forceinline__ int block_excl_scan256(int v, int* s_tmp, int* total) {
-    const int lane = ag_lane(), w = threadIdx.x >> 6;
-    const int inc = ag_wave_incl_scan(v);
-    if (lane == 63) s_tmp[w] = inc;
-    __syncthreads();
-    int pre = 0, all = 0;
-#pragma unroll
-    for (int q = 0; q < kThreads / 64; ++q) {
-        pre += q < w ? s_tmp[q] : 0;
-        all += s_tmp[q];
-    }
-    __syncthreads();
-    *total = all;
-    return pre + inc - v;
+    hist[by_tile ? (int64_t)blockIdx.x * 256 + threadIdx.x : (int64_t)threadIdx.x * nblocks + blockIdx.x] = t;
 }
 
 // Per digit d (one block each): exclusive scan of the per-block counts
@@ -303,7 +342,7 @@ __global__ void __launch_bounds__(kThreads) k_rs_rowscan(const int32_t* __restri
         const int b = b0 + threadIdx.x;
         const int v = b < nblocks ? hist[row + b] : 0;
         int sum;
-        const int ex = block_excl_scan256(v, s_tmp, &sum);
+        const int ex = ag_block_scan256(v, s_tmp, &sum);
         if (b < nblocks) hoff[row + b] = carry + ex;
         carry += sum;
     }
@@ -318,7 +357,10 @@ __global__ void __launch_bounds__(kThreads) k_rs_rowscan(const int32_t* __restri
 // digit over the four waves then places every element in the tile's
 // digit-ordered LDS copy, which is written out so that each digit's run goes
 // to consecutive addresses.  With `rank` set (last pass), rank[value]
-// receives the value's final position.
+// receives the value's final position.  With hoff null the counts come tile by
+// tile (hist[tile][digit]) and every workgroup adds up the tiles before its own
+// and all of them itself: with at most kRsFew tiles that is a few reads in
+// flight together and saves the row scan's launch (4.3 us a pass).
 __global__ void __launch_bounds__(kThreads) k_rs_scatter(const uint64_t* __restrict__ kin,
                                                          const int32_t* __restrict__ vin, int64_t n,
                                                          int shift, int nblocks,
@@ -336,11 +378,24 @@ __global__ void __launch_bounds__(kThreads) k_rs_scatter(const uint64_t* __restr
     __shared__ int s_tmp[kThreads / 64];
     const int t = threadIdx.x, w = t >> 6, lane = t & 63;
     {
-        int all;
-        const int base_d = block_excl_scan256(tot[t], s_tmp, &all);
-        const int loc = block_excl_scan256(hist[(int64_t)t * nblocks + blockIdx.x], s_tmp, &all);
+        int all, total, before, own;   // of digit t: all of it, in the tiles before, in this tile
+        if (hoff) {
+            total = tot[t];
+            before = hoff[(int64_t)t * nblocks + blockIdx.x];
+            own = hist[(int64_t)t * nblocks + blockIdx.x];
+        } else {
+            total = before = own = 0;
+            for (int b = 0; b < nblocks; ++b) {
+                const int v = hist[(int64_t)b * 256 + t];
+                total += v;
+                before += b < (int)blockIdx.x ? v : 0;
+                own = b == (int)blockIdx.x ? v : own;
+            }
+        }
+        const int base_d = ag_block_scan256(total, s_tmp, &all);
+        const int loc = ag_block_scan256(own, s_tmp, &all);
         s_loc[t] = loc;
-        s_gofs[t] = base_d + hoff[(int64_t)t * nblocks + blockIdx.x] - loc;
+        s_gofs[t] = base_d + before - loc;
     }
 #pragma unroll
     for (int q = 0; q < 4; ++q) s_w[q][t] = 0;
@@ -408,6 +463,104 @@ __global__ void __launch_bounds__(kThreads) k_rs_scatter(const uint64_t* __restr
     }
 }
 
+// Keys and the four passes of up to kSmallSort particles of one system in one
+// workgroup: the pairs stay in LDS, a wave ranks runs of 64 by ballots as above
+// (3000 particles: 10 launches of the passes less, 45 us).  The result is that
+// of the passes: a stable sort by key bits 31 .. 62.
+constexpr int kSmallSort = 4096;
+constexpr int kSmallThreads = 1024;
+__global__ void __launch_bounds__(kSmallThreads) k_small_sort(int n, const double* __restrict__ x,
+                                                              const uint64_t* __restrict__ part, int nparts,
+                                                              int shift0, uint64_t* __restrict__ kout,
+                                                              int32_t* __restrict__ vout,
+                                                              int32_t* __restrict__ rank, double pbox) {
+    constexpr int kWavesB = kSmallThreads / 64;
+    constexpr int kItems = kSmallSort / kSmallThreads;
+    __shared__ uint64_t s_key[kSmallSort];
+    __shared__ int s_val[kSmallSort];
+    __shared__ int s_w[kWavesB][256];
+    __shared__ int s_loc[256], s_tmp[4];
+    __shared__ uint64_t s_red[6][16], s_box[6];
+    const int t = threadIdx.x, w = t >> 6, lane = t & 63;
+    reduce_box(part, nparts, s_red, s_box);
+    const KeyBox B = key_box(s_box, (double)(1u << AG_MAX_LEVEL), pbox);
+    // a wave's own run of kItems x 64 positions
+    const int base = w * kItems * 64;
+    uint64_t key[kItems];
+    int val[kItems], rk[kItems];
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+        const int i = base + k * 64 + lane;
+        key[k] = i < n ? morton_key(x + 3 * (int64_t)i, B, ((int64_t)1 << AG_MAX_LEVEL) - 1, pbox) : 0;
+        val[k] = i;
+    }
+    for (int pass = 0; pass < 4; ++pass) {
+        const int shift = shift0 + 8 * pass;
+        for (int i = t; i < kWavesB * 256; i += kSmallThreads) (&s_w[0][0])[i] = 0;
+        __syncthreads();
+        int* cnt_w = s_w[w];
+#pragma unroll
+        for (int k = 0; k < kItems; ++k) {
+            const bool valid = base + k * 64 + lane < n;
+            const int d = (int)((key[k] >> shift) & 255);
+            uint64_t peers = __ballot(valid);
+#pragma unroll
+            for (int b = 0; b < 8; ++b) {
+                const bool bit = (d >> b) & 1;
+                const uint64_t bb = __ballot(bit);
+                peers &= bit ? bb : ~bb;
+            }
+            const int r = ag_prefix_count(peers);
+            int before = 0;
+            if (valid) before = cnt_w[d];
+            if (valid && r == 0) cnt_w[d] = before + __popcll(peers);
+            rk[k] = before + r;
+        }
+        __syncthreads();
+        int run = 0;
+        if (t < 256)
+            for (int q = 0; q < kWavesB; ++q) {
+                const int c = s_w[q][t];
+                s_w[q][t] = run;
+                run += c;
+            }
+        const int inc = t < 256 ? ag_wave_incl_scan(run) : 0;
+        if (t < 256 && lane == 63) s_tmp[w] = inc;
+        __syncthreads();
+        if (t < 256) {
+            int pre = 0;
+            for (int q = 0; q < 4; ++q) pre += q < w ? s_tmp[q] : 0;
+            s_loc[t] = pre + inc - run;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kItems; ++k)
+            if (base + k * 64 + lane < n) {
+                const int d = (int)((key[k] >> shift) & 255);
+                const int slot = s_loc[d] + cnt_w[d] + rk[k];
+                s_key[slot] = key[k];
+                s_val[slot] = val[k];
+            }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kItems; ++k) {
+            const int i = base + k * 64 + lane;
+            key[k] = i < n ? s_key[i] : 0;
+            val[k] = i < n ? s_val[i] : 0;
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+        const int i = base + k * 64 + lane;
+        if (i < n) {
+            kout[i] = key[k];
+            vout[i] = val[k];
+            rank[val[k]] = i;
+        }
+    }
+}
+
 int grid_for(int64_t n, int threads = kThreads) {
     int64_t b = (n + threads - 1) / threads;
     if (b > 8192) b = 8192;
@@ -424,15 +577,19 @@ int grid_for(int64_t n, int threads = kThreads) {
 //    on randomly ordered input: the gathered 24-byte reads cost more than
 //    the merged stores.)
 // ---------------------------------------------------------------------------
+__device__ __forceinline__ void to_sorted(int64_t i, const int32_t* __restrict__ rank, const double* __restrict__ x,
+                                          const double* __restrict__ m, double4* __restrict__ spos, double pbox,
+                                          const double* __restrict__ h, float* __restrict__ sh) {
+    const int64_t p = rank[i];
+    spos[p] = make_double4(in_box(x[3 * i], pbox), in_box(x[3 * i + 1], pbox), in_box(x[3 * i + 2], pbox), m[i]);
+    if (h) sh[p] = f_up(h[i]);   // per-particle softening, rounded up
+}
 __global__ void k_to_sorted_pos(int64_t n, const int32_t* __restrict__ rank, const double* __restrict__ x,
                                 const double* __restrict__ m, double4* __restrict__ spos, double pbox,
                                 const double* __restrict__ h, float* __restrict__ sh) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t p = rank[i];
-        spos[p] = make_double4(in_box(x[3 * i], pbox), in_box(x[3 * i + 1], pbox), in_box(x[3 * i + 2], pbox), m[i]);
-        if (h) sh[p] = f_up(h[i]);   // per-particle softening, rounded up
-    }
+         i += (int64_t)gridDim.x * blockDim.x)
+        to_sorted(i, rank, x, m, spos, pbox, h, sh);
 }
 void launch_to_sorted(ag_ctx* c, int64_t n, const double* x, const double* m, double pbox) {
     const int32_t* rank = c->rank.as<int32_t>();
@@ -453,7 +610,7 @@ __device__ __forceinline__ int common_digits(uint64_t a, uint64_t b) {
 // Minima of the shared-digit counts over aligned runs of 16^(k+1) positions,
 // k = 0 .. 5 (16 positions up to 2^24): the search for a far cell end skips
 // whole runs with them.  Levels 0-2 are written by k_cdig (a workgroup pass
-// covers 4096 positions), levels 3-5 by k_cd_min_top.
+// covers 4096 positions), levels 3-5 by cd_min_top.
 constexpr int kCdLevels = 6;
 struct CdMin {
     int32_t* lev[kCdLevels];
@@ -461,11 +618,29 @@ struct CdMin {
 constexpr int kRun = 256;                 // threads of k_cdig
 constexpr int64_t kCdPass = 16 * kRun;   // positions per k_cdig workgroup pass
 
+// What moving the particles into key order needs (k_cdig does both: neither
+// depends on the other).
+struct ToSorted {
+    const int32_t* rank;
+    const double* x;
+    const double* m;
+    double4* spos;
+    double pbox;
+    const double* h;
+    float* sh;
+};
+
 __global__ void __launch_bounds__(kRun) k_cdig(int64_t n, const uint64_t* __restrict__ keys, int32_t* __restrict__ cd,
-                                               CdMin M) {
+                                               CdMin M, int cd_blocks, ToSorted Q) {
     __shared__ int s_w[16][kRun / 64];
+    if ((int)blockIdx.x >= cd_blocks) {   // the workgroups past the first cd_blocks move the particles
+        const int64_t b = (int64_t)blockIdx.x - cd_blocks, nb = (int64_t)gridDim.x - cd_blocks;
+        for (int64_t i = b * blockDim.x + threadIdx.x; i < n; i += nb * blockDim.x)
+            to_sorted(i, Q.rank, Q.x, Q.m, Q.spos, Q.pbox, Q.h, Q.sh);
+        return;
+    }
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    for (int64_t g = blockIdx.x; g * kCdPass < n; g += gridDim.x) {
+    for (int64_t g = blockIdx.x; g * kCdPass < n; g += cd_blocks) {
         for (int j = 0; j < 16; ++j) {
             const int64_t p = g * kCdPass + j * kRun + threadIdx.x;
             int v = INT_MAX;
@@ -501,7 +676,7 @@ __global__ void __launch_bounds__(kRun) k_cdig(int64_t n, const uint64_t* __rest
 struct CdCounts {
     int64_t cnt[kCdLevels];
 };
-__global__ void k_cd_min_top(CdMin M, CdCounts C) {
+__device__ void cd_min_top(const CdMin& M, const CdCounts& C) {
     for (int k = 3; k < kCdLevels; ++k) {
         for (int64_t i = threadIdx.x; i < C.cnt[k]; i += blockDim.x) {
             int m = INT_MAX;
@@ -562,13 +737,24 @@ struct TopoParams {
 //    some q in (p, p + n_leaf] has cd'[q] < l, i.e. iff l > mn, mn the
 //    minimum of cd' there; so the leaf is at L = max(c + 1, system levels,
 //    min(21, mn + 1)) and L - c nodes start at p.
+// A workgroup takes a tile of consecutive positions and writes the tile's two
+// totals; k_node_offsets turns them into offsets.  The last workgroup, past the
+// tiles, forms the upper shared-digit minima.
 constexpr int kWin = 64;   // largest n_leaf
 
-__global__ void __launch_bounds__(kThreads) k_count_nodes(TopoParams P, const int32_t* __restrict__ cd,
-                                                          int32_t* __restrict__ cnt, int32_t* __restrict__ icnt) {
+__global__ void __launch_bounds__(kThreads) k_count_nodes(TopoParams P, const int32_t* __restrict__ cd, int tile,
+                                                          int32_t* __restrict__ cnt, int32_t* __restrict__ icnt,
+                                                          int2* __restrict__ tile_sum, CdMin M, CdCounts C) {
     __shared__ int s_cd[kThreads + 2 * kWin];
+    __shared__ int s_sum[2][kThreads / 64];
+    if (blockIdx.x == gridDim.x - 1) {
+        cd_min_top(M, C);
+        return;
+    }
     const int W = P.n_leaf;
-    for (int64_t p0 = (int64_t)blockIdx.x * kThreads; p0 < P.n; p0 += (int64_t)gridDim.x * kThreads) {
+    int nodes = 0, inner = 0;
+    const int64_t end = ((int64_t)blockIdx.x + 1) * tile < P.n ? ((int64_t)blockIdx.x + 1) * tile : P.n;
+    for (int64_t p0 = (int64_t)blockIdx.x * tile; p0 < end; p0 += kThreads) {
         __syncthreads();
         for (int k = threadIdx.x; k < kThreads + 2 * W; k += kThreads) {
             const int64_t q = p0 - W + k;
@@ -603,6 +789,58 @@ __global__ void __launch_bounds__(kThreads) k_count_nodes(TopoParams P, const in
         }
         cnt[p] = k;
         icnt[p] = k > 0 ? k - 1 : 0;
+        nodes += k;
+        inner += k > 0 ? k - 1 : 0;
+    }
+    nodes = ag_wave_sum(nodes);
+    inner = ag_wave_sum(inner);
+    if (ag_lane() == 0) {
+        s_sum[0][threadIdx.x >> 6] = nodes;
+        s_sum[1][threadIdx.x >> 6] = inner;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int2 t = make_int2(0, 0);
+        for (int w = 0; w < kThreads / 64; ++w) {
+            t.x += s_sum[0][w];
+            t.y += s_sum[1][w];
+        }
+        tile_sum[blockIdx.x] = t;
+    }
+}
+
+// Exclusive scans of both counts: every tile adds up the totals of the tiles
+// before it (read together; no scan launch of their own) and scans its own.
+__global__ void __launch_bounds__(kThreads) k_node_offsets(int64_t n, int tile, const int32_t* __restrict__ cnt,
+                                                           const int32_t* __restrict__ icnt,
+                                                           const int2* __restrict__ tile_sum,
+                                                           int32_t* __restrict__ off, int32_t* __restrict__ ioff) {
+    __shared__ int s_tmp[kThreads / 64];
+    int a = 0, b = 0;
+    for (int t = threadIdx.x; t < (int)blockIdx.x; t += kThreads) {
+        const int2 v = tile_sum[t];
+        a += v.x;
+        b += v.y;
+    }
+    int run, irun;
+    ag_block_scan256(a, s_tmp, &run);
+    ag_block_scan256(b, s_tmp, &irun);
+    const int64_t p1 = ((int64_t)blockIdx.x + 1) * tile < n ? ((int64_t)blockIdx.x + 1) * tile : n;
+    for (int64_t p0 = (int64_t)blockIdx.x * tile; p0 < p1; p0 += 2 * kThreads) {
+        const int64_t p = p0 + 2 * threadIdx.x;   // tiles are multiples of 512: p is even
+        int c0 = 0, c1 = 0, i0 = 0, i1 = 0, tot;
+        if (p < p1) { c0 = cnt[p]; i0 = icnt[p]; }
+        if (p + 1 < p1) { c1 = cnt[p + 1]; i1 = icnt[p + 1]; }
+        const int e = run + ag_block_scan256(c0 + c1, s_tmp, &tot);
+        run += tot;
+        const int ie = irun + ag_block_scan256(i0 + i1, s_tmp, &tot);
+        irun += tot;
+        if (p < p1) { off[p] = e; ioff[p] = ie; }
+        if (p + 1 < p1) { off[p + 1] = e + c0; ioff[p + 1] = ie + i0; }
+    }
+    if (p1 == n && threadIdx.x == 0) {
+        off[n] = run;
+        ioff[n] = irun;
     }
 }
 
@@ -640,20 +878,16 @@ constexpr int kSortedShift = 31;
 constexpr int kCellShift = 33;
 constexpr int kSegLds = 2048;   // cells up to this size sort in LDS
 
-__global__ void k_seg_heads(int64_t n, const uint64_t* __restrict__ k, int n_leaf, int32_t* __restrict__ flag) {
+// Lists the dense cells (in any order: each is sorted on its own): *count, zero
+// before, ends as their number.
+__global__ void k_seg_heads(int64_t n, const uint64_t* __restrict__ k, int n_leaf, int32_t* __restrict__ list,
+                            int32_t* __restrict__ count) {
     for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < n;
          p += (int64_t)gridDim.x * blockDim.x) {
         const uint64_t c = k[p] >> kCellShift;
         const bool head = p == 0 || (k[p - 1] >> kCellShift) != c;
-        flag[p] = head && p + n_leaf < n && (k[p + n_leaf] >> kCellShift) == c;
+        if (head && p + n_leaf < n && (k[p + n_leaf] >> kCellShift) == c) list[atomicAdd(count, 1)] = (int32_t)p;
     }
-}
-
-__global__ void k_seg_list(int64_t n, const int32_t* __restrict__ flag, const int32_t* __restrict__ off,
-                           int32_t* __restrict__ list) {
-    for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < n;
-         p += (int64_t)gridDim.x * blockDim.x)
-        if (flag[p]) list[off[p]] = (int32_t)p;
 }
 
 __device__ __forceinline__ bool pair_greater(uint64_t ka, int va, uint64_t kb, int vb) {
@@ -793,7 +1027,7 @@ __global__ void __launch_bounds__(kThreads) k_seg_sort(TopoParams P, const int32
 // fields are written there), gathered per wave in LDS and appended to the
 // global list with one atomic per workgroup (or per wave when its LDS list
 // fills).  The inner nodes per level and the deepest level go to
-// per-workgroup slots that k_tree_close adds up.
+// per-workgroup slots that tree_close adds up.
 constexpr int kWriteBlocks = 2048;   // eight workgroups per CU at most
 constexpr int kWaveLook = 208;       // positions searched past a wave's run (>= n_leaf + 1)
 constexpr int kWaveWin = 64 + kWaveLook;   // 17 runs of 16
@@ -951,7 +1185,7 @@ __global__ void __launch_bounds__(kThreads) k_write_nodes(TopoParams P, const in
             far_t[base + i] = s_ft[w][i];
         }
     }
-    // per-workgroup inner nodes per level and deepest level, reduced by k_tree_close
+    // per-workgroup inner nodes per level and deepest level, reduced by tree_close
     __shared__ int s_max[kWaves];
     maxl = ag_wave_max(maxl);
     if (lane == 0) s_max[w] = maxl;
@@ -1014,43 +1248,24 @@ __device__ int64_t next_below16(int64_t n, const int32_t* __restrict__ cd, const
     return i;
 }
 
-// Skip and count fields of the nodes k_write_nodes listed: a group of 16
-// lanes per entry (p, t) takes the nodes t, t - 1, .. 0 at p, each end found
-// from the one below it, the first from the end of the window k_write_nodes
-// searched (no shared-digit count there is below the level of node t, so
-// none is below the levels above it either).
-__global__ void __launch_bounds__(kThreads) k_far_ends(TopoParams P, const int32_t* __restrict__ cd, CdMin M,
-                                                       const int32_t* __restrict__ off,
-                                                       const int32_t* __restrict__ far_p,
-                                                       const int32_t* __restrict__ far_t,
-                                                       const int64_t* __restrict__ hdr, int4* __restrict__ link) {
-    const int64_t nq = hdr[3];
-    const int64_t n_nodes = off[P.n];
-    const int s = threadIdx.x & 15;
-    for (int64_t g = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 4; g < nq;
-         g += ((int64_t)gridDim.x * blockDim.x) >> 4) {
-        const int64_t p = far_p[g];
-        const int c = cd[p];
-        int64_t e = (p & ~(int64_t)63) + kWaveWin;   // the end of the wave's window
-        for (int t = far_t[g]; t >= 0; --t) {
-            e = next_below16(P.n, cd, M, e, c + 1 + t, s);
-            if (s == 0) {
-                int4* L = link + off[p] + t;
-                L->x = (int)(e < P.n ? (int64_t)off[e] : n_nodes);
-                L->z = (int)(e - p);
-            }
-        }
-    }
-}
-
 // One block closes the topology: the inner nodes per level and hdr[1] =
 // deepest level (from the per-workgroup rows of k_write_nodes), the end of
 // the leaves' start list, and the root node of every system.
-__global__ void k_tree_close(int nblk, const int32_t* __restrict__ blk, int64_t* __restrict__ hdr,
-                             int32_t* __restrict__ leaf_pos, int64_t n, int n_sys,
-                             int sys_levels, const int64_t* __restrict__ off, const int32_t* __restrict__ cd,
-                             const int32_t* __restrict__ noff, int32_t* __restrict__ root) {
+struct CloseArgs {
+    int nblk;
+    const int32_t* blk;
+    int32_t* leaf_pos;
+    int n_sys;
+    const int64_t* off;
+    int32_t* root;
+    int64_t* depth;   // pinned host word (null: none)
+};
+__device__ void tree_close(const CloseArgs& Q, const TopoParams& P, const int32_t* __restrict__ cd,
+                           const int32_t* __restrict__ noff, int64_t* __restrict__ hdr) {
     __shared__ int s_sum[kLevels + 1][16];
+    const int nblk = Q.nblk, n_sys = Q.n_sys;
+    const int32_t* __restrict__ blk = Q.blk;
+    const int64_t* __restrict__ off = Q.off;
     const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
     int v[kLevels + 1];
 #pragma unroll
@@ -1072,16 +1287,55 @@ __global__ void k_tree_close(int nblk, const int32_t* __restrict__ blk, int64_t*
         int t = 0;
         for (int k = 0; k < nw; ++k) t = l < kLevels ? t + s_sum[l][k] : (s_sum[l][k] > t ? s_sum[l][k] : t);
         if (l < kLevels) reinterpret_cast<int32_t*>(hdr + 8)[kLvlCnt + l] = t;
-        else hdr[1] = t;
+        else {
+            hdr[1] = t;
+            // this tree's depth, for the next build's launch plan (any
+            // build's will do: the host reads it without waiting)
+            if (Q.depth) __hip_atomic_store(Q.depth, (int64_t)t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
     }
-    if (threadIdx.x == 0) leaf_pos[hdr[0] - hdr[2]] = (int32_t)n;
+    if (threadIdx.x == 0) Q.leaf_pos[hdr[0] - hdr[2]] = (int32_t)P.n;
     for (int s = threadIdx.x; s < n_sys; s += blockDim.x) {
         const int64_t p0 = off[s];
         if (off[s + 1] <= p0) {
-            root[s] = -1;
+            Q.root[s] = -1;
             continue;
         }
-        root[s] = noff[p0] + (sys_levels - cd[p0] - 1);
+        Q.root[s] = noff[p0] + (P.sys_levels - cd[p0] - 1);
+    }
+}
+
+// Skip and count fields of the nodes k_write_nodes listed: a group of 16
+// lanes per entry (p, t) takes the nodes t, t - 1, .. 0 at p, each end found
+// from the one below it, the first from the end of the window k_write_nodes
+// searched (no shared-digit count there is below the level of node t, so
+// none is below the levels above it either).
+__global__ void __launch_bounds__(kThreads) k_far_ends(TopoParams P, const int32_t* __restrict__ cd, CdMin M,
+                                                       const int32_t* __restrict__ off,
+                                                       const int32_t* __restrict__ far_p,
+                                                       const int32_t* __restrict__ far_t,
+                                                       int64_t* __restrict__ hdr, int4* __restrict__ link,
+                                                       CloseArgs Q) {
+    if (blockIdx.x == 0) {
+        tree_close(Q, P, cd, off, hdr);
+        return;
+    }
+    const int64_t nq = hdr[3];
+    const int64_t n_nodes = off[P.n];
+    const int s = threadIdx.x & 15;
+    for (int64_t g = ((blockIdx.x - 1) * (int64_t)blockDim.x + threadIdx.x) >> 4; g < nq;
+         g += ((int64_t)(gridDim.x - 1) * blockDim.x) >> 4) {
+        const int64_t p = far_p[g];
+        const int c = cd[p];
+        int64_t e = (p & ~(int64_t)63) + kWaveWin;   // the end of the wave's window
+        for (int t = far_t[g]; t >= 0; --t) {
+            e = next_below16(P.n, cd, M, e, c + 1 + t, s);
+            if (s == 0) {
+                int4* L = link + off[p] + t;
+                L->x = (int)(e < P.n ? (int64_t)off[e] : n_nodes);
+                L->z = (int)(e - p);
+            }
+        }
     }
 }
 
@@ -1311,14 +1565,24 @@ template <int G> __device__ __forceinline__ void grp_reduce(MomentSums& S) {
 // empty), from the pre-order links (the first child follows the node, the
 // next follows the first child's subtree, ...).  A level's kernels then read
 // a node and its children from the same slot.
-__global__ void __launch_bounds__(kThreads) k_level_lists(const int64_t* __restrict__ hdr,
-                                                          const int32_t* __restrict__ ilist,
-                                                          const int4* __restrict__ link,
-                                                          const uint64_t* __restrict__ keys,
-                                                          int4* __restrict__ child,
-                                                          int32_t* __restrict__ lvl,
-                                                          int32_t* __restrict__ lvl_list,
-                                                          int32_t* __restrict__ nslot) {
+struct ListArgs {
+    int blocks;   // workgroups that make the lists (0: none)
+    const int32_t* ilist;
+    const int4* link;
+    const uint64_t* keys;
+    int4* child;
+    int32_t* lvl;
+    int32_t* lvl_list;
+    int32_t* nslot;
+};
+__device__ __forceinline__ void level_lists(const ListArgs& Q, const int64_t* __restrict__ hdr) {
+    const int32_t* __restrict__ ilist = Q.ilist;
+    const int4* __restrict__ link = Q.link;
+    const uint64_t* __restrict__ keys = Q.keys;
+    int4* __restrict__ child = Q.child;
+    int32_t* __restrict__ lvl = Q.lvl;
+    int32_t* __restrict__ lvl_list = Q.lvl_list;
+    int32_t* __restrict__ nslot = Q.nslot;
     __shared__ int s_off[AG_MAX_LEVEL + 2], s_cnt[AG_MAX_LEVEL + 1], s_base[AG_MAX_LEVEL + 1];
     const int64_t ni = hdr[2];
     if (threadIdx.x == 0) {
@@ -1332,7 +1596,7 @@ __global__ void __launch_bounds__(kThreads) k_level_lists(const int64_t* __restr
     if (threadIdx.x <= AG_MAX_LEVEL) s_cnt[threadIdx.x] = 0;
     __syncthreads();
     if (blockIdx.x == 0 && threadIdx.x <= AG_MAX_LEVEL + 1) lvl[kLvlOff + threadIdx.x] = s_off[threadIdx.x];
-    for (int64_t t0 = (int64_t)blockIdx.x * kThreads; t0 < ni; t0 += (int64_t)gridDim.x * kThreads) {
+    for (int64_t t0 = (int64_t)blockIdx.x * kThreads; t0 < ni; t0 += (int64_t)Q.blocks * kThreads) {
         const int64_t t = t0 + threadIdx.x;
         int node = -1, l = 0, r = 0;
         int c8[8] = {-1, -1, -1, -1, -1, -1, -1, -1};
@@ -1423,12 +1687,16 @@ __global__ void __launch_bounds__(kThreads) k_leaf_moments(const int64_t* __rest
                                                            const double4* __restrict__ spos,
                                                            const int32_t* __restrict__ perm,
                                                            const double* __restrict__ v,
-                                                           float4* __restrict__ svf, NodeOut O) {
+                                                           float4* __restrict__ svf, NodeOut O, ListArgs Q) {
     constexpr int G = kLeafLanes;
+    if ((int)blockIdx.x < Q.blocks) {   // the first workgroups make the level lists instead
+        level_lists(Q, hdr);
+        return;
+    }
     const int64_t nl = hdr[0] - hdr[2];
     const int s = threadIdx.x & (G - 1);
-    const int64_t stride = ((int64_t)gridDim.x * blockDim.x) / G;
-    for (int64_t g = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / G; g < nl; g += stride) {
+    const int64_t stride = ((int64_t)(gridDim.x - Q.blocks) * blockDim.x) / G;
+    for (int64_t g = ((int64_t)(blockIdx.x - Q.blocks) * blockDim.x + threadIdx.x) / G; g < nl; g += stride) {
         const int id = leaves[g];
         const int p0 = leaf_pos[g], p1 = leaf_pos[g + 1];   // the leaves cover the positions in order
         MomentSums S;
@@ -1464,7 +1732,7 @@ __global__ void __launch_bounds__(kThreads) k_leaf_moments(const int64_t* __rest
 // deepest up, so every child is complete when its parent is formed), or
 // several in a single-workgroup launch, the workgroup barrier between levels
 // ordering each level after its children's.
-__global__ void __launch_bounds__(kThreads) k_inner_level(int l_hi, int l_lo, const int32_t* __restrict__ lvl,
+__global__ void __launch_bounds__(1024) k_inner_level(int l_hi, int l_lo, const int32_t* __restrict__ lvl,
                                                           const int32_t* __restrict__ lvl_list,
                                                           const int32_t* __restrict__ child, NodeOut O) {
     constexpr int G = kInnerLanes;
@@ -1490,17 +1758,23 @@ __global__ void k_fill_i32(int32_t* __restrict__ p, int64_t n, int32_t v) {
 // (c->seen_max_level; 20 if none) take one single-workgroup launch (they are
 // usually empty), the levels from there to 3 one launch each, and levels 2-0
 // (at most 73 nodes) one single-workgroup launch.  A deeper tree than
-// expected is still complete, only slower.
-int moments_pass(ag_ctx* c, const double* v) {
+// expected is still complete, only slower.  Up to kSmallMoments particles (a
+// few hundred inner nodes) one workgroup takes every level in one launch.
+constexpr int64_t kSmallMoments = 8192;
+int moments_pass(ag_ctx* c, const double* v, bool lists) {
     hipStream_t st = c->stream;
     NodeOut O{c->nd_com.as<double4>(), c->nd_lo.as<float4>(), c->nd_hi.as<float4>(), c->nd_mp.as<float4>(),
               c->nd_64.as<double>(), c->tree_soft ? c->soft_s.as<float>() : nullptr};
     const int64_t n = c->n;
-    hipLaunchKernelGGL(k_leaf_moments, dim3(grid_for(kLeafLanes * n)), dim3(kThreads), 0, st, c->tree_hdr.as<int64_t>(),
-                       c->leaf_list.as<int32_t>(), c->leaf_pos.as<int32_t>(), c->spos.as<double4>(),
-                       c->perm.as<int32_t>(), v, c->svf.as<float4>(), O);
-    // level-21 cells are always leaves; empty levels exit at once
     const int64_t inner_bound = c->max_nodes - n;
+    int64_t* hdr = c->tree_hdr.as<int64_t>();
+    ListArgs Q{0, c->in_list.as<int32_t>(), c->nd_link.as<int4>(), c->keys[0].as<uint64_t>(), c->child.as<int4>(),
+               reinterpret_cast<int32_t*>(hdr + 8), c->lvl_list.as<int32_t>(), c->nd_slot.as<int32_t>()};
+    if (lists) Q.blocks = std::min(grid_for(inner_bound), 1024);
+    hipLaunchKernelGGL(k_leaf_moments, dim3(Q.blocks + grid_for(kLeafLanes * n)), dim3(kThreads), 0, st, hdr,
+                       c->leaf_list.as<int32_t>(), c->leaf_pos.as<int32_t>(), c->spos.as<double4>(),
+                       c->perm.as<int32_t>(), v, c->svf.as<float4>(), O, Q);
+    // level-21 cells are always leaves; empty levels exit at once
     int g = grid_for(kInnerLanes * (inner_bound > 0 ? inner_bound : 1));
     if (g > 1024) g = 1024;
     const int32_t* lvl = reinterpret_cast<const int32_t*>(c->tree_hdr.as<int64_t>() + 8);
@@ -1510,6 +1784,10 @@ int moments_pass(ag_ctx* c, const double* v) {
     if (lc < kTop + 1) lc = kTop;
     const int32_t* ll = c->lvl_list.as<int32_t>();
     const int32_t* ch = c->child.as<int32_t>();
+    if (n <= kSmallMoments) {
+        hipLaunchKernelGGL(k_inner_level, dim3(1), dim3(1024), 0, st, AG_MAX_LEVEL - 1, 0, lvl, ll, ch, O);
+        return AG_OK;
+    }
     if (lc < AG_MAX_LEVEL - 1)
         hipLaunchKernelGGL(k_inner_level, dim3(1), dim3(kThreads), 0, st, AG_MAX_LEVEL - 1, lc + 1, lvl, ll, ch, O);
     for (int l = lc; l > kTop; --l)
@@ -1535,12 +1813,11 @@ int ag_launch_build(ag_ctx* c, int64_t n, const double* x, const double* v, cons
     AG_TRY(ag_ensure(c, c->keys[0], n * 8)); AG_TRY(ag_ensure(c, c->keys[1], n * 8));
     AG_TRY(ag_ensure(c, c->vals[0], n * 4)); AG_TRY(ag_ensure(c, c->vals[1], n * 4));
     const int nblocks = (int)((n + kRsTile - 1) / kRsTile);
-    // (also the bounding boxes' per-workgroup partials before the sort, and
-    // k_write_nodes' per-workgroup rows after it)
+    // (also k_write_nodes' per-workgroup rows after the sort)
     const int wblocks = std::min(grid_for(n), kWriteBlocks);
     AG_TRY(ag_ensure(c, c->sort_hist, std::max({(size_t)(256 * nblocks + 256 + 1) * 4,
-                                                (size_t)(n / kBoxChunk + n_sys + 1) * 6 * sizeof(uint64_t),
                                                 (size_t)wblocks * (kLevels + 1) * sizeof(int32_t)})));
+    AG_TRY(ag_ensure(c, c->box_part, (size_t)(n / kBoxChunk + n_sys + 1) * 6 * sizeof(uint64_t)));
     AG_TRY(ag_ensure(c, c->pos_off, (size_t)(256 * (int64_t)nblocks + 1 > n + 1 ? 256 * (int64_t)nblocks + 1 : n + 1) * 4));
     AG_TRY(ag_ensure(c, c->perm, n * 4)); AG_TRY(ag_ensure(c, c->rank, n * 4));
     AG_TRY(ag_ensure(c, c->spos, n * 32)); AG_TRY(ag_ensure(c, c->svf, n * 16));
@@ -1571,10 +1848,16 @@ int ag_launch_build(ag_ctx* c, int64_t n, const double* x, const double* v, cons
     AG_TRY(ag_ensure(c, c->leaf_pos, (n + 1) * 4));
     AG_TRY(ag_ensure(c, c->child, (size_t)(inner_bound > 0 ? inner_bound : 1) * 32));
     AG_TRY(ag_ensure(c, c->sys_box, 6 * n_sys * 8 + 8 * (n_sys + 1)));
+    // tiles of the node counts: enough workgroups for the device, few enough
+    // totals for each to add up
+    const int ctile = n <= ((int64_t)1 << 19) ? 512 : 2048;
+    const int64_t ntile = (n + ctile - 1) / ctile;
+    AG_TRY(ag_ensure(c, c->scan_tmp, (size_t)ntile * sizeof(int2)));
+    if (c->soft_n > 0) AG_TRY(ag_ensure(c, c->soft_s, (size_t)n * sizeof(float)));
 
-    if (c->depth_pending && !c->capturing && hipEventQuery(c->depth_ev) == hipSuccess) {
-        c->seen_max_level = (int)*c->depth_host;
-        c->depth_pending = false;
+    if (c->depth_host && !c->capturing) {
+        const int64_t d = __atomic_load_n(c->depth_host, __ATOMIC_RELAXED);
+        if (d >= 0) c->seen_max_level = (int)d;
     }
 
     PhaseScope phase(c, AG_PHASE_BUILD);
@@ -1594,76 +1877,91 @@ int ag_launch_build(ag_ctx* c, int64_t n, const double* x, const double* v, cons
             q += cd_cnt[k];
         }
     }
-    hipLaunchKernelGGL(k_build_init, dim3(1), dim3(512), 0, st, n_sys, n, sys_offsets, off, flags, box, blk_off, hdr,
-                       (int)(kTreeHdrBytes / 8));
-    const int64_t box_blocks = n / kBoxChunk + n_sys + 1;
-    uint64_t* box_part = reinterpret_cast<uint64_t*>(c->sort_hist.p);   // free until the sort
-    hipLaunchKernelGGL(k_box, dim3((unsigned)box_blocks), dim3(kBoxThreads), 0, st, x, off, n_sys, blk_off, box_part,
-                       flags, c->box);
-    hipLaunchKernelGGL(k_box_reduce, dim3((unsigned)n_sys), dim3(256), 0, st, n_sys, blk_off, box_part, box);
+    const bool one = sys_offsets == nullptr;
+    if (!one)
+        hipLaunchKernelGGL(k_build_init, dim3(1), dim3(512), 0, st, n_sys, n, sys_offsets, off, flags, box, blk_off,
+                           hdr, (int)(kTreeHdrBytes / 8));
+    const int64_t box_blocks = one ? (n + kBoxChunk - 1) / kBoxChunk : n / kBoxChunk + n_sys + 1;
+    uint64_t* box_part = c->box_part.as<uint64_t>();
+    hipLaunchKernelGGL(k_box, dim3((unsigned)box_blocks), dim3(kBoxThreads), 0, st, x, n, off, n_sys,
+                       one ? nullptr : blk_off, box_part, flags, c->box, hdr, (int)(kTreeHdrBytes / 8));
+    // one system's partial boxes are reduced by every workgroup of the keys
+    // themselves while there are few of them (98 KB at 2^22)
+    const bool reduce = !one || box_blocks > 2048;
+    if (reduce)
+        hipLaunchKernelGGL(k_box_reduce, dim3((unsigned)n_sys), dim3(256), 0, st, n_sys, one ? nullptr : blk_off,
+                           (int)box_blocks, box_part, box);
 
     // 2. keys
     uint64_t* k0 = c->keys[0].as<uint64_t>();
     uint64_t* k1 = c->keys[1].as<uint64_t>();
     int32_t* v0 = c->vals[0].as<int32_t>();
     int32_t* v1 = c->vals[1].as<int32_t>();
-    hipLaunchKernelGGL(k_keys, dim3(grid_for(n)), dim3(kThreads), 0, st, n, x, off, n_sys, bits, box, k0, v0, c->box);
-
-    // 3. sort: four passes over bits 31..62 (the last writes the permutation
-    //    and its inverse), then the level-10 cells holding more than n_leaf
-    //    particles by their full keys
     int32_t* hist = c->sort_hist.as<int32_t>();
     int32_t* tot = hist + (int64_t)256 * nblocks;
     int32_t* hoff = c->pos_off.as<int32_t>();
     int32_t* perm = c->perm.as<int32_t>();
     int32_t* rank = c->rank.as<int32_t>();
-    for (int pass = 0; pass < 4; ++pass) {
-        const int shift = kSortedShift + 8 * pass;
-        uint64_t* kin = (pass & 1) ? k1 : k0;
-        uint64_t* kout = (pass & 1) ? k0 : k1;
-        int32_t* vin = (pass & 1) ? v1 : v0;
-        int32_t* vout = pass == 3 ? perm : ((pass & 1) ? v0 : v1);
-        hipLaunchKernelGGL(k_rs_hist, dim3(nblocks), dim3(kThreads), 0, st, kin, n, shift, nblocks, hist);
-        hipLaunchKernelGGL(k_rs_rowscan, dim3(256), dim3(kThreads), 0, st, hist, nblocks, hoff, tot);
-        hipLaunchKernelGGL(k_rs_scatter, dim3(nblocks), dim3(kThreads), 0, st, kin, vin, n, shift, nblocks, hist,
-                           hoff, tot, kout, vout, pass == 3 ? rank : (int32_t*)nullptr);
+    if (one && n <= kSmallSort) {
+        hipLaunchKernelGGL(k_small_sort, dim3(1), dim3(kSmallThreads), 0, st, (int)n, x, box_part, (int)box_blocks,
+                           kSortedShift, k0, perm, rank, c->box);
+    } else {
+        hipLaunchKernelGGL(k_keys, dim3(std::min(grid_for(n), reduce ? 8192 : 1024)), dim3(kThreads), 0, st, n, x,
+                           off, n_sys, bits, reduce ? box : box_part, reduce ? 0 : (int)box_blocks, k0, v0, c->box);
+
+        // 3. sort: four passes over bits 31..62 (the last writes the permutation
+        //    and its inverse), then the level-10 cells holding more than n_leaf
+        //    particles by their full keys
+        const bool few = nblocks <= kRsFew;
+        for (int pass = 0; pass < 4; ++pass) {
+            const int shift = kSortedShift + 8 * pass;
+            uint64_t* kin = (pass & 1) ? k1 : k0;
+            uint64_t* kout = (pass & 1) ? k0 : k1;
+            int32_t* vin = (pass & 1) ? v1 : v0;
+            int32_t* vout = pass == 3 ? perm : ((pass & 1) ? v0 : v1);
+            hipLaunchKernelGGL(k_rs_hist, dim3(nblocks), dim3(kThreads), 0, st, kin, n, shift, nblocks, (int)few,
+                               hist);
+            if (!few)
+                hipLaunchKernelGGL(k_rs_rowscan, dim3(256), dim3(kThreads), 0, st, hist, nblocks, hoff, tot);
+            hipLaunchKernelGGL(k_rs_scatter, dim3(nblocks), dim3(kThreads), 0, st, kin, vin, n, shift, nblocks, hist,
+                               few ? (const int32_t*)nullptr : hoff, tot, kout, vout,
+                               pass == 3 ? rank : (int32_t*)nullptr);
+        }
     }
     {
         TopoParams PS{n, n_leaf, sys_levels};
-        int32_t* flag = c->pos_cnt.as<int32_t>();   // free until the topology
-        int32_t* soff = c->pos_off.as<int32_t>();
-        int32_t* list = c->cdig.as<int32_t>();
-        hipLaunchKernelGGL(k_seg_heads, dim3(grid_for(n)), dim3(kThreads), 0, st, n, k0, n_leaf, flag);
-        AG_TRY(ag_scan_i32(c, flag, soff, n));
-        hipLaunchKernelGGL(k_seg_list, dim3(grid_for(n)), dim3(kThreads), 0, st, n, flag, soff, list);
+        int32_t* list = c->cdig.as<int32_t>();   // free until the topology
+        int32_t* count = reinterpret_cast<int32_t*>(hdr + 4);   // zeroed with the header
+        hipLaunchKernelGGL(k_seg_heads, dim3(grid_for(n)), dim3(kThreads), 0, st, n, k0, n_leaf, list, count);
         const int64_t cells = n / (n_leaf + 1) + 1;   // dense cells are disjoint and hold > n_leaf each
         hipLaunchKernelGGL(k_seg_sort, dim3((unsigned)(cells < 2048 ? cells : 2048)), dim3(kThreads), 0, st, PS,
-                           list, soff + n, k0, perm, rank, k1, v1);
+                           list, count, k0, perm, rank, k1, v1);
     }
 
     // 4. particle data into key order
     c->tree_soft = c->soft_n > 0;
-    if (c->tree_soft) AG_TRY(ag_ensure(c, c->soft_s, (size_t)n * sizeof(float)));
-    launch_to_sorted(c, n, x, m, c->box);
     c->tree_box = c->box;
 
     // 5. topology
     int32_t* cd = c->cdig.as<int32_t>();
     {
-        int64_t cb = passes < 4096 ? passes : 4096;
-        hipLaunchKernelGGL(k_cdig, dim3((unsigned)cb), dim3(kRun), 0, st, n, k0, cd, M);
-        CdCounts C;
-        for (int k = 0; k < kCdLevels; ++k) C.cnt[k] = cd_cnt[k];
-        hipLaunchKernelGGL(k_cd_min_top, dim3(1), dim3(1024), 0, st, M, C);
+        const int cb = (int)(passes < 4096 ? passes : 4096);
+        const ToSorted Q{rank, x, m, c->spos.as<double4>(), c->box, c->tree_soft ? c->soft_h.as<double>() : nullptr,
+                         c->soft_s.as<float>()};
+        hipLaunchKernelGGL(k_cdig, dim3((unsigned)(cb + grid_for(n))), dim3(kRun), 0, st, n, k0, cd, M, cb, Q);
     }
+    CdCounts C;
+    for (int k = 0; k < kCdLevels; ++k) C.cnt[k] = cd_cnt[k];
     TopoParams P{n, n_leaf, sys_levels};
     int32_t* pcnt = c->pos_cnt.as<int32_t>();
     int32_t* poff = c->pos_off.as<int32_t>();
     int32_t* icnt = c->in_cnt.as<int32_t>();
     int32_t* ioff = c->in_off.as<int32_t>();
-    hipLaunchKernelGGL(k_count_nodes, dim3(grid_for(n)), dim3(kThreads), 0, st, P, cd, pcnt, icnt);
-    AG_TRY(ag_scan_i32(c, pcnt, poff, n));
-    AG_TRY(ag_scan_i32(c, icnt, ioff, n));
+    int2* tsum = c->scan_tmp.as<int2>();
+    hipLaunchKernelGGL(k_count_nodes, dim3((unsigned)(ntile + 1)), dim3(kThreads), 0, st, P, cd, ctile, pcnt, icnt,
+                       tsum, M, C);
+    hipLaunchKernelGGL(k_node_offsets, dim3((unsigned)ntile), dim3(kThreads), 0, st, n, ctile, pcnt, icnt, tsum, poff,
+                       ioff);
     // (the node counts are free after their scans: they hold the list of far
     // ends; the sort's histograms hold the per-workgroup rows)
     int32_t* blk_rows = c->sort_hist.as<int32_t>();
@@ -1671,20 +1969,10 @@ int ag_launch_build(ag_ctx* c, int64_t n, const double* x, const double* v, cons
                        c->nd_link.as<int4>(), c->in_list.as<int32_t>(), c->leaf_list.as<int32_t>(),
                        c->leaf_pos.as<int32_t>(), hdr, blk_rows,
                        pcnt, icnt);
-    hipLaunchKernelGGL(k_far_ends, dim3(grid_for(n / 16 + 1)), dim3(kThreads), 0, st, P, cd, M, poff, pcnt, icnt,
-                       hdr, c->nd_link.as<int4>());
-    hipLaunchKernelGGL(k_tree_close, dim3(1), dim3(1024), 0, st, wblocks, blk_rows, hdr, c->leaf_pos.as<int32_t>(),
-                       n, n_sys, sys_levels, off, cd,
-                       poff, c->sys_root.as<int32_t>());
-    if (!c->capturing && c->depth_host) {   // this tree's depth, for the next build's launch plan
-        (void)hipMemcpyAsync(c->depth_host, hdr + 1, sizeof(int64_t), hipMemcpyDeviceToHost, st);
-        (void)hipEventRecord(c->depth_ev, st);
-        c->depth_pending = true;
-    }
-    hipLaunchKernelGGL(k_level_lists, dim3(grid_for(inner_bound) < 1024 ? grid_for(inner_bound) : 1024),
-                       dim3(kThreads), 0, st, hdr, c->in_list.as<int32_t>(), c->nd_link.as<int4>(), k0,
-                       c->child.as<int4>(), reinterpret_cast<int32_t*>(hdr + 8), c->lvl_list.as<int32_t>(),
-                       c->nd_slot.as<int32_t>());
+    const CloseArgs Q{wblocks, blk_rows, c->leaf_pos.as<int32_t>(), n_sys, off, c->sys_root.as<int32_t>(),
+                      c->depth_host};
+    hipLaunchKernelGGL(k_far_ends, dim3(1 + grid_for(n / 16 + 1)), dim3(kThreads), 0, st, P, cd, M, poff, pcnt, icnt,
+                       hdr, c->nd_link.as<int4>(), Q);
 
     c->n = n;
     c->n_leaf = n_leaf;
@@ -1692,13 +1980,13 @@ int ag_launch_build(ag_ctx* c, int64_t n, const double* x, const double* v, cons
     c->sys_levels = sys_levels;
     c->max_nodes = max_nodes;
 
-    // 6. moments
-    return moments_pass(c, v);
+    // 6. level lists and moments
+    return moments_pass(c, v, true);
 }
 
 int ag_launch_refit(ag_ctx* c, const double* x, const double* v, const double* m) {
     const int64_t n = c->n;
     PhaseScope phase(c, AG_PHASE_BUILD);
     launch_to_sorted(c, n, x, m, c->tree_box);
-    return moments_pass(c, v);
+    return moments_pass(c, v, false);
 }

@@ -1622,17 +1622,14 @@ __global__ void k_ewald_table(double L, int ne, double h, float4* __restrict__ t
 // active targets (coincident points at the deepest level) is cut in chunks
 // of 64.  Cells of the system-prefix levels are never packed together, so a
 // group never mixes systems.
-__global__ void k_fill0(int32_t* __restrict__ p, int64_t n) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = 0;
-}
-
-// Active rows -> flags over sorted positions, without atomics: every listed
-// entry k stamps k + 1 at its position, then each entry checks that its own
-// stamp survived (a repeated row loses to one of its copies) and sets the flag.
-// The list's length is n_act, or, with n_dev set, the count stored at *n_dev
-// (at most n_act = n; a count outside [0, n] raises the flag and lists none).
+// Active rows -> sorted positions, without atomics: every listed entry k stamps
+// k + 1 at its row's position; a position is active if the entry its stamp
+// names still names its row (stamps of earlier lists fail that unless a
+// current entry names the row, and then the stamp is that entry's).  A list
+// whose entries are in range and unique marks as many positions as it has
+// entries; otherwise the flag is raised.  The list's length is n_act, or, with
+// n_dev set, the count stored at *n_dev (at most n_act = n; a count outside
+// [0, n] raises the flag and lists none).
 __device__ __forceinline__ int64_t list_len(int64_t n_act, const int64_t* __restrict__ n_dev) {
     if (!n_dev) return n_act;
     const int64_t v = *n_dev;
@@ -1651,34 +1648,54 @@ __global__ void k_mark_stamp(int64_t n_act, const int64_t* __restrict__ n_dev, c
     for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n_act;
          k += (int64_t)gridDim.x * blockDim.x) {
         const int64_t i = idx[k];
-        if (i < 0 || i >= n) {
-            atomicOr(flags, AGF_BADINDEX);
-            continue;
-        }
-        stamp[rank[i]] = (int32_t)(k + 1);
+        if (i >= 0 && i < n) stamp[rank[i]] = (int32_t)(k + 1);
     }
 }
 
-__global__ void k_mark_check(int64_t n_act, const int64_t* __restrict__ n_dev, const int32_t* __restrict__ idx,
-                             int64_t n, const int32_t* __restrict__ rank, const int32_t* __restrict__ stamp,
-                             int32_t* __restrict__ flag, int32_t* __restrict__ flags) {
+constexpr int kMarkTile = 2048;   // positions a workgroup takes
+__global__ void __launch_bounds__(256) k_mark_flag(int64_t n_act, const int64_t* __restrict__ n_dev,
+                                                   const int32_t* __restrict__ idx, int64_t n,
+                                                   const int32_t* __restrict__ perm,
+                                                   const int32_t* __restrict__ stamp, int32_t* __restrict__ flag,
+                                                   int32_t* __restrict__ tile_sum) {
+    __shared__ int s_sum[4];
     n_act = list_len(n_act, n_dev);
-    for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n_act;
-         k += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t i = idx[k];
-        if (i < 0 || i >= n) continue;
-        const int p = rank[i];
-        if (stamp[p] == (int32_t)(k + 1)) flag[p] = 1;
-        else atomicOr(flags, AGF_BADINDEX);
+    int sum = 0;
+#pragma unroll
+    for (int r = 0; r < kMarkTile / 256; ++r) {
+        const int64_t p = (int64_t)blockIdx.x * kMarkTile + r * 256 + threadIdx.x;
+        if (p >= n) continue;
+        const int64_t k = (int64_t)stamp[p] - 1;
+        const int f = k >= 0 && k < n_act && idx[k] == perm[p];
+        flag[p] = f;
+        sum += f;
     }
+    sum = ag_wave_sum(sum);
+    if (ag_lane() == 0) s_sum[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) tile_sum[blockIdx.x] = s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
 }
 
-
-__global__ void k_compact_pos(int64_t n, const int32_t* __restrict__ flag, const int32_t* __restrict__ off,
-                              int32_t* __restrict__ out) {
-    for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < n;
-         p += (int64_t)gridDim.x * blockDim.x)
-        if (flag[p]) out[off[p]] = (int32_t)p;
+// offsets of the active positions (n + 1 of them) and their list
+__global__ void __launch_bounds__(256) k_mark_list(int64_t n_act, const int64_t* __restrict__ n_dev, int64_t n,
+                                                   const int32_t* __restrict__ flag,
+                                                   const int32_t* __restrict__ tile_sum, int32_t* __restrict__ off,
+                                                   int32_t* __restrict__ out, int32_t* __restrict__ flags) {
+    __shared__ int s_tmp[4];
+    int run = ag_tiles_before256(tile_sum, (int)blockIdx.x, s_tmp);
+    for (int r = 0; r < kMarkTile / 256; ++r) {
+        const int64_t p = (int64_t)blockIdx.x * kMarkTile + r * 256 + threadIdx.x;
+        const int f = p < n ? flag[p] : 0;
+        int tot;
+        const int e = run + ag_block_scan256(f, s_tmp, &tot);
+        if (p < n) off[p] = e;
+        if (f) out[e] = (int32_t)p;
+        run += tot;
+    }
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+        off[n] = run;
+        if (run != list_len(n_act, n_dev)) atomicOr(flags, AGF_BADINDEX);
+    }
 }
 
 struct GroupCtx {
@@ -1778,24 +1795,46 @@ __device__ int node_groups(const GroupCtx& C, int id, int4* __restrict__ out) {
     return ng;
 }
 
-// counts for every slot up to the node bound (zero past the last node)
-__global__ void k_group_count(GroupCtx C, const int64_t* __restrict__ hdr, int64_t max_nodes,
-                              int32_t* __restrict__ gcnt) {
+// Groups each node owns, and the total of every tile of nodes.
+constexpr int kGroupTile = 1024;   // nodes a workgroup takes
+__global__ void __launch_bounds__(256) k_group_count(GroupCtx C, const int64_t* __restrict__ hdr,
+                                                     int32_t* __restrict__ gcnt, int32_t* __restrict__ tile_sum) {
+    __shared__ int s_sum[4];
     const int64_t nn = hdr[0];
-    for (int64_t id = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; id < max_nodes;
-         id += (int64_t)gridDim.x * blockDim.x)
-        gcnt[id] = id < nn ? node_groups(C, (int)id, nullptr) : 0;
+    if ((int64_t)blockIdx.x * kGroupTile >= nn) return;
+    int sum = 0;
+    for (int r = 0; r < kGroupTile / 256; ++r) {
+        const int64_t id = (int64_t)blockIdx.x * kGroupTile + r * 256 + threadIdx.x;
+        if (id >= nn) continue;
+        const int g = node_groups(C, (int)id, nullptr);
+        gcnt[id] = g;
+        sum += g;
+    }
+    sum = ag_wave_sum(sum);
+    if (ag_lane() == 0) s_sum[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) tile_sum[blockIdx.x] = s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
 }
 
-__global__ void k_group_emit(GroupCtx C, const int64_t* __restrict__ hdr, const int32_t* __restrict__ goff,
-                             int4* __restrict__ grp, int32_t* __restrict__ ghdr, int* __restrict__ qctr) {
+// The groups in node order, their number, and the walks' work queues reset.
+__global__ void __launch_bounds__(256) k_group_emit(GroupCtx C, const int64_t* __restrict__ hdr,
+                                                    const int32_t* __restrict__ gcnt,
+                                                    const int32_t* __restrict__ tile_sum, int4* __restrict__ grp,
+                                                    int32_t* __restrict__ ghdr, int* __restrict__ qctr) {
+    __shared__ int s_tmp[4];
     const int64_t nn = hdr[0];
-    for (int64_t id = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; id < nn;
-         id += (int64_t)gridDim.x * blockDim.x) {
-        if (goff[id + 1] > goff[id]) node_groups(C, (int)id, grp + goff[id]);
-    }
     if (blockIdx.x == 0 && threadIdx.x < 2 * 8) qctr[threadIdx.x * kQueueStride] = 0;   // two walks' queues
-    if (blockIdx.x == 0 && threadIdx.x == 0) ghdr[0] = goff[nn];
+    if ((int64_t)blockIdx.x * kGroupTile >= nn) return;
+    int run = ag_tiles_before256(tile_sum, (int)blockIdx.x, s_tmp);
+    for (int r = 0; r < kGroupTile / 256; ++r) {
+        const int64_t id = (int64_t)blockIdx.x * kGroupTile + r * 256 + threadIdx.x;
+        const int g = id < nn ? gcnt[id] : 0;
+        int tot;
+        const int e = run + ag_block_scan256(g, s_tmp, &tot);
+        if (g > 0) node_groups(C, (int)id, grp + e);
+        run += tot;
+    }
+    if ((int64_t)(blockIdx.x + 1) * kGroupTile >= nn && threadIdx.x == 0) ghdr[0] = run;
 }
 
 int grid_for(int64_t n, int threads = 256) {
@@ -1810,28 +1849,31 @@ int ag_prepare_groups(ag_ctx* c, const int32_t* idx, int64_t n_act, int64_t* max
                       int64_t* n_total) {
     const int64_t n = c->n;
     const int64_t mg = n_act + c->n_sys + 1;   // every group holds at least one target
+    const int64_t mtiles = (n + kMarkTile - 1) / kMarkTile, gtiles = (c->max_nodes + kGroupTile - 1) / kGroupTile;
+    AG_TRY(ag_ensure(c, c->act_stamp, n * 4));
     AG_TRY(ag_ensure(c, c->act_flag, n * 4));
     AG_TRY(ag_ensure(c, c->act_off, (n + 1) * 4));
     AG_TRY(ag_ensure(c, c->act_pos, n * 4));
     AG_TRY(ag_ensure(c, c->grp, mg * 16));
     AG_TRY(ag_ensure(c, c->grp_hdr, (1 + 2 * 8) * kQueueStride * sizeof(int32_t)));
-    AG_TRY(ag_ensure(c, c->grp_cnt, (c->max_nodes + 1) * 4));
-    AG_TRY(ag_ensure(c, c->grp_off, (c->max_nodes + 1) * 4));
+    AG_TRY(ag_ensure(c, c->grp_cnt, c->max_nodes * 4));
+    AG_TRY(ag_ensure(c, c->grp_tile, gtiles * 4));
+    AG_TRY(ag_ensure(c, c->scan_tmp, mtiles * 4));
     PhaseScope phase(c, AG_PHASE_GROUPS);
     hipStream_t st = c->stream;
-    int32_t* flag = c->act_flag.as<int32_t>();
     int32_t* off = c->act_off.as<int32_t>();
     c->all_active = idx == nullptr;
     if (idx) {
-        hipLaunchKernelGGL(k_fill0, dim3(grid_for(n)), dim3(256), 0, st, flag, n);
-        // the scan output doubles as the stamp array until the scan runs
+        int32_t* flag = c->act_flag.as<int32_t>();
+        int32_t* stamp = c->act_stamp.as<int32_t>();
+        int32_t* msum = c->scan_tmp.as<int32_t>();
+        int32_t* flags = c->dflags.as<int32_t>();
         hipLaunchKernelGGL(k_mark_stamp, dim3(grid_for(n_act)), dim3(256), 0, st, n_act, n_dev, idx, n,
-                           c->rank.as<int32_t>(), off, c->dflags.as<int32_t>(), n_total);
-        hipLaunchKernelGGL(k_mark_check, dim3(grid_for(n_act)), dim3(256), 0, st, n_act, n_dev, idx, n,
-                           c->rank.as<int32_t>(), off, flag, c->dflags.as<int32_t>());
-        AG_TRY(ag_scan_i32(c, flag, off, n));
-        hipLaunchKernelGGL(k_compact_pos, dim3(grid_for(n)), dim3(256), 0, st, n, flag, off,
-                           c->act_pos.as<int32_t>());
+                           c->rank.as<int32_t>(), stamp, flags, n_total);
+        hipLaunchKernelGGL(k_mark_flag, dim3((unsigned)mtiles), dim3(256), 0, st, n_act, n_dev, idx, n,
+                           c->perm.as<int32_t>(), stamp, flag, msum);
+        hipLaunchKernelGGL(k_mark_list, dim3((unsigned)mtiles), dim3(256), 0, st, n_act, n_dev, n, flag, msum, off,
+                           c->act_pos.as<int32_t>(), flags);
     }
     // with every particle active the flags, their scan and the position list
     // are the identity: the grouping and the walk use sorted positions directly
@@ -1839,11 +1881,10 @@ int ag_prepare_groups(ag_ctx* c, const int32_t* idx, int64_t n_act, int64_t* max
                c->sys_levels, c->group_span, c->group_cap, c->group_split, c->group_pack};
     const int64_t* hdr = c->tree_hdr.as<int64_t>();
     int32_t* gcnt = c->grp_cnt.as<int32_t>();
-    int32_t* goff = c->grp_off.as<int32_t>();
-    hipLaunchKernelGGL(k_group_count, dim3(grid_for(c->max_nodes)), dim3(256), 0, st, C, hdr, c->max_nodes, gcnt);
-    AG_TRY(ag_scan_i32(c, gcnt, goff, c->max_nodes));
+    int32_t* gsum = c->grp_tile.as<int32_t>();
     int32_t* ghdr = c->grp_hdr.as<int32_t>();
-    hipLaunchKernelGGL(k_group_emit, dim3(grid_for(c->max_nodes)), dim3(256), 0, st, C, hdr, goff,
+    hipLaunchKernelGGL(k_group_count, dim3((unsigned)gtiles), dim3(256), 0, st, C, hdr, gcnt, gsum);
+    hipLaunchKernelGGL(k_group_emit, dim3((unsigned)gtiles), dim3(256), 0, st, C, hdr, gcnt, gsum,
                        c->grp.as<int4>(), ghdr, ghdr + kQueueStride);
     *max_groups = mg;
     return AG_OK;
