@@ -1700,6 +1700,8 @@ __global__ void __launch_bounds__(256) k_mark_list(int64_t n_act, const int64_t*
 
 struct GroupCtx {
     const int4* __restrict__ link;
+    const int32_t* __restrict__ slot;   // row of an inner node's children ...
+    const int4* __restrict__ child;     // ... by octant (-1: none), two int4 a row
     const int32_t* __restrict__ aoff;   // exclusive scan of the active flags over sorted positions (null: all)
     const int64_t* __restrict__ sys_off;
     int n_sys;
@@ -1766,10 +1768,25 @@ __device__ int node_groups(const GroupCtx& C, int id, int4* __restrict__ out) {
         }
         for (int k = 0; k < cnt; k += C.cap) emit(start + k, cnt - k < C.cap ? cnt - k : C.cap, pos);
     };
-    for (int ch = id + 1, k8 = 0; ch < L.x && k8 < 8; ch = C.link[ch].x, ++k8) {
-        const int4 Lc = C.link[ch];
-        const int c0 = C.aoff ? C.aoff[Lc.y] : Lc.y;
-        const int ac = (C.aoff ? C.aoff[Lc.y + Lc.z] : Lc.y + Lc.z) - c0;
+    // the children (in order) all at once from the node's row: following their
+    // skip links would take a chain of up to eight loads
+    const int64_t row = C.slot[id];
+    const int4 ra = C.child[2 * row], rb = C.child[2 * row + 1];
+    const int ch8[8] = {ra.x, ra.y, ra.z, ra.w, rb.x, rb.y, rb.z, rb.w};
+    int4 link8[8];
+    int act0[8], act1[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) link8[k] = ch8[k] >= 0 ? C.link[ch8[k]] : make_int4(0, 0, 0, 0);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        act0[k] = C.aoff && ch8[k] >= 0 ? C.aoff[link8[k].y] : link8[k].y;
+        act1[k] = C.aoff && ch8[k] >= 0 ? C.aoff[link8[k].y + link8[k].z] : link8[k].y + link8[k].z;
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        if (ch8[k] < 0) continue;
+        const int4 Lc = link8[k];
+        const int c0 = act0[k], ac = act1[k] - c0;
         const bool leafc = (Lc.w & 0x100) != 0;
         const bool bigc = (Lc.w & 0xff) < C.sys_levels || ac > C.cap || (C.span > 0 && !leafc && Lc.z > C.span);
         if (bigc || ac == 0 || forced) {
@@ -1796,24 +1813,24 @@ __device__ int node_groups(const GroupCtx& C, int id, int4* __restrict__ out) {
 }
 
 // Groups each node owns, and the total of every tile of nodes.
-constexpr int kGroupTile = 1024;   // nodes a workgroup takes
+// One node a thread: the work is a chain of dependent loads, so more nodes a
+// thread only lengthen it (four: 25 + 16 us for the two kernels at 2^15
+// particles, now 7 + 7; 22 + 25 at 2^20, now 8 + 10).
+constexpr int kGroupTile = 256;   // nodes a workgroup takes at a time
 __global__ void __launch_bounds__(256) k_group_count(GroupCtx C, const int64_t* __restrict__ hdr,
                                                      int32_t* __restrict__ gcnt, int32_t* __restrict__ tile_sum) {
     __shared__ int s_sum[4];
     const int64_t nn = hdr[0];
-    if ((int64_t)blockIdx.x * kGroupTile >= nn) return;
-    int sum = 0;
-    for (int r = 0; r < kGroupTile / 256; ++r) {
-        const int64_t id = (int64_t)blockIdx.x * kGroupTile + r * 256 + threadIdx.x;
-        if (id >= nn) continue;
-        const int g = node_groups(C, (int)id, nullptr);
-        gcnt[id] = g;
-        sum += g;
+    for (int64_t t = blockIdx.x; t * kGroupTile < nn; t += gridDim.x) {
+        const int64_t id = t * kGroupTile + threadIdx.x;
+        const int g = id < nn ? node_groups(C, (int)id, nullptr) : 0;
+        if (id < nn) gcnt[id] = g;
+        const int sum = ag_wave_sum(g);
+        __syncthreads();
+        if (ag_lane() == 0) s_sum[threadIdx.x >> 6] = sum;
+        __syncthreads();
+        if (threadIdx.x == 0) tile_sum[t] = s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
     }
-    sum = ag_wave_sum(sum);
-    if (ag_lane() == 0) s_sum[threadIdx.x >> 6] = sum;
-    __syncthreads();
-    if (threadIdx.x == 0) tile_sum[blockIdx.x] = s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
 }
 
 // The groups in node order, their number, and the walks' work queues reset.
@@ -1824,17 +1841,15 @@ __global__ void __launch_bounds__(256) k_group_emit(GroupCtx C, const int64_t* _
     __shared__ int s_tmp[4];
     const int64_t nn = hdr[0];
     if (blockIdx.x == 0 && threadIdx.x < 2 * 8) qctr[threadIdx.x * kQueueStride] = 0;   // two walks' queues
-    if ((int64_t)blockIdx.x * kGroupTile >= nn) return;
-    int run = ag_tiles_before256(tile_sum, (int)blockIdx.x, s_tmp);
-    for (int r = 0; r < kGroupTile / 256; ++r) {
-        const int64_t id = (int64_t)blockIdx.x * kGroupTile + r * 256 + threadIdx.x;
+    for (int64_t t = blockIdx.x; t * kGroupTile < nn; t += gridDim.x) {
+        const int64_t id = t * kGroupTile + threadIdx.x;
+        const int before = ag_tiles_before256(tile_sum, (int)t, s_tmp);
         const int g = id < nn ? gcnt[id] : 0;
         int tot;
-        const int e = run + ag_block_scan256(g, s_tmp, &tot);
+        const int e = before + ag_block_scan256(g, s_tmp, &tot);
         if (g > 0) node_groups(C, (int)id, grp + e);
-        run += tot;
+        if ((t + 1) * kGroupTile >= nn && threadIdx.x == 0) ghdr[0] = before + tot;
     }
-    if ((int64_t)(blockIdx.x + 1) * kGroupTile >= nn && threadIdx.x == 0) ghdr[0] = run;
 }
 
 int grid_for(int64_t n, int threads = 256) {
@@ -1877,14 +1892,15 @@ int ag_prepare_groups(ag_ctx* c, const int32_t* idx, int64_t n_act, int64_t* max
     }
     // with every particle active the flags, their scan and the position list
     // are the identity: the grouping and the walk use sorted positions directly
-    GroupCtx C{c->nd_link.as<int4>(), idx ? off : (const int32_t*)nullptr, c->sys_off.as<int64_t>(), c->n_sys,
+    GroupCtx C{c->nd_link.as<int4>(), c->nd_slot.as<int32_t>(), c->child.as<int4>(), idx ? off : (const int32_t*)nullptr, c->sys_off.as<int64_t>(), c->n_sys,
                c->sys_levels, c->group_span, c->group_cap, c->group_split, c->group_pack};
     const int64_t* hdr = c->tree_hdr.as<int64_t>();
     int32_t* gcnt = c->grp_cnt.as<int32_t>();
     int32_t* gsum = c->grp_tile.as<int32_t>();
     int32_t* ghdr = c->grp_hdr.as<int32_t>();
-    hipLaunchKernelGGL(k_group_count, dim3((unsigned)gtiles), dim3(256), 0, st, C, hdr, gcnt, gsum);
-    hipLaunchKernelGGL(k_group_emit, dim3((unsigned)gtiles), dim3(256), 0, st, C, hdr, gcnt, gsum,
+    const unsigned gblocks = (unsigned)std::min<int64_t>(gtiles, 4096);
+    hipLaunchKernelGGL(k_group_count, dim3(gblocks), dim3(256), 0, st, C, hdr, gcnt, gsum);
+    hipLaunchKernelGGL(k_group_emit, dim3(gblocks), dim3(256), 0, st, C, hdr, gcnt, gsum,
                        c->grp.as<int4>(), ghdr, ghdr + kQueueStride);
     *max_groups = mg;
     return AG_OK;
