@@ -34,8 +34,7 @@ struct NearArgs {
     const int4* __restrict__ link;
     const int32_t* __restrict__ slot;    // row of an inner node's children ...
     const int4* __restrict__ child;      // ... by octant, -1 where there is none (two int4 a row)
-    const float4* __restrict__ lo;
-    const float4* __restrict__ hi;
+    const NodeRec* __restrict__ rec;
     const double4* __restrict__ spos;
     const int32_t* __restrict__ perm;
     const int32_t* __restrict__ sys_root;
@@ -290,7 +289,7 @@ __device__ __forceinline__ void each_near(NearLds& S, const NearArgs& A, const N
         if (lane < m) {
             const int a = S.stack[sp + lane];
             L = A.link[a];
-            const float4 lo = A.lo[a], hi = A.hi[a];
+            const float4 lo = A.rec[a].lo, hi = A.rec[a].hi;
             const int row = A.slot[a];
             double r2 = R2;
             if (kNodeH) {
@@ -769,7 +768,7 @@ __global__ void __launch_bounds__(kW, 4) k_near(NearArgs A, int run, int cuts) {
             sum_pairs<kMode>(S, A, t, gb, root);
         } else {
             // no two particles are farther apart (a margin for the rounding; not 0)
-            const float4 lo = A.lo[root], hi = A.hi[root];
+            const float4 lo = A.rec[root].lo, hi = A.rec[root].hi;
             const double ex = (double)hi.x - lo.x, ey = (double)hi.y - lo.y, ez = (double)hi.z - lo.z;
             const double diag = fmax(1.001 * sqrt(ex * ex + ey * ey + ez * ez), DBL_MIN);
             // (every particle is a target: positions are slots)
@@ -786,8 +785,7 @@ NearArgs near_args(ag_ctx* c) {
     A.link = c->nd_link.as<int4>();
     A.slot = c->nd_slot.as<int32_t>();
     A.child = c->child.as<int4>();
-    A.lo = c->nd_lo.as<float4>();
-    A.hi = c->nd_hi.as<float4>();
+    A.rec = c->nd_rec.as<NodeRec>();
     A.spos = c->spos.as<double4>();
     A.perm = c->perm.as<int32_t>();
     A.sys_root = c->sys_root.as<int32_t>();

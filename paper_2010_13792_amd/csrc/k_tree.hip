@@ -1365,9 +1365,7 @@ __global__ void __launch_bounds__(kThreads) k_far_ends(TopoParams P, const int32
 constexpr int kM64 = 25;
 
 struct NodeOut {
-    double4* com;
-    float4* lo4;
-    float4* hi4;
+    NodeRec* rec;
     float4* mp;
     double* m64;
     const float* sh;   // sorted softening lengths, or null
@@ -1385,10 +1383,9 @@ __device__ __forceinline__ uint4 u4_f4(float a, float b, float c, float d) {
 // Writes node id's record from a group of G lanes (aligned to G, all
 // active) that all hold it (lane s = 0..G-1), so that each store instruction
 // writes whole runs: the 25 FP64 moments as runs of G doubles, and the FP32
-// copies as 16-byte words, word s of every G (centre of mass and extent in
-// two, box low, box high, the four packed multipole words).  lo4.w holds the
-// largest softening length in the node (0 without per-particle softening),
-// hi4.w the mass.
+// copies as 16-byte words, word s of every G (the opening test's record in
+// four, the four packed multipole words).  lo.w holds the largest softening
+// length in the node (0 without per-particle softening), hi.w the mass.
 template <int G>
 __device__ __forceinline__ void store_node_g(int64_t id, int s, const double* r, const NodeOut& O, float hmax) {
     // the lane's words are picked by masks, not by indexing or selects on
@@ -1411,10 +1408,17 @@ __device__ __forceinline__ void store_node_g(int64_t id, int s, const double* r,
         const double e = r[22 + c] - r[19 + c];
         L = e > L ? e : L;
     }
+    const float4 lo = make_float4(f_down(r[19]), f_down(r[20]), f_down(r[21]), hmax);
+    const float4 hi = make_float4(f_up(r[22]), f_up(r[23]), f_up(r[24]), (float)r[0]);
+    const float ox = (float)r[1] - 0.5f * (lo.x + hi.x);
+    const float oy = (float)r[2] - 0.5f * (lo.y + hi.y);
+    const float oz = (float)r[3] - 0.5f * (lo.z + hi.z);
+    const float len = (float)L, mac = len + sqrtf(ox * ox + oy * oy + oz * oz);
+    const unsigned long long zbits = (unsigned long long)__double_as_longlong(r[3]);
     const uint4 w[8] = {u4_d2(r[1], r[2]),
-                        u4_d2(r[3], L),
-                        u4_f4(f_down(r[19]), f_down(r[20]), f_down(r[21]), hmax),
-                        u4_f4(f_up(r[22]), f_up(r[23]), f_up(r[24]), (float)r[0]),
+                        make_uint4((unsigned)zbits, (unsigned)(zbits >> 32), __float_as_uint(len), __float_as_uint(mac)),
+                        u4_f4(lo.x, lo.y, lo.z, lo.w),
+                        u4_f4(hi.x, hi.y, hi.z, hi.w),
                         u4_f4((float)r[0], (float)r[4], (float)r[5], (float)r[6]),
                         u4_f4((float)r[7], (float)r[8], (float)r[9], (float)r[10]),
                         u4_f4((float)r[11], (float)r[12], (float)r[13], (float)r[14]),
@@ -1431,10 +1435,8 @@ __device__ __forceinline__ void store_node_g(int64_t id, int s, const double* r,
             val.w |= w[b + k].w & m;
         }
         const int wi = b + s;
-        uint4* dst = wi < 2 ? reinterpret_cast<uint4*>(O.com + id) + wi
-                   : wi == 2 ? reinterpret_cast<uint4*>(O.lo4 + id)
-                   : wi == 3 ? reinterpret_cast<uint4*>(O.hi4 + id)
-                             : reinterpret_cast<uint4*>(O.mp + 4 * id) + (wi - 4);
+        uint4* dst = wi < 4 ? reinterpret_cast<uint4*>(O.rec + id) + wi
+                            : reinterpret_cast<uint4*>(O.mp + 4 * id) + (wi - 4);
         *dst = val;
     }
 }
@@ -1681,7 +1683,7 @@ __device__ void form_inner(int in, int id, int s, const int32_t* __restrict__ ch
                 S.Qd[k] += cm[13 + k];
             }
             S.box(cm + 19, cm + 22);
-            hm = fmaxf(hm, O.lo4[ch].w);
+            hm = fmaxf(hm, O.rec[ch].lo.w);
         }
     }
     grp_reduce<G>(S);
@@ -1786,7 +1788,7 @@ __global__ void k_fill_i32(int32_t* __restrict__ p, int64_t n, int32_t v) {
 constexpr int64_t kSmallMoments = 8192;
 int moments_pass(ag_ctx* c, const double* v, bool lists) {
     hipStream_t st = c->stream;
-    NodeOut O{c->nd_com.as<double4>(), c->nd_lo.as<float4>(), c->nd_hi.as<float4>(), c->nd_mp.as<float4>(),
+    NodeOut O{c->nd_rec.as<NodeRec>(), c->nd_mp.as<float4>(),
               c->nd_64.as<double>(), c->tree_soft ? c->soft_s.as<float>() : nullptr};
     const int64_t n = c->n;
     const int64_t inner_bound = c->max_nodes - n;
@@ -1859,8 +1861,7 @@ int ag_launch_build(ag_ctx* c, int64_t n, const double* x, const double* v, cons
     }
     for (int k = 0; k < kCdLevels; ++k) cd_tot += cd_cnt[k];
     AG_TRY(ag_ensure(c, c->cd_min, (size_t)cd_tot * sizeof(int32_t)));
-    AG_TRY(ag_ensure(c, c->nd_com, max_nodes * 32)); AG_TRY(ag_ensure(c, c->nd_lo, max_nodes * 16));
-    AG_TRY(ag_ensure(c, c->nd_hi, max_nodes * 16)); AG_TRY(ag_ensure(c, c->nd_link, max_nodes * 16));
+    AG_TRY(ag_ensure(c, c->nd_rec, max_nodes * sizeof(NodeRec))); AG_TRY(ag_ensure(c, c->nd_link, max_nodes * 16));
     AG_TRY(ag_ensure(c, c->nd_slot, max_nodes * 4));
     AG_TRY(ag_ensure(c, c->nd_mp, max_nodes * 64)); AG_TRY(ag_ensure(c, c->nd_64, max_nodes * kM64 * 8));
     AG_TRY(ag_ensure(c, c->in_list, max_nodes * 4)); AG_TRY(ag_ensure(c, c->in_cnt, (n + 1) * 4));

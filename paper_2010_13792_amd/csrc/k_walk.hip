@@ -33,6 +33,7 @@ namespace {
 
 constexpr int kW = 64;          // lanes per wave = targets per group = tile size
 constexpr int kPCap = 256;      // pending particle indices
+constexpr int kListSlack = 64;  // room behind them for what list_run writes past the end
 constexpr int kNCap = 128;      // pending accepted nodes
 constexpr int kSCap = 128;      // stacked cursor ranges
 constexpr int kMaxSub = 32;     // most lanes given to one target of a small group
@@ -57,9 +58,7 @@ constexpr int AG_WALK_PP_FLOPS = 57;
 constexpr int AG_PN_FLOPS = 179;
 
 struct Tree {
-    const double4* __restrict__ com;   // centre of mass, extent
-    const float4* __restrict__ lo;
-    const float4* __restrict__ hi;
+    const NodeRec* __restrict__ rec;
     const int4* __restrict__ link;     // skip, start, count, level | leaf
     const float4* __restrict__ mp;     // 4 per node
     const double4* __restrict__ spos;  // sorted x, y, z, m
@@ -84,7 +83,7 @@ struct WalkOut {
     unsigned long long* stats;
     double G;
     int32_t* flags;
-    int64_t iter_cap;   // > nodes + particles: every group finishes well within it
+    unsigned iter_cap;  // > nodes + particles: every group finishes well within it
     int small_node;     // accepted nodes this small are summed pairwise
     bool mac_offset;    // opening test adds the centre-of-mass offset to the extent
     const float* rel_a; // relative opening test: |a| of the last evaluation per row (null: off)
@@ -113,14 +112,16 @@ struct GroupBox {
     float amin;                 // relative opening test: smallest |a| of the group's targets
 };
 
+// d rounded to float towards minus or plus infinity (kept within the finite
+// floats): the nearest float, or where that lies on the wrong side its
+// neighbour, by counting the bits.
 __device__ __forceinline__ float f_dn(double d) {
-    float f = (float)d;
-    return (double)f > d ? nextafterf(f, -FLT_MAX) : f;
+    const float f = (float)d;
+    const int b = __float_as_int(f);
+    const float g = f == 0.f ? -FLT_TRUE_MIN : __int_as_float(b + (b < 0 ? 1 : -1));
+    return (double)f > d ? fmaxf(g, -FLT_MAX) : f;
 }
-__device__ __forceinline__ float f_upr(double d) {
-    float f = (float)d;
-    return (double)f < d ? nextafterf(f, FLT_MAX) : f;
-}
+__device__ __forceinline__ float f_upr(double d) { return -f_dn(-d); }
 
 __device__ __forceinline__ GroupBox group_box(double x, double y, double z) {
     double mnx = x, mny = y, mnz = z;
@@ -142,10 +143,10 @@ __device__ __forceinline__ float near_imgf(float d, const WalkOut& O) {
     return __builtin_fmaf(-O.boxf, rintf(d * O.boxf_inv), d);
 }
 
-// Opening test for node data (com, extent, box) against the group box.
+// Opening test for a node's record against the group box.
 // Accept iff  L' <= theta * r_min  (r_min: distance from the node's centre of
 // mass to the nearest point of the group box; L' the node's extent L, plus,
-// with `offset` set, the distance from its centre of mass to the centre of
+// with mac_offset set, the distance from its centre of mass to the centre of
 // its box, which opens lopsided nodes sooner)  and the node's box is at least
 // eps away from the group box (so only Newtonian pairs are approximated).
 // Periodic (kPer != 0): distances are taken at the nearest image of the node, and
@@ -153,8 +154,8 @@ __device__ __forceinline__ float near_imgf(float d, const WalkOut& O) {
 // half a box side of all of the group box -- then every particle-target pair
 // of the node has that same nearest image, and the multipole stands for it.
 template <int kPer>
-__device__ __forceinline__ bool mac_accept(const GroupBox& g, const double4 c, const float4 lo, const float4 hi,
-                                           float theta2, float eps2, bool offset, const WalkOut& O) {
+__device__ __forceinline__ bool mac_accept(const GroupBox& g, const NodeRec& c, float theta2, float eps2, const WalkOut& O) {
+    const float4 lo = c.lo, hi = c.hi;
     double cdx = c.x - g.cx, cdy = c.y - g.cy, cdz = c.z - g.cz;
     if (kPer) {   // the node's image about the image origin, seen from the group centre
         cdx = near_img(c.x - g.ox, O) + (g.ox - g.cx);
@@ -165,13 +166,7 @@ __device__ __forceinline__ bool mac_accept(const GroupBox& g, const double4 c, c
     const float ry = fmaxf(fabsf((float)cdy) - g.hy, 0.f);
     const float rz = fmaxf(fabsf((float)cdz) - g.hz, 0.f);
     const float r2 = rx * rx + ry * ry + rz * rz;
-    float L = (float)c.w;
-    if (offset) {
-        const float ox = (float)c.x - 0.5f * (lo.x + hi.x);
-        const float oy = (float)c.y - 0.5f * (lo.y + hi.y);
-        const float oz = (float)c.z - 0.5f * (lo.z + hi.z);
-        L += sqrtf(ox * ox + oy * oy + oz * oz);
-    }
+    const float L = O.mac_offset ? c.mac : c.len;
     float gx, gy, gz;
     float bx, by, bz;   // box centre offset from the group centre (at its nearest image)
     if (!kPer) {
@@ -209,7 +204,7 @@ __device__ __forceinline__ bool mac_accept(const GroupBox& g, const double4 c, c
     // centre.  For a group, r is the distance from the centre of mass to the
     // group's box (r2 above) and |a_old| the smallest of its targets, so
     // every target passes; the cube must miss the whole group box.
-    const float Ln = (float)c.w;
+    const float Ln = c.len;
     if (!(O.rel_g * hi.w * Ln * Ln <= O.rel_alpha * g.amin * (r2 * r2))) return false;
     if (!kPer) {
         bx = fabsf((float)(0.5 * ((double)lo.x + (double)hi.x) - g.cx));
@@ -297,7 +292,7 @@ struct TileLds {
 };
 // lists of one traversal
 struct ListLds {
-    int plist[kPCap];
+    int plist[kPCap + kListSlack];
     int nlist[kNCap];
     int2 stack[kSCap];
 };
@@ -448,7 +443,7 @@ struct ForwardPolicy {
     template <int kPer>
     __device__ static void stage_node(Tile& S, const Tree& T, const GroupBox& gb, int lane, int nk,
                                       const WalkOut& O) {
-        const double4 c = T.com[nk];
+        const NodeRec& c = T.rec[nk];
         const float4 m0 = T.mp[4 * nk], m1 = T.mp[4 * nk + 1], m2 = T.mp[4 * nk + 2], m3 = T.mp[4 * nk + 3];
         float4* d = S.tile;
         double dx = c.x - gb.ox, dy = c.y - gb.oy, dz = c.z - gb.oz;
@@ -567,7 +562,7 @@ struct AdjointPolicy {
     }
     template <int kPer>
     __device__ static void stage_node(Tile& S, const Tree& T, const GroupBox& gb, int lane, int nk, const WalkOut&) {
-        const double4 c = T.com[nk];
+        const NodeRec& c = T.rec[nk];
         float4* d = S.tile;
         d[lane] = make_float4((float)(c.x - gb.cx), (float)(c.y - gb.cy), (float)(c.z - gb.cz), 0.f);
 #pragma unroll
@@ -719,8 +714,8 @@ __device__ __forceinline__ void ewald_lookup(const WalkOut& O, float dx, float d
 // node's box and the group's box shifted by any n L, n != 0.  Per axis the
 // gap is either the one about the group centre or, across the cut, the one
 // through the neighbouring image; at least one axis takes the latter.
-__device__ __forceinline__ bool ewald_accept(const GroupBox& g, const double4 c, const float4 lo, const float4 hi,
-                                             const WalkOut& O) {
+__device__ __forceinline__ bool ewald_accept(const GroupBox& g, const NodeRec& c, const WalkOut& O) {
+    const float4 lo = c.lo, hi = c.hi;
     float b[3], e[3];
     b[0] = fabsf((float)(near_img(0.5 * ((double)lo.x + (double)hi.x) - g.ox, O) + (g.ox - g.cx)));
     b[1] = fabsf((float)(near_img(0.5 * ((double)lo.y + (double)hi.y) - g.oy, O) + (g.oy - g.cy)));
@@ -742,7 +737,7 @@ __device__ __forceinline__ bool ewald_accept(const GroupBox& g, const double4 c,
         }
     }
     if (!shifted) s2 += step;
-    return (float)c.w <= O.ewald_theta * sqrtf(s2);
+    return c.len <= O.ewald_theta * sqrtf(s2);
 }
 
 // The correction walk: accepted nodes (and the particles of opened leaves)
@@ -802,7 +797,7 @@ struct EwaldPolicy {
     }
     template <int kPer>
     __device__ static void stage_node(Tile& S, const Tree& T, const GroupBox& gb, int lane, int nk, const WalkOut& O) {
-        const double4 c = T.com[nk];
+        const NodeRec& c = T.rec[nk];
         const float4 m0 = T.mp[4 * nk], m1 = T.mp[4 * nk + 1], m2 = T.mp[4 * nk + 2];
         S.tile[lane] = make_float4((float)near_img(c.x - gb.ox, O), (float)near_img(c.y - gb.oy, O),
                                    (float)near_img(c.z - gb.oz, O), m0.x);
@@ -1048,11 +1043,51 @@ __device__ __forceinline__ GroupSetup group_setup(const Tree& T, const Groups& G
     return U;
 }
 
+// Every lane's numbers first, first + 1, ... (give of them, give >= 0) to its
+// own run of the list at p; the lanes' runs follow one another.  All lanes
+// write as many as the longest run needs, from the last number to the first:
+// what a lane writes past its own run lies in the runs of later lanes, at
+// numbers that those write afterwards (a later lane's run starts later, so the
+// same place is a smaller number there), or in the slack behind the list.  A
+// number then takes two instructions, not a loop of eight that every lane
+// waits for.  (The barriers keep the compiler from reordering or pairing the
+// writes; the LDS takes a wave's writes in order.)
+__device__ __forceinline__ void list_run(int* p, int first, int give) {
+    auto put = [&](int k) {
+        p[k] = first + k;
+        asm volatile("" ::: "memory");
+    };
+    const bool more = __ballot(give > 8) != 0, most = __ballot(give > 16) != 0;
+    if (give > 0) {
+        if (most) {   // leaves of more than 16 particles
+            for (int k = give - 1; k >= kListSlack; --k) put(k);
+#pragma unroll 4
+            for (int k = kListSlack - 1; k >= 16; --k) put(k);
+        }
+        if (more) {
+#pragma unroll
+            for (int k = 15; k >= 8; --k) put(k);
+        }
+#pragma unroll
+        for (int k = 7; k >= 0; --k) put(k);
+    }
+}
+
 // One wave walks the tree for a group and hands every full tile of accepted
 // nodes or of particles (64 list entries, the list's last ones first), and at
 // the end the two remainders, to tile(is_node, list, count).  The order of the
 // tiles and of the entries in them depends on the tree and the group alone.
-template <class Pol, int kPer, bool kSoft, class TileFn>
+//
+// A step tests one node per lane.  With kAhead the next nodes' records are
+// asked for as soon as the step has decided which they are, and the step's
+// lists and tiles are written while the loads are on their way: for a wave that
+// does nothing but traverse, one load per step was 40 % of its time (3000
+// particles: 2820 cycles a step, now 2130; step of 2^15 particles 0.30 ms, now
+// 0.28).  A wave
+// that evaluates its tiles itself asks for them when it needs them (the
+// registers are worth more; other waves fill the wait).  tile() gets a function
+// that asks again, for after it has used the registers itself.
+template <class Pol, int kPer, bool kSoft, bool kAhead, class TileFn>
 __device__ __forceinline__ void traverse(ListLds& S, const Tree& T, const WalkOut& O, const GroupBox& gb, float gh2,
                                          int root, int lane, float theta2, float eps2,
                                          TileFn tile) {
@@ -1064,50 +1099,46 @@ __device__ __forceinline__ void traverse(ListLds& S, const Tree& T, const WalkOu
     }
     int sp = 0;                  // stack depth (uniform)
     int npend = 0, ppend = 0;    // list fills (uniform)
-    int64_t iters = 0;
+    NodeRec c;                   // node ca, for a lane that walks
+    int4 L;
+    float wn = 1.f;
+    auto load = [&] {   // (by all lanes: the old values need no registers meanwhile)
+        const int64_t a = ca < cb && pc == 0 ? ca : 0;
+        L = T.link[a];
+        c = T.rec[a];
+        if (Pol::kSkipEmpty) wn = T.wf[8 * a].w;
+    };
+    if (kAhead) load();
+    unsigned iters = 0;
     for (;;) {
-        // every step tests a node or lists particles, so the loop ends within
-        // (nodes + particles) steps; the cap only guards against a corrupt tree
-        if (++iters > O.iter_cap) {
-            if (lane == 0) atomicOr(O.flags, AGF_INTERNAL);
-            break;
-        }
-        // 1. idle lanes take ranges from the stack
-        {
-            const bool idle = (ca >= cb) && pc == 0;
-            const uint64_t im = __ballot(idle);
-            const int nidle = __popcll(im);
-            const int take = nidle < sp ? nidle : sp;
-            if (take > 0) {
-                const int r = ag_prefix_count(im);
-                if (idle && r < take) {
-                    const int2 e = S.stack[sp - 1 - r];
-                    ca = e.x;
-                    cb = e.y;
-                }
-                sp -= take;
-            }
-            wave_sync();
-        }
         const bool walking = (ca < cb) && pc == 0;
-        if (__ballot(walking || pc > 0) == 0) break;
+        const bool end = __ballot(walking || pc > 0) == 0 || iters > O.iter_cap;
+        // 6. full tiles, and at the end the remainders
+        const int least = end ? 1 : kW;
+        while (npend >= least || ppend >= least) {
+            const bool node = npend >= least;
+            int& pend = node ? npend : ppend;
+            const int cnt = pend < kW ? pend : kW;
+            pend -= cnt;
+            tile(node, (node ? S.nlist : S.plist) + pend, cnt, load);
+        }
+        if (end) break;
+        ++iters;
+        if (!kAhead) load();
 
-        // 2. test one node per walking lane
+        // 1. test one node per walking lane
         int push_node = -1;
         int push_range_a = 0, push_range_b = 0;
         bool want_push = false;
         if (walking) {
             const int a = ca;
-            const int4 L = T.link[a];
             const bool leaf = (L.w & 0x100) != 0;
-            if (Pol::kSkipEmpty && T.wf[8 * a].w == 0.f) {
+            if (Pol::kSkipEmpty && wn == 0.f) {
                 ca = L.x;                  // nothing below this node matters
             } else {
                 const bool acc_ok =
-                    Pol::kImageMac ? ewald_accept(gb, T.com[a], T.lo[a], T.hi[a], O)
-                                   : mac_accept<kPer>(gb, T.com[a], T.lo[a], T.hi[a], theta2,
-                                                      kSoft ? fmaxf(gh2, T.lo[a].w * T.lo[a].w) : eps2,
-                                                      O.mac_offset, O);
+                    Pol::kImageMac ? ewald_accept(gb, c, O)
+                                   : mac_accept<kPer>(gb, c, theta2, kSoft ? fmaxf(gh2, c.lo.w * c.lo.w) : eps2, O);
                 if (acc_ok && L.z > O.small_node) {
                     push_node = a;
                     ca = L.x;
@@ -1125,16 +1156,7 @@ __device__ __forceinline__ void traverse(ListLds& S, const Tree& T, const WalkOu
                 }
             }
         }
-        // 3a. accepted nodes -> node list (always fits: npend < 64 here)
-        {
-            const uint64_t m = __ballot(push_node >= 0);
-            if (m) {
-                const int r = ag_prefix_count(m);
-                if (push_node >= 0) S.nlist[npend + r] = push_node;
-                npend += __popcll(m);
-            }
-        }
-        // 3b. split ranges -> stack (lanes beyond capacity keep their range)
+        // 2. split ranges -> stack (lanes beyond capacity keep their range)
         {
             const uint64_t m = __ballot(want_push);
             if (m) {
@@ -1148,33 +1170,59 @@ __device__ __forceinline__ void traverse(ListLds& S, const Tree& T, const WalkOu
                 sp += pushed < room ? pushed : room;
             }
         }
-        // 3c. particles of opened leaves -> particle list, as room allows
-        if (__ballot(pc > 0) != 0) {
+        // 3. the share of the particle list that each opened leaf gets, as room allows
+        const bool listing = __ballot(pc > 0) != 0;
+        const int first = ps;
+        int excl = 0, give = 0, listed = 0;
+        if (listing) {
             const int want = pc;
             const int incl = ag_wave_incl_scan(want);
-            const int excl = incl - want;
+            excl = incl - want;
             const int total = __builtin_amdgcn_readlane(incl, 63);
             const int room = kPCap - ppend;
-            int give = room - excl;
+            give = room - excl;
             give = give < 0 ? 0 : (give > want ? want : give);
-            for (int k = 0; k < give; ++k) S.plist[ppend + excl + k] = ps + k;
             ps += give;
             pc -= give;
-            ppend += total < room ? total : room;
+            listed = total < room ? total : room;
         }
         wave_sync();
-        // 4. full tiles
-        while (npend >= kW) {
-            npend -= kW;
-            tile(true, S.nlist + npend, kW);
+        // 4. idle lanes take ranges from the stack
+        {
+            const bool idle = (ca >= cb) && pc == 0;
+            const uint64_t im = __ballot(idle);
+            const int nidle = __popcll(im);
+            const int take = nidle < sp ? nidle : sp;
+            if (take > 0) {
+                const int r = ag_prefix_count(im);
+                if (idle && r < take) {
+                    const int2 e = S.stack[sp - 1 - r];
+                    ca = e.x;
+                    cb = e.y;
+                }
+                sp -= take;
+            }
         }
-        while (ppend >= kW) {
-            ppend -= kW;
-            tile(false, S.plist + ppend, kW);
+        if (kAhead) load();
+        // 5. accepted nodes -> node list (always fits: npend < 64 here),
+        // particles of opened leaves -> particle list
+        {
+            const uint64_t m = __ballot(push_node >= 0);
+            if (m) {
+                const int r = ag_prefix_count(m);
+                if (push_node >= 0) S.nlist[npend + r] = push_node;
+                npend += __popcll(m);
+            }
         }
+        if (listing) {
+            list_run(S.plist + ppend + excl, first, give);
+            ppend += listed;
+        }
+        wave_sync();
     }
-    if (npend > 0) tile(true, S.nlist, npend);
-    if (ppend > 0) tile(false, S.plist, ppend);
+    // every step tests a node or lists particles, so the loop ends within
+    // (nodes + particles) steps; the cap only guards against a corrupt tree
+    if (iters > O.iter_cap && lane == 0) atomicOr(O.flags, AGF_INTERNAL);
 }
 
 // What a wave's groups add to the context's counters: kept by the wave and
@@ -1212,8 +1260,8 @@ __device__ __forceinline__ void walk_group(typename Pol::Lds& S, const Tree& T, 
     acc.zero();
 
     uint64_t n_pp = 0, n_pn = 0;
-    traverse<Pol, kPer, kSoft>(S, T, O, U.gb, U.gh2, T.sys_root[gd.z], lane, theta2, eps2,
-                               [&](bool node, const int* list, int cnt) {
+    traverse<Pol, kPer, kSoft, false>(S, T, O, U.gb, U.gh2, T.sys_root[gd.z], lane, theta2, eps2,
+                                      [&](bool node, const int* list, int cnt, auto) {
         if (lane < cnt) {
             if (node) Pol::template stage_node<kPer>(S, T, U.gb, lane, list[lane], O);
             else Pol::template stage_particle<kPer>(S, T, U.gb, lane, list[lane], O);
@@ -1364,12 +1412,15 @@ __device__ __forceinline__ void walk_group_team(TeamLds<Pol>& S, typename Pol::T
     uint64_t n_pp = 0, n_pn = 0;
     if (wave == 0) {
         int tail = 0;
-        traverse<Pol, kPer, kSoft>(S.lists, T, O, U.gb, U.gh2, T.sys_root[gd.z], lane,
-                                   theta2, eps2, [&](bool node, const int* list, int cnt) {
+        __builtin_amdgcn_s_setprio(2);   // the team waits for this wave's tiles
+        traverse<Pol, kPer, kSoft, true>(S.lists, T, O, U.gb, U.gh2, T.sys_root[gd.z], lane,
+                                         theta2, eps2, [&](bool node, const int* list, int cnt, auto reload) {
             const int s = tail % kRing;
+            int full = lds_get(&S.full[s]);
+            const int id = lane < cnt ? list[lane] : 0;
             // a full queue: take its oldest tile that no wave has asked for,
             // or wait for the wave that has asked for the slot's
-            while (lds_get(&S.full[s]) != 0) {
+            while (full != 0) {
                 int t = -1;
                 if (lane == 0) {
                     int h = lds_get(&S.head);
@@ -1382,22 +1433,27 @@ __device__ __forceinline__ void walk_group_team(TeamLds<Pol>& S, typename Pol::T
                 if (t >= 0) {
                     team_acquire();
                     evaluate(t);
+                    reload();
                 } else {
                     __builtin_amdgcn_s_sleep(1);
                 }
+                full = lds_get(&S.full[s]);
             }
-            if (lane < cnt) S.ring[s][lane] = list[lane];
+            if (lane < cnt) S.ring[s][lane] = id;
             if (lane == 0) {
                 lds_put(&S.info[s], node ? -cnt : cnt);
                 lds_put(&S.full[s], 1);
             }
-            team_release();
+            // (the LDS takes a wave's writes in order: no wait for the tile's
+            // before the one that announces it)
+            asm volatile("" ::: "memory");
             ++tail;
             if (lane == 0) lds_put(&S.tail, tail);
             if (node) n_pn += (uint64_t)cnt;
             else n_pp += (uint64_t)cnt;
             wave_sync();
         });
+        __builtin_amdgcn_s_setprio(0);
         team_release();
         if (lane == 0) lds_put(&S.done, 1);
     }
@@ -2028,10 +2084,8 @@ __global__ void k_inner_wlevel(int l_hi, int l_lo, const int32_t* __restrict__ l
 
 static Tree make_tree(ag_ctx* c) {
     Tree T;
-    T.com = c->nd_com.as<double4>();
+    T.rec = c->nd_rec.as<NodeRec>();
     T.sh = c->tree_soft ? c->soft_s.as<float>() : nullptr;
-    T.lo = c->nd_lo.as<float4>();
-    T.hi = c->nd_hi.as<float4>();
     T.link = c->nd_link.as<int4>();
     T.mp = c->nd_mp.as<float4>();
     T.spos = c->spos.as<double4>();
@@ -2095,7 +2149,7 @@ static WalkOut make_out(ag_ctx* c, double G) {
     O.stats = c->stats.as<unsigned long long>();
     O.G = G;
     O.flags = c->dflags.as<int32_t>();
-    O.iter_cap = c->max_nodes + c->n + 1024;
+    O.iter_cap = (unsigned)std::min<int64_t>(c->max_nodes + c->n + 1024, UINT_MAX - 1);
     O.small_node = c->small_node;
     O.mac_offset = c->mac_offset != 0;
     O.box = c->box;
