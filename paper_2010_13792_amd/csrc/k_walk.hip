@@ -1312,6 +1312,7 @@ __device__ __forceinline__ void walk_group(typename Pol::Lds& S, const Tree& T, 
 // results are the same bit for bit whichever way a group is walked.
 constexpr int kRing = 16;   // queued tiles
 constexpr int kMinTeam = 4; // waves of the smallest team
+constexpr int kTeamClosed = 0, kTeamOpen = 1, kTeamDone = 2;
 template <class Pol>
 struct TeamLds {
     ListLds lists;
@@ -1321,7 +1322,8 @@ struct TeamLds {
     int full[kRing];        // slot holds a tile that no wave has taken yet
     int head, tail, done;   // next tile to take, tiles queued, traversal finished
     int turn;               // next tile whose sums are folded
-    int g;                  // the team's group
+    int g;                  // the team's group, -1 when none is left
+    int state;              // kTeamClosed, kTeamOpen (its tiles may be taken), kTeamDone
     int arrived;            // waves that have come to the team's barriers so far
 };
 
@@ -1347,7 +1349,7 @@ __device__ __forceinline__ void team_barrier(int* arrived, int ts) {
 }
 
 template <class Pol, int kPer, bool kSoft>
-__device__ __forceinline__ void walk_group_team(TeamLds<Pol>& S, typename Pol::Tile& st, int wave, int ts,
+__device__ __forceinline__ void walk_group_team(TeamLds<Pol>& S, typename Pol::Tile& st, int wave, int ts, bool guest,
                                                 const Tree& T, const Groups& Gr, const WalkOut& O, const int4 gd,
                                                 float theta2, float eps2, float h2, float hinv, WalkCount& C) {
     constexpr int kN = Pol::kWords;
@@ -1359,12 +1361,15 @@ __device__ __forceinline__ void walk_group_team(TeamLds<Pol>& S, typename Pol::T
     const GroupSetup U = group_setup<Pol, kPer, kSoft>(T, Gr, O, gd, eps2, lane);
     const Target tg = U.tg;
     const int count = U.count, sub = U.sub, slot = U.slot, part = U.part;
-    for (int k = wave; k < kN; k += ts) S.acc[k][lane] = 0;
-    if (wave == 0) {
-        if (lane < kRing) S.full[lane] = 0;
-        if (lane == 0) S.head = S.tail = S.done = S.turn = 0;
+    if (!guest) {
+        for (int k = wave; k < kN; k += ts) S.acc[k][lane] = 0;
+        if (wave == 0) {
+            if (lane < kRing) S.full[lane] = 0;
+            if (lane == 0) S.head = S.tail = S.done = S.turn = 0;
+        }
+        team_barrier(&S.arrived, ts);
+        if (wave == 0 && lane == 0) lds_put(&S.state, kTeamOpen);
     }
-    team_barrier(&S.arrived, ts);
 
     // the queue's tile t: staged, evaluated and, in its turn, folded
     auto evaluate = [&](int t) {
@@ -1410,8 +1415,8 @@ __device__ __forceinline__ void walk_group_team(TeamLds<Pol>& S, typename Pol::T
     };
 
     uint64_t n_pp = 0, n_pn = 0;
-    if (wave == 0) {
-        int tail = 0;
+    int tail = 0;
+    if (wave == 0 && !guest) {
         __builtin_amdgcn_s_setprio(2);   // the team waits for this wave's tiles
         traverse<Pol, kPer, kSoft, true>(S.lists, T, O, U.gb, U.gh2, T.sys_root[gd.z], lane,
                                          theta2, eps2, [&](bool node, const int* list, int cnt, auto reload) {
@@ -1475,8 +1480,11 @@ __device__ __forceinline__ void walk_group_team(TeamLds<Pol>& S, typename Pol::T
         team_acquire();
         evaluate(t);
     }
+    if (guest) return;
     team_barrier(&S.arrived, ts);
     if (wave == 0) {
+        while (lds_get(&S.turn) != tail) __builtin_amdgcn_s_sleep(1);   // guests may hold the last tiles
+        team_acquire();
         typename Pol::Acc acc;
         typename Pol::Word* a = reinterpret_cast<typename Pol::Word*>(&acc);
 #pragma unroll
@@ -1546,17 +1554,53 @@ __global__ void __launch_bounds__(W * kW, Pol::kWaves) k_walk_team(Tree T, Group
         }
     } else {
         const int ts = n_groups > R.teams_above ? R.mid : W;
-        Team& S = reinterpret_cast<Team*>(s_mem + W * sizeof(Tile))[wave / ts];
+        Team* teams = reinterpret_cast<Team*>(s_mem + W * sizeof(Tile));
+        const int n_teams = W / ts, own = wave / ts;
         Tile& st = reinterpret_cast<Tile*>(s_mem)[wave];
         const int me = wave % ts;
-        if (me == 0 && ag_lane() == 0) S.arrived = 0;
+        if (me == 0 && ag_lane() == 0) {
+            teams[own].arrived = 0;
+            teams[own].state = kTeamClosed;
+        }
         __syncthreads();
+        bool guest = false;
         for (;;) {
-            if (me == 0 && ag_lane() == 0) S.g = pop_group(qctr, n_groups, q);
-            team_barrier(&S.arrived, ts);
-            const int g = lds_get(&S.g);
-            if (g < 0) break;
-            walk_group_team<Pol, kPer, kSoft>(S, st, me, ts, T, Gr, O, Gr.grp[g], theta2, eps2, h2, hinv, C);
+            int team = own;
+            if (!guest) {
+                if (me == 0 && ag_lane() == 0) {
+                    lds_put(&teams[own].state, kTeamClosed);
+                    const int g = pop_group(qctr, n_groups, q);
+                    lds_put(&teams[own].g, g);
+                    if (g < 0) lds_put(&teams[own].state, kTeamDone);
+                }
+                team_barrier(&teams[own].arrived, ts);
+                guest = lds_get(&teams[own].g) < 0;
+            }
+            if (guest) {
+                // No group is left for any team (the queues only run up): a
+                // team that is open walks its last one, and this wave takes
+                // tiles of it.  The waves of a team start at different hosts.
+                bool left = false;
+                team = -1;
+                for (int k = 0; k < n_teams - 1; ++k) {
+                    const int o = (own + 1 + (me + k) % (n_teams - 1)) % n_teams;
+                    const int state = lds_get(&teams[o].state);
+                    left |= state != kTeamDone;
+                    if (team < 0 && state == kTeamOpen &&
+                        (lds_get(&teams[o].done) == 0 || lds_get(&teams[o].head) < lds_get(&teams[o].tail)))
+                        team = o;
+                }
+                if (!left) break;
+                if (team < 0) {
+                    __builtin_amdgcn_s_sleep(8);
+                    continue;
+                }
+                team_acquire();
+            }
+            const int g = lds_get(&teams[team].g);
+            if (g < 0) continue;   // the host has just ended
+            walk_group_team<Pol, kPer, kSoft>(teams[team], st, me, ts, guest, T, Gr, O, Gr.grp[g], theta2, eps2, h2,
+                                              hinv, C);
         }
     }
     C.add_to(O.stats);
