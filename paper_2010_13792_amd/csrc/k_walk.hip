@@ -326,9 +326,9 @@ struct ForwardPolicy {
     static constexpr bool kSkipEmpty = false;
     static constexpr bool kImageMac = false;
     static constexpr bool kGroupSum = false;
+    static constexpr int kTerms = 0;
     static constexpr int kWaves = 4;   // launch bound: waves per SIMD (128 registers)
-    static constexpr int kTeamWaves = 16;   // largest team; with the relative opening test the middle one has kRelTeam
-    static constexpr int kRelTeam = 8;
+    static constexpr int kTeamWaves = 16;   // waves of a workgroup: the largest team
     using Tile = TileLds<5>;
     using Lds = WalkLds<5>;
     using Sum = PairAcc<float>;   // one tile's sums
@@ -506,9 +506,9 @@ struct AdjointPolicy {
     static constexpr bool kSkipEmpty = true;   // nodes without charge add nothing
     static constexpr bool kImageMac = false;
     static constexpr bool kGroupSum = false;
+    static constexpr int kTerms = 0;
     static constexpr int kWaves = 3;   // launch bound: waves per SIMD (168 registers)
     static constexpr int kTeamWaves = 12;
-    static constexpr int kRelTeam = 4;
     using Tile = TileLds<9>;
     using Lds = WalkLds<9>;
     using Sum = AdjAccF;
@@ -758,7 +758,6 @@ struct EwaldPolicy {
     static constexpr bool kGroupSum = true;
     static constexpr int kWaves = 4;   // launch bound: waves per SIMD (128 registers)
     static constexpr int kTeamWaves = 16;
-    static constexpr int kRelTeam = 4;
     using Tile = TileLds<3>;
     using Lds = WalkLds<3>;
     // one tile's terms of a group sum (each lane holds at most one entry)
@@ -905,34 +904,42 @@ struct EwaldPolicy {
     // about the group centre; the periodic field is the same at the nearest
     // image d', where the table is accurate, so add
     // dg(d') + g_single(d') - g_single(d)  (the last two only when d' != d).
-    // The terms go straight into the walk's sums, entry by entry.
+    // The terms (of g and T, entry k) go straight into the walk's sums, entry by
+    // entry.
+    static constexpr int kTerms = 9;
+    __device__ static void target_terms(const Tile& S, int k, const Target& t, float* term, const WalkOut& O) {
+        EwaldVal E;
+        const float4 e = S.tile[k];
+        const float4 q0 = S.tile[kW + k], q1 = S.tile[2 * kW + k];
+        const float dx = e.x - t.tx, dy = e.y - t.ty, dz = e.z - t.tz;
+        const float nx = near_imgf(dx, O), ny = near_imgf(dy, O), nz = near_imgf(dz, O);
+        ewald_lookup<true>(O, nx, ny, nz, E);
+        float gq[3] = {e.w * E.g[0], e.w * E.g[1], e.w * E.g[2]};
+        float tq[6];
+#pragma unroll
+        for (int c = 0; c < 6; ++c) tq[c] = e.w * E.t[c];
+        quad_g(q0, q1, E, gq);
+        if (nx != dx || ny != dy || nz != dz) {
+            float g1[3], t1[6], g0[3], t0[6];
+            newton_quad(nx, ny, nz, e.w, q0, q1, g1, t1);
+            newton_quad(dx, dy, dz, e.w, q0, q1, g0, t0);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) gq[c] += g1[c] - g0[c];
+#pragma unroll
+            for (int c = 0; c < 6; ++c) tq[c] += t1[c] - t0[c];
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) term[c] = gq[c];
+#pragma unroll
+        for (int c = 0; c < 6; ++c) term[3 + c] = tq[c];
+    }
     __device__ static void target_entries(const Tile& S, int cnt, const Target& t, Acc& acc, int k0, int ks,
                                           const WalkOut& O) {
-        EwaldVal E;
         for (int k = k0; k < cnt; k += ks) {
-            const float4 e = S.tile[k];
-            const float4 q0 = S.tile[kW + k], q1 = S.tile[2 * kW + k];
-            const float dx = e.x - t.tx, dy = e.y - t.ty, dz = e.z - t.tz;
-            const float nx = near_imgf(dx, O), ny = near_imgf(dy, O), nz = near_imgf(dz, O);
-            ewald_lookup<true>(O, nx, ny, nz, E);
-            float gq[3] = {e.w * E.g[0], e.w * E.g[1], e.w * E.g[2]};
-            float tq[6];
+            float term[kTerms];
+            target_terms(S, k, t, term, O);
 #pragma unroll
-            for (int c = 0; c < 6; ++c) tq[c] = e.w * E.t[c];
-            quad_g(q0, q1, E, gq);
-            if (nx != dx || ny != dy || nz != dz) {
-                float g1[3], t1[6], g0[3], t0[6];
-                newton_quad(nx, ny, nz, e.w, q0, q1, g1, t1);
-                newton_quad(dx, dy, dz, e.w, q0, q1, g0, t0);
-#pragma unroll
-                for (int c = 0; c < 3; ++c) gq[c] += g1[c] - g0[c];
-#pragma unroll
-                for (int c = 0; c < 6; ++c) tq[c] += t1[c] - t0[c];
-            }
-#pragma unroll
-            for (int c = 0; c < 3; ++c) acc.v[c] += gq[c];
-#pragma unroll
-            for (int c = 0; c < 6; ++c) acc.v[3 + c] += tq[c];
+            for (int c = 0; c < kTerms; ++c) acc.v[c] += term[c];
         }
     }
     template <int kPer, bool kSoft>
@@ -1312,6 +1319,13 @@ __device__ __forceinline__ void walk_group(typename Pol::Lds& S, const Tree& T, 
 // results are the same bit for bit whichever way a group is walked.
 constexpr int kRing = 16;   // queued tiles
 constexpr int kMinTeam = 4; // waves of the smallest team
+// Where a tile's terms go into the group's sums one entry after another
+// (Ewald, groups wider than the expansion allows), it is queued in parts of
+// this many entries: the waves of the team work out their parts' terms at the
+// same time and only add them up in turn.  Taken a tile at a time, one wave of
+// the team worked and the others waited (2^18 particles, a third of them
+// active: 3.04 ms per evaluation, now 2.03).
+constexpr int kPart = 4;
 constexpr int kTeamClosed = 0, kTeamOpen = 1, kTeamDone = 2;
 template <class Pol>
 struct TeamLds {
@@ -1371,12 +1385,13 @@ __device__ __forceinline__ void walk_group_team(TeamLds<Pol>& S, typename Pol::T
         if (wave == 0 && lane == 0) lds_put(&S.state, kTeamOpen);
     }
 
+    const bool in_turn = Pol::kGroupSum && !tg.grp;   // terms go straight into the group's sums
     // the queue's tile t: staged, evaluated and, in its turn, folded
     auto evaluate = [&](int t) {
         const int s = t % kRing;
         const int info = lds_get(&S.info[s]);
         const bool node = info < 0;
-        const int cnt = node ? -info : info;
+        const int cnt = (node ? -info : info) & 127;
         const int id = S.ring[s][lane];
         team_release();              // the slot is read ...
         if (lane == 0) lds_put(&S.full[s], 0);   // ... before it is given back
@@ -1386,22 +1401,31 @@ __device__ __forceinline__ void walk_group_team(TeamLds<Pol>& S, typename Pol::T
         }
         wave_sync();
         typename Pol::Sum F;
-        const bool in_turn = Pol::kGroupSum && !tg.grp;   // terms go straight into the group's sums
+        float term[Pol::kGroupSum ? kPart * Pol::kTerms : 1];   // (in_turn) of every sub-th entry
+        int k0 = 0;
         if (!in_turn) {
             if (node) Pol::nodes(st, cnt, tg, F, part, sub, O);
             else Pol::template particles<kPer, kSoft>(st, cnt, tg, F, h2, hinv, part, sub, O);
+        } else if constexpr (Pol::kGroupSum) {
+            const int off = (node ? -info : info) >> 7;   // the part's first entry in its tile
+            k0 = (part + off * (sub - 1)) % sub;          // (part - off) modulo sub
+#pragma unroll
+            for (int j = 0; j < kPart; ++j)
+                if (k0 + j * sub < cnt) Pol::target_terms(st, k0 + j * sub, tg, term + j * Pol::kTerms, O);
         }
         // every earlier tile is held by a wave that does not wait for this one
         while (lds_get(&S.turn) != t) __builtin_amdgcn_s_sleep(1);
         team_acquire();
         if constexpr (Pol::kGroupSum) {
             if (in_turn) {
-                typename Pol::Acc a;
 #pragma unroll
-                for (int k = 0; k < kN; ++k) a.v[k] = S.acc[k][lane];
-                Pol::target_entries(st, cnt, tg, a, part, sub, O);
+                for (int c = 0; c < Pol::kTerms; ++c) {
+                    float v = S.acc[c][lane];
 #pragma unroll
-                for (int k = 0; k < kN; ++k) S.acc[k][lane] = a.v[k];
+                    for (int j = 0; j < kPart; ++j)
+                        if (k0 + j * sub < cnt) v += term[j * Pol::kTerms + c];
+                    S.acc[c][lane] = v;
+                }
             }
         }
         if (!in_turn) {
@@ -1420,40 +1444,44 @@ __device__ __forceinline__ void walk_group_team(TeamLds<Pol>& S, typename Pol::T
         __builtin_amdgcn_s_setprio(2);   // the team waits for this wave's tiles
         traverse<Pol, kPer, kSoft, true>(S.lists, T, O, U.gb, U.gh2, T.sys_root[gd.z], lane,
                                          theta2, eps2, [&](bool node, const int* list, int cnt, auto reload) {
-            const int s = tail % kRing;
-            int full = lds_get(&S.full[s]);
-            const int id = lane < cnt ? list[lane] : 0;
-            // a full queue: take its oldest tile that no wave has asked for,
-            // or wait for the wave that has asked for the slot's
-            while (full != 0) {
-                int t = -1;
+            const int step = in_turn ? kPart : kW;
+            for (int off = 0; off < cnt; off += step) {
+                const int n = cnt - off < step ? cnt - off : step;
+                const int s = tail % kRing;
+                int full = lds_get(&S.full[s]);
+                const int id = lane < n ? list[off + lane] : 0;
+                // a full queue: take its oldest tile that no wave has asked for,
+                // or wait for the wave that has asked for the slot's
+                while (full != 0) {
+                    int t = -1;
+                    if (lane == 0) {
+                        int h = lds_get(&S.head);
+                        if (h < tail && __hip_atomic_compare_exchange_strong(&S.head, &h, h + 1, __ATOMIC_RELAXED,
+                                                                             __ATOMIC_RELAXED,
+                                                                             __HIP_MEMORY_SCOPE_WORKGROUP))
+                            t = h;
+                    }
+                    t = __builtin_amdgcn_readfirstlane(t);
+                    if (t >= 0) {
+                        team_acquire();
+                        evaluate(t);
+                        reload();
+                    } else {
+                        __builtin_amdgcn_s_sleep(1);
+                    }
+                    full = lds_get(&S.full[s]);
+                }
+                if (lane < n) S.ring[s][lane] = id;
                 if (lane == 0) {
-                    int h = lds_get(&S.head);
-                    if (h < tail && __hip_atomic_compare_exchange_strong(&S.head, &h, h + 1, __ATOMIC_RELAXED,
-                                                                         __ATOMIC_RELAXED,
-                                                                         __HIP_MEMORY_SCOPE_WORKGROUP))
-                        t = h;
+                    lds_put(&S.info[s], node ? -(n + 128 * off) : n + 128 * off);
+                    lds_put(&S.full[s], 1);
                 }
-                t = __builtin_amdgcn_readfirstlane(t);
-                if (t >= 0) {
-                    team_acquire();
-                    evaluate(t);
-                    reload();
-                } else {
-                    __builtin_amdgcn_s_sleep(1);
-                }
-                full = lds_get(&S.full[s]);
+                // (the LDS takes a wave's writes in order: no wait for the tile's
+                // before the one that announces it)
+                asm volatile("" ::: "memory");
+                ++tail;
+                if (lane == 0) lds_put(&S.tail, tail);
             }
-            if (lane < cnt) S.ring[s][lane] = id;
-            if (lane == 0) {
-                lds_put(&S.info[s], node ? -cnt : cnt);
-                lds_put(&S.full[s], 1);
-            }
-            // (the LDS takes a wave's writes in order: no wait for the tile's
-            // before the one that announces it)
-            asm volatile("" ::: "memory");
-            ++tail;
-            if (lane == 0) lds_put(&S.tail, tail);
             if (node) n_pn += (uint64_t)cnt;
             else n_pp += (uint64_t)cnt;
             wave_sync();
@@ -1525,8 +1553,7 @@ __device__ __forceinline__ int pop_group(int* __restrict__ qctr, int n_groups, i
 // is held to 128 VGPRs (four waves per SIMD); the few values this spills live
 // outside the interaction loops.
 struct TeamRule {
-    int solo_above, teams_above;   // more groups than this: single waves; teams of `mid` waves; else of W waves
-    int mid;
+    int solo_above, teams_above;   // more groups than this: single waves; teams of kMinTeam waves; else of W waves
 };
 template <class Pol, int kPer, bool kSoft, int W>
 __global__ void __launch_bounds__(W * kW, Pol::kWaves) k_walk_team(Tree T, Groups Gr, WalkOut O,
@@ -1535,6 +1562,7 @@ __global__ void __launch_bounds__(W * kW, Pol::kWaves) k_walk_team(Tree T, Group
     using Solo = typename Pol::Lds;
     using Tile = typename Pol::Tile;
     using Team = TeamLds<Pol>;
+    static_assert(W % kMinTeam == 0, "teams of kMinTeam waves fill a workgroup");
     constexpr size_t kTeamBytes = W * sizeof(Tile) + W / kMinTeam * sizeof(Team);
     constexpr size_t kBytes = W * sizeof(Solo) > kTeamBytes ? W * sizeof(Solo) : kTeamBytes;
     __shared__ __align__(16) char s_mem[kBytes];   // one or the other, never both
@@ -1553,7 +1581,7 @@ __global__ void __launch_bounds__(W * kW, Pol::kWaves) k_walk_team(Tree T, Group
             wave_sync();
         }
     } else {
-        const int ts = n_groups > R.teams_above ? R.mid : W;
+        const int ts = n_groups > R.teams_above ? kMinTeam : W;
         Team* teams = reinterpret_cast<Team*>(s_mem + W * sizeof(Tile));
         const int n_teams = W / ts, own = wave / ts;
         Tile& st = reinterpret_cast<Tile*>(s_mem)[wave];
@@ -2152,15 +2180,15 @@ static int device_cus(ag_ctx* c) {
 // goes by how many there are for the P waves launched, read on the device:
 //   above 4 P   single waves: they keep every lane at interactions, and the
 //               last groups' tail is short (2^20 particles, 23 000 groups:
-//               2.99 ms per step, 3.7 ms in teams of 8)
-//   above P/4   teams of 4, whose traversing wave keeps three evaluating
-//               (200 000 particles, 4500 groups: 0.84 ms per step, 0.96 by
-//               single waves, 0.98 in teams of 8); of 8 with the relative
-//               opening test, where a group's cost goes by its smallest
-//               |a_old| and the longest ones set the time (180 000: 1.51 ms
-//               in teams of 8, 1.79 of 4, 4.1 by single waves)
-//   else        the whole workgroup (3000 particles, 70 groups: 0.30 ms per
-//               step, 0.34 in teams of 8, 0.43 of 4, 0.92 by single waves)
+//               2.64 ms per step, 2.79 in teams of 4)
+//   above P/4   teams of 4, whose traversing wave keeps three evaluating and
+//               whose waves help the others at the end (64 systems of 4000
+//               particles, 5900 groups: 1.25 ms per step, 2.2 by single waves,
+//               1.8 by whole workgroups; 180 000 with the relative opening
+//               test, whose longest groups set the time: 1.33, 4.2 and 1.6)
+//   else        the whole workgroup (3000 particles, 96 groups: 0.20 ms per
+//               step, 0.23 in teams of 8, 0.25 of 4, 0.63 by single waves;
+//               32^3 periodic ones, 704 groups: 0.90 ms, 0.93, 1.12 and 3.5)
 template <class Pol, int kPer, bool kSoft = false>
 static void launch_walk(ag_ctx* c, int64_t max_groups, const Groups& Gr, const WalkOut& O, int32_t* qctr,
                         float theta2, float eps2, float h2, float hinv) {
@@ -2168,7 +2196,7 @@ static void launch_walk(ag_ctx* c, int64_t max_groups, const Groups& Gr, const W
     int64_t blocks = (int64_t)device_cus(c) * std::max(1, c->walk_waves_per_cu / W);
     const int waves = (int)(blocks * W);
     if (blocks > max_groups) blocks = (max_groups + 7) / 8 * 8;
-    const TeamRule R{4 * waves, waves / 4, O.rel_a ? Pol::kRelTeam : kMinTeam};
+    const TeamRule R{4 * waves, waves / 4};
     hipLaunchKernelGGL((k_walk_team<Pol, kPer, kSoft, W>), dim3((unsigned)blocks), dim3(W * kW), 0, c->stream,
                        make_tree(c), Gr, O, qctr, R, theta2, eps2, h2, hinv);
 }

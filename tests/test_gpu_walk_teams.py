@@ -1,4 +1,4 @@
-"""A tree walk by single waves, by teams of 4 or 8 waves or by whole workgroups
+"""A tree walk by single waves, by teams of 4 waves or by whole workgroups
 (picked by the number of groups against the waves launched) gives the same
 bits: teams evaluate the same tiles and fold their sums in the same order.
 AG_OPT_WALK_WAVES_PER_CU moves the boundaries, so each case runs the same
