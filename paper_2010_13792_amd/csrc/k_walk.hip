@@ -226,6 +226,7 @@ __device__ __forceinline__ bool mac_accept(const GroupBox& g, const NodeRec& c, 
 // with d.Qd.d = d.V - P.nu (Q is symmetric).  Accumulates g, j and S = -T
 // (same convention as pair_interact); the ca I part of S is summed into
 // `sca` and added to the diagonal once per tile.
+template <bool kTidal>
 __device__ __forceinline__ void node_interact(float dx, float dy, float dz, float nx, float ny, float nz,
                                               float M, const float* Q, const float* Qd, PairAcc<float>& A,
                                               float& sca) {
@@ -248,9 +249,11 @@ __device__ __forceinline__ void node_interact(float dx, float dy, float dz, floa
     const float ca = __builtin_fmaf(M, ri3, hq);
     const float beta = ri2 * __builtin_fmaf(4.f, hq, 3.f * ca);
     const float nr5 = -ri5;
-    A.ax = __builtin_fmaf(nr5, Px, __builtin_fmaf(ca, dx, A.ax));
-    A.ay = __builtin_fmaf(nr5, Py, __builtin_fmaf(ca, dy, A.ay));
-    A.az = __builtin_fmaf(nr5, Pz, __builtin_fmaf(ca, dz, A.az));
+    if (!kTidal) {
+        A.ax = __builtin_fmaf(nr5, Px, __builtin_fmaf(ca, dx, A.ax));
+        A.ay = __builtin_fmaf(nr5, Py, __builtin_fmaf(ca, dy, A.ay));
+        A.az = __builtin_fmaf(nr5, Pz, __builtin_fmaf(ca, dz, A.az));
+    }
     const float ePx = e * Px, ePy = e * Py, ePz = e * Pz;
     const float wx = __builtin_fmaf(-beta, dx, ePx), wy = __builtin_fmaf(-beta, dy, ePy),
                 wz = __builtin_fmaf(-beta, dz, ePz);
@@ -261,6 +264,7 @@ __device__ __forceinline__ void node_interact(float dx, float dy, float dz, floa
     A.sxy = __builtin_fmaf(nr5, Q[3], __builtin_fmaf(ePy, dx, __builtin_fmaf(wx, dy, A.sxy)));
     A.sxz = __builtin_fmaf(nr5, Q[4], __builtin_fmaf(ePz, dx, __builtin_fmaf(wx, dz, A.sxz)));
     A.syz = __builtin_fmaf(nr5, Q[5], __builtin_fmaf(ePz, dy, __builtin_fmaf(wy, dz, A.syz)));
+    if (kTidal) return;
     const float Vx = __builtin_fmaf(Qd[4], dz, __builtin_fmaf(Qd[3], dy, __builtin_fmaf(Qd[0], dx,
                      __builtin_fmaf(Q[4], nz, __builtin_fmaf(Q[3], ny, Q[0] * nx)))));
     const float Vy = __builtin_fmaf(Qd[5], dz, __builtin_fmaf(Qd[1], dy, __builtin_fmaf(Qd[3], dx,
@@ -275,13 +279,6 @@ __device__ __forceinline__ void node_interact(float dx, float dy, float dz, floa
     A.jx = __builtin_fmaf(nr5, Vx, __builtin_fmaf(cp, Px, __builtin_fmaf(cd, dx, __builtin_fmaf(ca, nx, A.jx))));
     A.jy = __builtin_fmaf(nr5, Vy, __builtin_fmaf(cp, Py, __builtin_fmaf(cd, dy, __builtin_fmaf(ca, ny, A.jy))));
     A.jz = __builtin_fmaf(nr5, Vz, __builtin_fmaf(cp, Pz, __builtin_fmaf(cd, dz, __builtin_fmaf(ca, nz, A.jz))));
-}
-
-__device__ __forceinline__ void fold(PairAcc<double>& D, const PairAcc<float>& F) {
-    D.ax += F.ax; D.ay += F.ay; D.az += F.az;
-    D.jx += F.jx; D.jy += F.jy; D.jz += F.jz;
-    D.sxx += F.sxx; D.syy += F.syy; D.szz += F.szz;
-    D.sxy += F.sxy; D.sxz += F.sxz; D.syz += F.syz;
 }
 
 // one staged tile of sources (layout set by the policy)
@@ -322,7 +319,11 @@ __device__ __forceinline__ void soft_fd(float r2, float h, float hinv, float& f,
 }
 
 // ---- forward: g, j and S = -T from particle masses and node multipoles ----
-struct ForwardPolicy {
+// kTidal: the tidal tensor alone, which the gradient's first walk needs: half of
+// a node's multiply-adds are the jerk's (gradient of 100 000 particles 2.26 ms,
+// now 2.06).
+template <bool kTidal>
+struct ForwardSums {
     static constexpr bool kSkipEmpty = false;
     static constexpr bool kImageMac = false;
     static constexpr bool kGroupSum = false;
@@ -333,14 +334,23 @@ struct ForwardPolicy {
     using Lds = WalkLds<5>;
     using Sum = PairAcc<float>;   // one tile's sums
     using Word = double;          // the walk's sums: kWords of them per lane
-    static constexpr int kWords = 12;
+    static constexpr int kFirst = kTidal ? 6 : 0, kWords = 12 - kFirst;   // of a PairAcc's words
     struct Acc {
         PairAcc<double> a;
-        __device__ void fold(const Sum& f) { ::fold(a, f); }
+        __device__ void fold(const Sum& f) {
+            if (!kTidal) {
+                a.ax += f.ax; a.ay += f.ay; a.az += f.az;
+                a.jx += f.jx; a.jy += f.jy; a.jz += f.jz;
+            }
+            a.sxx += f.sxx; a.syy += f.syy; a.szz += f.szz;
+            a.sxy += f.sxy; a.sxz += f.sxz; a.syz += f.syz;
+        }
         __device__ void zero() { a.zero(); }
         __device__ void add(const Acc& o) {
-            a.ax += o.a.ax; a.ay += o.a.ay; a.az += o.a.az;
-            a.jx += o.a.jx; a.jy += o.a.jy; a.jz += o.a.jz;
+            if (!kTidal) {
+                a.ax += o.a.ax; a.ay += o.a.ay; a.az += o.a.az;
+                a.jx += o.a.jx; a.jy += o.a.jy; a.jz += o.a.jz;
+            }
             a.sxx += o.a.sxx; a.syy += o.a.syy; a.szz += o.a.szz;
             a.sxy += o.a.sxy; a.sxz += o.a.sxz; a.syz += o.a.syz;
         }
@@ -404,9 +414,11 @@ struct ForwardPolicy {
                 mf = mj * (f1 + f2);
                 mD = mj * (D1 + D2);
             }
-            F.ax = __builtin_fmaf(mf, dx, F.ax);
-            F.ay = __builtin_fmaf(mf, dy, F.ay);
-            F.az = __builtin_fmaf(mf, dz, F.az);
+            if (!kTidal) {
+                F.ax = __builtin_fmaf(mf, dx, F.ax);
+                F.ay = __builtin_fmaf(mf, dy, F.ay);
+                F.az = __builtin_fmaf(mf, dz, F.az);
+            }
             float jdx = dx, jdy = dy, jdz = dz, jmf = mf, jmD = mD;
             if (kPer == kEwald) {
                 // g and T take the image about the group centre (the Ewald
@@ -423,10 +435,12 @@ struct ForwardPolicy {
                     jdz = ez;
                 }
             }
-            const float sd = jmD * __builtin_fmaf(jdz, nz, __builtin_fmaf(jdy, ny, jdx * nx));
-            F.jx = __builtin_fmaf(sd, jdx, __builtin_fmaf(jmf, nx, F.jx));
-            F.jy = __builtin_fmaf(sd, jdy, __builtin_fmaf(jmf, ny, F.jy));
-            F.jz = __builtin_fmaf(sd, jdz, __builtin_fmaf(jmf, nz, F.jz));
+            if (!kTidal) {
+                const float sd = jmD * __builtin_fmaf(jdz, nz, __builtin_fmaf(jdy, ny, jdx * nx));
+                F.jx = __builtin_fmaf(sd, jdx, __builtin_fmaf(jmf, nx, F.jx));
+                F.jy = __builtin_fmaf(sd, jdy, __builtin_fmaf(jmf, ny, F.jy));
+                F.jz = __builtin_fmaf(sd, jdz, __builtin_fmaf(jmf, nz, F.jz));
+            }
             const float tx = mD * dx, ty = mD * dy, tz = mD * dz;
             smf += mf;
             F.sxx = __builtin_fmaf(tx, dx, F.sxx);
@@ -466,8 +480,8 @@ struct ForwardPolicy {
             const float4 a0 = d[k], a1 = d[kW + k], a2 = d[2 * kW + k], a3 = d[3 * kW + k], a4 = d[4 * kW + k];
             const float Q[6] = {a1.w, a2.x, a2.y, a2.z, a2.w, a3.x};
             const float Qd[6] = {a3.y, a3.z, a3.w, a4.x, a4.y, a4.z};
-            node_interact(a0.x - t.tx, a0.y - t.ty, a0.z - t.tz, a1.x - t.vx, a1.y - t.vy, a1.z - t.vz, a0.w, Q, Qd,
-                          F, sca);
+            node_interact<kTidal>(a0.x - t.tx, a0.y - t.ty, a0.z - t.tz, a1.x - t.vx, a1.y - t.vy, a1.z - t.vz, a0.w,
+                                  Q, Qd, F, sca);
         }
         F.sxx += sca;
         F.syy += sca;
@@ -478,10 +492,10 @@ struct ForwardPolicy {
         const PairAcc<double>& acc = A.a;
         const int64_t i = T.perm[p];
         const double G = O.G;
-        if (O.acc) {
+        if (!kTidal && O.acc) {
             O.acc[3 * i] = G * acc.ax; O.acc[3 * i + 1] = G * acc.ay; O.acc[3 * i + 2] = G * acc.az;
         }
-        if (O.jerk) {
+        if (!kTidal && O.jerk) {
             O.jerk[3 * i] = G * acc.jx; O.jerk[3 * i + 1] = G * acc.jy; O.jerk[3 * i + 2] = G * acc.jz;
         }
         if (O.tidal) {
@@ -491,6 +505,9 @@ struct ForwardPolicy {
         }
     }
 };
+
+using ForwardPolicy = ForwardSums<false>;
+using TidalPolicy = ForwardSums<true>;
 
 // ---- adjoint: V = sum_j J(d) w_j and s = sum_j f d.w_j over vector charges ----
 // For a node with charge sum W0 = sum w and first moment W1_bc = sum w_b y_c
@@ -513,7 +530,7 @@ struct AdjointPolicy {
     using Lds = WalkLds<9>;
     using Sum = AdjAccF;
     using Word = double;
-    static constexpr int kWords = 4;
+    static constexpr int kFirst = 0, kWords = 4;
     struct Acc {
         double vx, vy, vz, s;
         __device__ void fold(const Sum& f) { vx += f.vx; vy += f.vy; vz += f.vz; s += f.s; }
@@ -765,7 +782,7 @@ struct EwaldPolicy {
         float v[19];
     };
     using Word = float;
-    static constexpr int kWords = 19;
+    static constexpr int kFirst = 0, kWords = 19;
     struct Acc {
         // g 3, T 6, (group sums only) H 10; FP32 sums of at most a few
         // thousand terms per lane: rounding ~1e-6 relative, below the table's
@@ -1323,8 +1340,8 @@ constexpr int kMinTeam = 4; // waves of the smallest team
 // (Ewald, groups wider than the expansion allows), it is queued in parts of
 // this many entries: the waves of the team work out their parts' terms at the
 // same time and only add them up in turn.  Taken a tile at a time, one wave of
-// the team worked and the others waited (2^18 particles, a third of them
-// active: 3.04 ms per evaluation, now 2.03).
+// the team worked and the others waited (64^3 particles: 3.04 ms per
+// evaluation, now 2.03).
 constexpr int kPart = 4;
 constexpr int kTeamClosed = 0, kTeamOpen = 1, kTeamDone = 2;
 template <class Pol>
@@ -1429,7 +1446,7 @@ __device__ __forceinline__ void walk_group_team(TeamLds<Pol>& S, typename Pol::T
             }
         }
         if (!in_turn) {
-            const float* f = reinterpret_cast<const float*>(&F);
+            const float* f = reinterpret_cast<const float*>(&F) + Pol::kFirst;
 #pragma unroll
             for (int k = 0; k < kN; ++k) S.acc[k][lane] += (typename Pol::Word)f[k];
         }
@@ -1514,7 +1531,7 @@ __device__ __forceinline__ void walk_group_team(TeamLds<Pol>& S, typename Pol::T
         while (lds_get(&S.turn) != tail) __builtin_amdgcn_s_sleep(1);   // guests may hold the last tiles
         team_acquire();
         typename Pol::Acc acc;
-        typename Pol::Word* a = reinterpret_cast<typename Pol::Word*>(&acc);
+        typename Pol::Word* a = reinterpret_cast<typename Pol::Word*>(&acc) + Pol::kFirst;
 #pragma unroll
         for (int k = 0; k < kN; ++k) a[k] = S.acc[k][lane];
         if (Pol::kGroupSum && tg.grp) {
@@ -2271,6 +2288,8 @@ int ag_launch_eval(ag_ctx* c, const int32_t* idx, int64_t n_act, double theta, d
             launch_walk<ForwardPolicy, kEwald>(c, mg, Gr, O, qctr, th * th, e2, e2, hi);
         } else if (c->box > 0.0) {
             launch_walk<ForwardPolicy, kNear>(c, mg, Gr, O, qctr, th * th, e2, e2, hi);
+        } else if (!acc && !jerk) {
+            launch_walk<TidalPolicy, kOpen>(c, mg, Gr, O, qctr, th * th, e2, e2, hi);
         } else {
             launch_walk<ForwardPolicy, kOpen>(c, mg, Gr, O, qctr, th * th, e2, e2, hi);
         }

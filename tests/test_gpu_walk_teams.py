@@ -72,3 +72,19 @@ def test_same_bits_by_single_waves_and_teams(ag, what, n, targets, ways):
     assert seen == ways, (groups, seen)
     for a, b in zip(*got):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("n,targets", [(1, 64), (3001, 64), (150001, 64), (250007, 12)])
+def test_tidal_tensor_alone(ag, n, targets):
+    """The walk that sums the tidal tensor alone (whole workgroups, small teams,
+    single waves) gives the bits of the one that also sums g and the jerk."""
+    x, m, _ = workloads.uniform_sphere(n, seed=3)
+    v = np.random.default_rng(n).normal(size=x.shape)
+    with ag.Context(0) as c:
+        c.set_option(ag.AG_OPT_GROUP_TARGETS, targets)
+        c.tree_build(_t(x), _t(v), _t(m), 16)
+        acc, jerk = (torch.zeros((n, 3), dtype=torch.float64, device=DEV) for _ in range(2))
+        both, alone = (torch.zeros((n, 6), dtype=torch.float64, device=DEV) for _ in range(2))
+        c.grav_eval(None, 0.7, 1e-3, 1.0, acc, jerk, both)
+        c.grav_eval(None, 0.7, 1e-3, 1.0, None, None, alone)
+    assert torch.equal(both, alone)
