@@ -27,6 +27,7 @@ class GravEval(torch.autograd.Function):
         fctx.save_for_backward(x, v, m)
         fctx.ag = (ctx, active_idx, theta, eps, G, n_leaf)
         fctx.mark_non_differentiable(jerk, tidal)
+        fctx.set_materialize_grads(False)   # unused outputs give None, not zeros to be looked at on the device
         return acc, jerk, tidal
 
     @staticmethod
