@@ -100,9 +100,15 @@ __device__ __forceinline__ void pair_add(R dx, R dy, R dz, R nx, R ny, R nz, R m
     A.az += mf * dz;
     const R dn = dx * nx + dy * ny + dz * nz;
     const R s = mD * dn;
-    A.jx += mf * nx + s * dx;
-    A.jy += mf * ny + s * dy;
-    A.jz += mf * nz + s * dz;
+    if constexpr (sizeof(R) == 8) {   // chains of multiply-adds: one operation less per component
+        A.jx = __builtin_fma(mf, nx, __builtin_fma(s, dx, A.jx));
+        A.jy = __builtin_fma(mf, ny, __builtin_fma(s, dy, A.jy));
+        A.jz = __builtin_fma(mf, nz, __builtin_fma(s, dz, A.jz));
+    } else {
+        A.jx += mf * nx + s * dx;
+        A.jy += mf * ny + s * dy;
+        A.jz += mf * nz + s * dz;
+    }
     const R tx = mD * dx, ty = mD * dy, tz = mD * dz;
     A.smf += mf;
     A.sxx += tx * dx;
@@ -412,6 +418,13 @@ __global__ void __launch_bounds__(256) k_direct_splits(DirectArgs P, int64_t til
 // per CU for FP32 pairs); only below that at Gs = 16 is the source range
 // split as well (grid.y), so that tiles x splits stays below 2 blocks.  Each
 // split covers a multiple of the 8 Gs subsets.
+// FP64 goes on to more lane groups where that leaves less of the last round
+// of workgroups empty: a round takes the time of the targets per workgroup T
+// plus about 10^4 / n targets for its start and its final sums.
+// (20 000 particles: 313 workgroups of 64 targets are two rounds, the second
+// a quarter full, 1.09 ms; 1250 of 16 are five, 0.76 ms; 9000: 0.27 and
+// 0.21 ms, 40 000: 3.43 and 2.80.  FP32 pairs keep the
+// first shape, on which the rounding of their sums depends.)
 constexpr int64_t kBlocks64 = 256;
 constexpr int64_t kBlocks32 = 512;
 constexpr int64_t kDirectBlocks = kBlocks64 > kBlocks32 ? kBlocks64 : kBlocks32;   // bounds the split scratch
@@ -423,6 +436,18 @@ void ag_direct_shape(int64_t n, int64_t n_act, int precision, int* tshift, int64
     int64_t t = (n_act + 63) >> 6;
     while (ts > kMinTShift && t < blocks) {
         --ts;
+        t = (n_act + (1 << ts) - 1) >> ts;
+    }
+    if (precision == AG_FP64 && t >= blocks) {
+        const double start = 1e4 / (double)n;
+        auto cost = [&](int k) {
+            const int64_t rounds = (((n_act + (1 << k) - 1) >> k) + blocks - 1) / blocks;
+            return (double)rounds * ((double)(1 << k) + start);
+        };
+        int best = ts;
+        for (int k = ts - 1; k >= kMinTShift; --k)
+            if (cost(k) < cost(best)) best = k;
+        ts = best;
         t = (n_act + (1 << ts) - 1) >> ts;
     }
     const int64_t nsub = (int64_t)kWaves * (64 >> ts);
