@@ -380,7 +380,7 @@ struct ForwardSums {
                                      int k0, int ks, const WalkOut& O) {
         F.zero();
         float smf = 0.f;
-        for (int k = k0; k < cnt; k += ks) {
+        auto entry = [&](int k) {
             const float4 q = S.tile[k];
             const float4 u = S.tile[kW + k];
             float dx = q.x - t.tx, dy = q.y - t.ty, dz = q.z - t.tz;
@@ -449,6 +449,12 @@ struct ForwardSums {
             F.sxy = __builtin_fmaf(tx, dy, F.sxy);
             F.sxz = __builtin_fmaf(tx, dz, F.sxz);
             F.syz = __builtin_fmaf(ty, dz, F.syz);
+        };
+        if (ks == 1) {
+#pragma unroll 2
+            for (int k = 0; k < cnt; ++k) entry(k);
+        } else {
+            for (int k = k0; k < cnt; k += ks) entry(k);
         }
         F.sxx += smf;
         F.syy += smf;
@@ -476,12 +482,18 @@ struct ForwardSums {
         F.zero();
         float sca = 0.f;
         const float4* d = S.tile;
-        for (int k = k0; k < cnt; k += ks) {
+        auto entry = [&](int k) {
             const float4 a0 = d[k], a1 = d[kW + k], a2 = d[2 * kW + k], a3 = d[3 * kW + k], a4 = d[4 * kW + k];
             const float Q[6] = {a1.w, a2.x, a2.y, a2.z, a2.w, a3.x};
             const float Qd[6] = {a3.y, a3.z, a3.w, a4.x, a4.y, a4.z};
             node_interact<kTidal>(a0.x - t.tx, a0.y - t.ty, a0.z - t.tz, a1.x - t.vx, a1.y - t.vy, a1.z - t.vz, a0.w,
                                   Q, Qd, F, sca);
+        };
+        if (ks == 1) {
+#pragma unroll 2
+            for (int k = 0; k < cnt; ++k) entry(k);
+        } else {
+            for (int k = k0; k < cnt; k += ks) entry(k);
         }
         F.sxx += sca;
         F.syy += sca;
