@@ -1522,30 +1522,6 @@ struct MomentSums {
     }
 };
 
-// Reductions over the G lanes of a group (G = 2, 4 or 8, aligned to G,
-// all active) by DPP moves, which stay in the vector unit (no LDS
-// permutes): partners at xor 1 and xor 2 within each quad, then the mirror
-// lane within each eight (lane 7 - i, which is in the other quad).  Every
-// lane ends with the same bits: each step adds two values that are equal on
-// both partners.
-constexpr int kDppXor1 = 0xB1;         // quad_perm [1, 0, 3, 2]
-constexpr int kDppXor2 = 0x4E;         // quad_perm [2, 3, 0, 1]
-constexpr int kDppHalfMirror = 0x141;  // row_half_mirror
-template <int C> __device__ __forceinline__ double dpp_f64(double v) {
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, C, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), C, 0xF, 0xF, false);
-    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
-}
-template <int C> __device__ __forceinline__ float dpp_f32(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), C, 0xF, 0xF, false));
-}
-template <int G> __device__ __forceinline__ double grp_sum(double v) {
-    if (G >= 2) v += dpp_f64<kDppXor1>(v);
-    if (G >= 4) v += dpp_f64<kDppXor2>(v);
-    if (G >= 8) v += dpp_f64<kDppHalfMirror>(v);
-    return v;
-}
 template <int G> __device__ __forceinline__ double grp_min(double v) {
     if (G >= 2) v = fmin(v, dpp_f64<kDppXor1>(v));
     if (G >= 4) v = fmin(v, dpp_f64<kDppXor2>(v));
