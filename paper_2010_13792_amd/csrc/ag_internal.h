@@ -157,6 +157,7 @@ struct ag_ctx {
     DevBuf grp_hdr;               // i32: [0] number of groups, then two walks' eight work-queue counters, kQueueStride apart
     DevBuf grp_cnt;               // i32 [max_nodes]: groups owned per node
     DevBuf grp_tile;              // i32: their totals per tile
+    DevBuf grp_ord, grp_amin;     // i32: the groups in the order they are walked; f32: smallest |a_old| of each
     DevBuf sys_act;               // i32 [n_sys + 1]
     DevBuf wsorted;               // double4 [n]: adjoint weights in sorted order
     DevBuf direct_part;           // direct sum: FP64 per-split sums of a small target set

@@ -26,6 +26,7 @@ def _way(groups, waves_per_cu, team):
 # (what, particles, targets per group, the two ways)
 CASES = [("forward", 150001, 64, {"small teams", "workgroup"}), ("forward", 250007, 12, {"solo", "small teams"}),
          ("soft", 250007, 12, {"solo", "small teams"}), ("relative", 150001, 64, {"small teams", "workgroup"}),
+         ("relative list", 150001, 64, {"small teams", "workgroup"}),
          ("near", 40 ** 3, 64, {"small teams", "workgroup"}),
          ("ewald", 44 ** 3, 64, {"small teams", "workgroup"}), ("ewald", 60 ** 3, 10, {"solo", "small teams"}),
          ("ewald wide", 64 ** 3, 64, {"small teams", "workgroup"}),
@@ -45,6 +46,8 @@ def test_same_bits_by_single_waves_and_teams(ag, what, n, targets, ways):
     idx = None
     if what == "ewald wide":   # few targets in each group's cells: wide groups sum target by target
         idx = _t(workloads.random_subset(n, 0.3, seed=8).astype(np.int32), torch.int32)
+    if what == "relative list":   # teams walk the groups of 40 000 targets or more in an order of their own
+        idx = _t(workloads.random_subset(n, 0.5, seed=9).astype(np.int32), torch.int32)
     got, seen = [], set()
     with ag.Context(0) as c:
         c.set_option(ag.AG_OPT_GROUP_TARGETS, targets)
@@ -53,7 +56,7 @@ def test_same_bits_by_single_waves_and_teams(ag, what, n, targets, ways):
         if per:
             c.set_periodic(1.0, what != "near")
         c.tree_build(tx, tv, tm, 16)
-        if what == "relative":
+        if what.startswith("relative"):
             c.set_relative_opening(0.0025, _t(-x))
         w = _t(rng.normal(size=x.shape))
         for waves in (16, 64):
