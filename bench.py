@@ -65,7 +65,7 @@ WALK_SOURCES = ("paper_2010_13792_amd/csrc/k_walk.hip", "paper_2010_13792_amd/cs
                 "paper_2010_13792_amd/csrc/ag_internal.h")
 # algorithmic bytes of one build: per particle, read x, v, m (56), write them
 # in key order (positions and masses as double4, FP32 velocities and masses:
-# 48), keys and rows (24); per node, link 16, centre 32, box 32, FP32 moments 64 and FP64
+# 48), keys and rows (24); per node, link 16, opening record 64, FP32 moments 64 and FP64
 # moments 200 (344)
 BUILD_BYTES_PER_PARTICLE = 56 + 48 + 24
 BUILD_BYTES_PER_NODE = 344

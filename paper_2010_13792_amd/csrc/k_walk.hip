@@ -4,7 +4,7 @@
 // Work decomposition: the active targets, in key (Morton) order, are cut
 // into groups of at most 64 consecutive targets of one system; one wave64,
 // or a team of waves where groups are few, walks the tree once for the whole
-// group.  Every lane owns
+// group, and waves left without a group take tiles of the others.  Every lane owns
 // one target; in a group of fewer than 64 targets each target is given
 // several lanes, which share out the interaction list and add their parts
 // at the end, so the wave stays full.  The opening test is applied to the group's bounding box
@@ -1480,7 +1480,7 @@ __device__ __forceinline__ void walk_group(typename Pol::Lds* all, HelpLds<W>& H
 // ---- one group walked by a team of waves ----
 // With fewer groups than the device has waves, a walk by single waves lasts as
 // long as its longest group (3000 particles: 70 groups on 1024 SIMDs, 0.74 ms).
-// A team (of 4 to 16 waves) walks one group: its first wave traverses the tree and queues the
+// A team (of 4 waves or the whole workgroup) walks one group: its first wave traverses the tree and queues the
 // full tiles in LDS, the others (and the first when the queue is full or the
 // traversal done) take tiles from the queue, stage and evaluate them, and fold
 // the tile sums into the group's sums in LDS in the order of the queue.  Tiles,
