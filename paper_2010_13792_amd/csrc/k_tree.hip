@@ -1414,7 +1414,7 @@ __device__ __forceinline__ void store_node_g(int64_t id, int s, const double* r,
     const float ox = (float)r[1] - 0.5f * (lo.x + hi.x);
     const float oy = (float)r[2] - 0.5f * (lo.y + hi.y);
     const float oz = (float)r[3] - 0.5f * (lo.z + hi.z);
-    const float len = (float)L, mac = len + sqrtf(ox * ox + oy * oy + oz * oz);
+    const float len = (float)L, mac = len + sqrtf(__builtin_fmaf(oz, oz, __builtin_fmaf(ox, ox, oy * oy)));
     const unsigned long long zbits = (unsigned long long)__double_as_longlong(r[3]);
     const uint4 w[8] = {u4_d2(r[1], r[2]),
                         make_uint4((unsigned)zbits, (unsigned)(zbits >> 32), __float_as_uint(len), __float_as_uint(mac)),

@@ -170,7 +170,9 @@ __device__ __forceinline__ bool mac_accept(const GroupBox& g, const NodeRec& c, 
     const float rx = fmaxf(fabsf((float)cdx) - g.hx, 0.f);
     const float ry = fmaxf(fabsf((float)cdy) - g.hy, 0.f);
     const float rz = fmaxf(fabsf((float)cdz) - g.hz, 0.f);
-    const float r2 = rx * rx + ry * ry + rz * rz;
+    // (the order of these sums is written out: left to the compiler it changes with
+    // the code around it, and a node on the edge of the test with it)
+    const float r2 = __builtin_fmaf(rz, rz, __builtin_fmaf(rx, rx, ry * ry));
     const float L = O.mac_offset ? c.mac : c.len;
     float gx, gy, gz;
     float bx, by, bz;   // box centre offset from the group centre (at its nearest image)
@@ -198,7 +200,7 @@ __device__ __forceinline__ bool mac_accept(const GroupBox& g, const NodeRec& c, 
         gy = fmaxf(by - ey, 0.f);
         gz = fmaxf(bz - ez, 0.f);
     }
-    const float sep2 = gx * gx + gy * gy + gz * gz;
+    const float sep2 = __builtin_fmaf(gz, gz, __builtin_fmaf(gx, gx, gy * gy));
     if (!(r2 > 0.f && L * L <= theta2 * r2 && sep2 >= eps2)) return false;
     if (!O.rel_a) return true;
     // Relative test (Springel 2005) on top of the geometric one: a node of
@@ -216,8 +218,11 @@ __device__ __forceinline__ bool mac_accept(const GroupBox& g, const NodeRec& c, 
         by = fabsf((float)(0.5 * ((double)lo.y + (double)hi.y) - g.cy));
         bz = fabsf((float)(0.5 * ((double)lo.z + (double)hi.z) - g.cz));
     }
-    const float e = 0.6f * Ln;
-    return !(bx < e + g.hx && by < e + g.hy && bz < e + g.hz);
+    {
+#pragma clang fp contract(off)
+        const float e = 0.6f * Ln;
+        return !(bx < __builtin_fmaf(0.6f, Ln, g.hx) && by < e + g.hy && bz < e + g.hz);
+    }
 }
 
 // particle-node interaction at quadrupole order.  d = node centre - target,
