@@ -44,23 +44,23 @@ PEAK_FP32_PACKED_SPEC = 157.3                   # MI355X's published FP32 vector
 PEAK_HBM_GBS = 8000.0
 
 # HBM traffic of the walk kernel at the default workload, from two rocprofv3
-# --pmc passes (FETCH_SIZE, WRITE_SIZE; KiB per dispatch, mean of the 4
+# --pmc passes (FETCH_SIZE, WRITE_SIZE; KiB per dispatch, mean of the 5
 # walk dispatches of a --no-tune run, the configuration named below)
 # scaled by what the same counters read for a plain 1 GiB device copy
 # (FETCH_SIZE 524305 KiB -> x2.0, WRITE_SIZE 1048576 KiB -> x1.0).  Valid only
 # while the walk kernel's sources hash to `src_sha256`; reported as null
 # otherwise, or for another workload.
 WALK_COUNTERS = {
-    "src_sha256": "30ac2560443a8882c15bb3a317bb901a8600b4370058d644dd844c9bc248bb53",
+    "src_sha256": "6345fe3711c5c4d790309e59532916a182d333fd410154eb2449c9a84cb2c731",
     "workload": {"n": 1 << 20, "theta": 0.7, "eps": 1e-3, "n_leaf": 16, "mac_offset": 1, "group_targets": 64,
                  "waves_per_cu": 16, "group_split": 42, "group_pack": 0},
-    "fetch_kib": 349323.4, "write_kib": 222362.8,
+    "fetch_kib": 214446.2, "write_kib": 171078.4,
     "fetch_factor": 1048576.0 / 524304.5, "write_factor": 1.0,
 }
 # FP32 flops the hardware executed in one walk launch at the same workload
 # (SQ_INSTS_VALU_FLOPS_FP32 + _TRANS, per wave instruction, times 64 lanes);
 # they include the repeated work of lanes left over in small groups
-WALK_EXECUTED_FP32_FLOPS = (2494782010.0 + 22164085.0) * 64
+WALK_EXECUTED_FP32_FLOPS = (2475455898.0 + 21293289.0) * 64
 WALK_SOURCES = ("paper_2010_13792_amd/csrc/k_walk.hip", "paper_2010_13792_amd/csrc/pair.h",
                 "paper_2010_13792_amd/csrc/ag_internal.h")
 # algorithmic bytes of one build: per particle, read x, v, m (56), write them
