@@ -496,13 +496,15 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_sort(int n, const doubl
     const int t = threadIdx.x, w = t >> 6, lane = t & 63;
     reduce_box(part, nparts, s_red, s_box);
     const KeyBox B = key_box(s_box, (double)(1u << AG_MAX_LEVEL), pbox);
-    // a wave's own run of kItems x 64 positions
-    const int base = w * kItems * 64;
+    // a wave's own run of positions: as few rows of 64 as n needs (a step of 256
+    // particles 143 us with four rows always, 135 with one)
+    const int rows = (n + kSmallThreads - 1) / kSmallThreads;
+    const int base = w * rows * 64;
     uint64_t key[kItems];
     int val[kItems], rk[kItems];
 #pragma unroll
     for (int k = 0; k < kItems; ++k) {
-        const int i = base + k * 64 + lane;
+        const int i = k < rows ? base + k * 64 + lane : n;
         key[k] = i < n ? morton_key(x + 3 * (int64_t)i, B, ((int64_t)1 << AG_MAX_LEVEL) - 1, pbox) : 0;
         val[k] = i;
     }
@@ -513,6 +515,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_sort(int n, const doubl
         int* cnt_w = s_w[w];
 #pragma unroll
         for (int k = 0; k < kItems; ++k) {
+            if (k >= rows) break;
             const bool valid = base + k * 64 + lane < n;
             const int d = (int)((key[k] >> shift) & 255);
             uint64_t peers = __ballot(valid);
@@ -547,7 +550,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_sort(int n, const doubl
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < kItems; ++k)
-            if (base + k * 64 + lane < n) {
+            if (k < rows && base + k * 64 + lane < n) {
                 const int d = (int)((key[k] >> shift) & 255);
                 const int slot = s_loc[d] + cnt_w[d] + rk[k];
                 s_key[slot] = key[k];
@@ -556,7 +559,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_sort(int n, const doubl
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < kItems; ++k) {
-            const int i = base + k * 64 + lane;
+            const int i = k < rows ? base + k * 64 + lane : n;
             key[k] = i < n ? s_key[i] : 0;
             val[k] = i < n ? s_val[i] : 0;
         }
@@ -564,7 +567,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_sort(int n, const doubl
     }
 #pragma unroll
     for (int k = 0; k < kItems; ++k) {
-        const int i = base + k * 64 + lane;
+        const int i = k < rows ? base + k * 64 + lane : n;
         if (i < n) {
             kout[i] = key[k];
             vout[i] = val[k];

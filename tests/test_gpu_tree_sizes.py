@@ -1,5 +1,5 @@
 """The tree build at the sizes where its kernels change: one workgroup sorts up
-to 4096 particles, the radix sort takes tiles of 1024, 2048 or 4096 and adds up
+to 4096 particles in rows of 1024, the radix sort takes tiles of 1024, 2048 or 4096 and adds up
 few tiles' counts itself, the inner levels run in one launch up to 8192
 particles, and the nodes are counted by tiles of 512, 1024 or 2048 positions.
 The tree is the oct-tree of the same particles on both sides of each edge.  The
@@ -31,7 +31,7 @@ class _Extended:
         return {"M": float(M), "com": f(c), "u": f(u), "Q": f(Q), "Qdot": f(Qd), "lo": f(x.min(0)), "hi": f(x.max(0))}
 
 
-@pytest.mark.parametrize("n", [2, 4096, 4097, 8192, 8193, 65536, 65537, 131073, 262144, 262145, (1 << 19) + 1,
+@pytest.mark.parametrize("n", [2, 1024, 1025, 2049, 4096, 4097, 8192, 8193, 65536, 65537, 131073, 262144, 262145, (1 << 19) + 1,
                                (1 << 21) + 1])
 def test_tree_at_edges(ctx, n):
     print(f"tree n={n}", flush=True)
