@@ -100,15 +100,12 @@ __device__ __forceinline__ void pair_add(R dx, R dy, R dz, R nx, R ny, R nz, R m
     A.az += mf * dz;
     const R dn = dx * nx + dy * ny + dz * nz;
     const R s = mD * dn;
-    if constexpr (sizeof(R) == 8) {   // chains of multiply-adds: one operation less per component
-        A.jx = __builtin_fma(mf, nx, __builtin_fma(s, dx, A.jx));
-        A.jy = __builtin_fma(mf, ny, __builtin_fma(s, dy, A.jy));
-        A.jz = __builtin_fma(mf, nz, __builtin_fma(s, dz, A.jz));
-    } else {
-        A.jx += mf * nx + s * dx;
-        A.jy += mf * ny + s * dy;
-        A.jz += mf * nz + s * dz;
-    }
+    // (each pair's jerk is rounded by itself and added once: as a chain of two
+    // multiply-adds into the sum, one operation less, it would be rounded twice at
+    // the size of the sum)
+    A.jx += mf * nx + s * dx;
+    A.jy += mf * ny + s * dy;
+    A.jz += mf * nz + s * dz;
     const R tx = mD * dx, ty = mD * dy, tz = mD * dz;
     A.smf += mf;
     A.sxx += tx * dx;
