@@ -5,10 +5,10 @@
 // holds all T targets, Gs times over: lane l serves target l mod T in lane
 // group l / T, and the 8 Gs lane groups of the workgroup each sum their own
 // subset of the sources (source q of a staged tile belongs to subset
-// q mod 8 Gs).  Gs (1 .. 16) is the smallest that gives enough workgroups to
+// q mod 8 Gs).  Gs (1 .. 16) gives enough workgroups to
 // fill the chip, so a target set of a few thousand still spreads over every
-// SIMD without any exchange between workgroups.  Sources are staged through
-// LDS 1024 at a time (two coalesced loads per thread); the Gs groups of a
+// SIMD without any exchange between workgroups (which Gs: direct_shape).  Sources are staged
+// through LDS 1024 at a time (two coalesced loads per thread); the Gs groups of a
 // wave read Gs neighbouring sources at once (broadcasts within each group).
 // FP64 runs one workgroup per CU with up to 256 registers and takes kChains
 // sources per lane at a time (independent dependency chains); FP32 pairs
@@ -416,18 +416,23 @@ __global__ void __launch_bounds__(256) k_direct_splits(DirectArgs P, int64_t til
 // split as well (grid.y), so that tiles x splits stays below 2 blocks.  Each
 // split covers a multiple of the 8 Gs subsets.
 // FP64 goes on to more lane groups where that leaves less of the last round
-// of workgroups empty: a round takes the time of the targets per workgroup T
-// plus about 10^4 / n targets for its start and its final sums.
-// (20 000 particles: 313 workgroups of 64 targets are two rounds, the second
-// a quarter full, 1.09 ms; 1250 of 16 are five, 0.76 ms; 9000: 0.27 and
-// 0.21 ms, 40 000: 3.43 and 2.80.  FP32 pairs keep the
-// first shape, on which the rounding of their sums depends.)
+// of workgroups empty.  A round takes the time of the targets per workgroup T, of
+// about 2.5 targets more for staging the sources (every workgroup stages all
+// of them; 2 with softening lengths or in a periodic cube, whose pairs take
+// longer), and of 10^4 / n for its start and its final sums (300 000 targets: 8.6,
+// 4.5, 2.4, 1.36 and 0.88 ms a round at T = 64 .. 4).  The first shape stays where
+// the gain would be below 1 %, which the estimate cannot tell.
+// Measured at T = 64, 32, 16, 8 and 4 (ms, the one taken in brackets): 9000
+// particles -, 0.262, 0.214, [0.209], 0.250; 20 000 1.09, 0.86, [0.79], 0.89,
+// 1.13; 30 000 [1.65], 1.72, 1.87, 1.98, 2.50; 50 000 5.98, [5.31], 5.18, 5.46,
+// 6.66; 100 000 21.4, [19.8], 20.1, 22.3, 29.1; 300 000 [164], 166, 178, 200, 258.
+// FP32 pairs keep the first shape, on which the rounding of their sums depends.
 constexpr int64_t kBlocks64 = 256;
 constexpr int64_t kBlocks32 = 512;
 constexpr int64_t kDirectBlocks = kBlocks64 > kBlocks32 ? kBlocks64 : kBlocks32;   // bounds the split scratch
 
-void ag_direct_shape(int64_t n, int64_t n_act, int precision, int* tshift, int64_t* tiles, int64_t* nsplit,
-                     int64_t* chunk) {
+static void direct_shape(int64_t n, int64_t n_act, int precision, bool plain, int* tshift, int64_t* tiles,
+                         int64_t* nsplit, int64_t* chunk) {
     const int64_t blocks = precision == AG_FP64 ? kBlocks64 : kBlocks32;
     int ts = 6;
     int64_t t = (n_act + 63) >> 6;
@@ -436,15 +441,15 @@ void ag_direct_shape(int64_t n, int64_t n_act, int precision, int* tshift, int64
         t = (n_act + (1 << ts) - 1) >> ts;
     }
     if (precision == AG_FP64 && t >= blocks) {
-        const double start = 1e4 / (double)n;
+        const double extra = (plain ? 2.5 : 2.0) + 1e4 / (double)n;
         auto cost = [&](int k) {
             const int64_t rounds = (((n_act + (1 << k) - 1) >> k) + blocks - 1) / blocks;
-            return (double)rounds * ((double)(1 << k) + start);
+            return (double)rounds * ((double)(1 << k) + extra);
         };
         int best = ts;
         for (int k = ts - 1; k >= kMinTShift; --k)
             if (cost(k) < cost(best)) best = k;
-        ts = best;
+        if (cost(best) < 0.99 * cost(ts)) ts = best;
         t = (n_act + (1 << ts) - 1) >> ts;
     }
     const int64_t nsub = (int64_t)kWaves * (64 >> ts);
@@ -467,7 +472,7 @@ void ag_direct_shape(int64_t n, int64_t n_act, int precision, int* tshift, int64
 size_t ag_direct_scratch_bytes(int64_t n, int64_t n_act, int precision) {
     int ts;
     int64_t t, s, c;
-    ag_direct_shape(n, n_act, precision, &ts, &t, &s, &c);
+    direct_shape(n, n_act, precision, true, &ts, &t, &s, &c);   // (whole sums, plain or not, are never split)
     if (s <= 1) return 0;
     return (size_t)t * s * kParts * ((size_t)1 << ts) * sizeof(double);
 }
@@ -477,7 +482,8 @@ int ag_launch_direct(ag_ctx* c, int64_t n, const double* x, const double* v, con
                      double* acc, double* jerk, double* tidal, void* scratch, bool timed) {
     int tshift;
     int64_t tiles, nsplit, chunk;
-    ag_direct_shape(n, n_act, precision, &tshift, &tiles, &nsplit, &chunk);
+    const bool plain = c->soft_n == 0 && c->box <= 0.0;
+    direct_shape(n, n_act, precision, plain, &tshift, &tiles, &nsplit, &chunk);
     DirectArgs P{};
     P.n = n;
     P.x = x;
