@@ -243,6 +243,14 @@ int ag_launch_predict_poly(ag_ctx* c, int64_t n, const uint8_t* mask, int32_t de
 int ag_launch_build(ag_ctx* c, int64_t n, const double* x, const double* v, const double* m,
                     int32_t n_sys, const int64_t* sys_offsets, int32_t n_leaf);
 int ag_launch_refit(ag_ctx* c, const double* x, const double* v, const double* m);
+// Of more tiles than this the totals are summed by a launch between the two
+// passes: read by every tile their number grows with its square (due rows of
+// 2^24 particles, 8192 tiles, 82 us, of 2^26 587, four times as many being 327).
+constexpr int64_t kTilesRead = 8192;
+// exclusive sums, in place, of the totals of `tiles` tiles (`words` interleaved
+// numbers each); with n_dev set there are as many tiles of `tile` as *n_dev
+// items take, and up to kTilesRead of them stay as they are
+void ag_tile_scan(ag_ctx* c, int32_t* tile_sum, int words, int64_t tiles, const int64_t* n_dev = nullptr, int tile = 1);
 int ag_launch_eval(ag_ctx* c, const int32_t* idx, int64_t n_act, double theta, double eps,
                    double G, double* acc, double* jerk, double* tidal, const int64_t* n_dev = nullptr,
                    int64_t* n_total = nullptr);
@@ -407,8 +415,11 @@ __device__ __forceinline__ int ag_block_scan256(int v, int* s_tmp, int* total) {
 
 // sum of the totals of the tiles before this one (256 threads, all of them
 // read together): the scans here are a pass that writes each tile's total and
-// one that adds up the totals before its own, with no launch between them
-__device__ __forceinline__ int ag_tiles_before256(const int32_t* __restrict__ tile_sum, int tile, int* s_tmp) {
+// one that adds up the totals before its own, with no launch between them.
+// With `scanned` set ag_tile_scan has left the sums where the totals were.
+__device__ __forceinline__ int ag_tiles_before256(const int32_t* __restrict__ tile_sum, int tile, bool scanned,
+                                                  int* s_tmp) {
+    if (scanned) return tile_sum[tile];
     int v = 0, total;
     for (int t = threadIdx.x; t < tile; t += 256) v += tile_sum[t];
     ag_block_scan256(v, s_tmp, &total);

@@ -1,7 +1,7 @@
 // k_step.hip -- per-particle kernels of the adaptive scheme: the tidal
 // timestep and its block bin (Eq. 7), the force-age counter and update test
 // (Eq. 3, Eq. 4) with stream compaction, and the jerk predictor (Eq. 6);
-// plus the device-wide exclusive scan used across the library.
+// plus the scan of many tiles' totals used across the library.
 //
 // This file is compiled with -ffp-contract=off: the bin decision and the
 // predictor are defined operation by operation (each rounded once), so the
@@ -108,11 +108,11 @@ __global__ void __launch_bounds__(kThreads) k_select(int64_t n, int64_t* __restr
 }
 
 __global__ void __launch_bounds__(kThreads) k_compact(int64_t n, const int32_t* __restrict__ flag,
-                                                      const int32_t* __restrict__ tile_sum,
+                                                      const int32_t* __restrict__ tile_sum, bool scanned,
                                                       int32_t* __restrict__ out, int64_t* __restrict__ count,
                                                       double* __restrict__ t0, double t) {
     __shared__ int s_tmp[kThreads / 64];
-    int run = ag_tiles_before256(tile_sum, (int)blockIdx.x, s_tmp);
+    int run = ag_tiles_before256(tile_sum, (int)blockIdx.x, scanned, s_tmp);
     for (int r = 0; r < kSelTile / kThreads; ++r) {
         const int64_t i = (int64_t)blockIdx.x * kSelTile + r * kThreads + threadIdx.x;
         const int f = i < n ? flag[i] : 0;
@@ -257,7 +257,54 @@ __global__ void k_predict_poly(int64_t n, const uint8_t* __restrict__ mask, int 
     }
 }
 
+// ---------------------------------------------------------------------------
+// exclusive sums of the totals of many tiles, in place (ag_tile_scan)
+// ---------------------------------------------------------------------------
+// One workgroup per interleaved word, which carries its sum from one run of
+// kScanThreads * kScanItems totals to the next.
+constexpr int kScanThreads = 1024;
+constexpr int kScanItems = 8;
+__global__ void __launch_bounds__(kScanThreads) k_tile_scan(int32_t* __restrict__ sums, int words, int64_t tiles,
+                                                            const int64_t* __restrict__ n_dev, int tile) {
+    __shared__ int s_w[kScanThreads / 64];
+    if (n_dev) {
+        tiles = (*n_dev + tile - 1) / tile;
+        if (tiles <= kTilesRead) return;
+    }
+    const int w = threadIdx.x >> 6;
+    int32_t* s = sums + blockIdx.x;
+    int carry = 0;
+    for (int64_t b = 0; b < tiles; b += kScanThreads * kScanItems) {
+        const int64_t i0 = b + (int64_t)threadIdx.x * kScanItems;
+        int v[kScanItems], sum = 0;
+#pragma unroll
+        for (int k = 0; k < kScanItems; ++k) v[k] = i0 + k < tiles ? s[(i0 + k) * words] : 0;
+#pragma unroll
+        for (int k = 0; k < kScanItems; ++k) sum += v[k];
+        const int incl = ag_wave_incl_scan(sum);
+        if (ag_lane() == 63) s_w[w] = incl;
+        __syncthreads();
+        int run = carry + incl - sum;
+        for (int q = 0; q < kScanThreads / 64; ++q) {
+            const int t = s_w[q];
+            run += q < w ? t : 0;
+            carry += t;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kScanItems; ++k) {
+            if (i0 + k < tiles) s[(i0 + k) * words] = run;
+            run += v[k];
+        }
+    }
+}
+
 }  // namespace
+
+void ag_tile_scan(ag_ctx* c, int32_t* tile_sum, int words, int64_t tiles, const int64_t* n_dev, int tile) {
+    hipLaunchKernelGGL(k_tile_scan, dim3((unsigned)words), dim3(kScanThreads), 0, c->stream, tile_sum, words, tiles,
+                       n_dev, tile);
+}
 
 int ag_launch_timestep(ag_ctx* c, int64_t n, const int32_t* idx, int64_t n_idx, const double* tidal,
                        double eta, double dt_max, int32_t k_max, double* dt, int8_t* bin, const int64_t* n_dev) {
@@ -302,7 +349,9 @@ int ag_launch_select(ag_ctx* c, int64_t n, int64_t* tf, const int8_t* bin, int64
     int32_t* sum = c->sel_tile.as<int32_t>();
     hipLaunchKernelGGL(k_select, dim3((unsigned)tiles), dim3(kThreads), 0, c->stream, n, tf, bin, step_ticks,
                        (int)tick_bin, q_f, flag, sum);
-    hipLaunchKernelGGL(k_compact, dim3((unsigned)tiles), dim3(kThreads), 0, c->stream, n, flag, sum, active_idx,
+    const bool scan = tiles > kTilesRead;
+    if (scan) ag_tile_scan(c, sum, 1, tiles);
+    hipLaunchKernelGGL(k_compact, dim3((unsigned)tiles), dim3(kThreads), 0, c->stream, n, flag, sum, scan, active_idx,
                        n_active_dev, t0, t);
     return AG_OK;
 }

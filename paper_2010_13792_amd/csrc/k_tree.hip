@@ -833,21 +833,28 @@ __global__ void __launch_bounds__(kThreads) k_count_nodes(TopoParams P, const in
 }
 
 // Exclusive scans of both counts: every tile adds up the totals of the tiles
-// before it (read together; no scan launch of their own) and scans its own.
+// before it (read together; a scan launch of their own only where they are
+// many) and scans its own.
 __global__ void __launch_bounds__(kThreads) k_node_offsets(int64_t n, int tile, const int32_t* __restrict__ cnt,
                                                            const int32_t* __restrict__ icnt,
-                                                           const int2* __restrict__ tile_sum,
+                                                           const int2* __restrict__ tile_sum, bool scanned,
                                                            int32_t* __restrict__ off, int32_t* __restrict__ ioff) {
     __shared__ int s_tmp[kThreads / 64];
-    int a = 0, b = 0;
-    for (int t = threadIdx.x; t < (int)blockIdx.x; t += kThreads) {
-        const int2 v = tile_sum[t];
-        a += v.x;
-        b += v.y;
-    }
     int run, irun;
-    ag_block_scan256(a, s_tmp, &run);
-    ag_block_scan256(b, s_tmp, &irun);
+    if (scanned) {
+        const int2 v = tile_sum[blockIdx.x];
+        run = v.x;
+        irun = v.y;
+    } else {
+        int a = 0, b = 0;
+        for (int t = threadIdx.x; t < (int)blockIdx.x; t += kThreads) {
+            const int2 v = tile_sum[t];
+            a += v.x;
+            b += v.y;
+        }
+        ag_block_scan256(a, s_tmp, &run);
+        ag_block_scan256(b, s_tmp, &irun);
+    }
     const int64_t p1 = ((int64_t)blockIdx.x + 1) * tile < n ? ((int64_t)blockIdx.x + 1) * tile : n;
     for (int64_t p0 = (int64_t)blockIdx.x * tile; p0 < p1; p0 += 2 * kThreads) {
         const int64_t p = p0 + 2 * threadIdx.x;   // tiles are multiples of 512: p is even
@@ -1971,8 +1978,10 @@ int ag_launch_build(ag_ctx* c, int64_t n, const double* x, const double* v, cons
     int2* tsum = c->scan_tmp.as<int2>();
     hipLaunchKernelGGL(k_count_nodes, dim3((unsigned)(ntile + 1)), dim3(kThreads), 0, st, P, cd, ctile, pcnt, icnt,
                        tsum, M, C);
-    hipLaunchKernelGGL(k_node_offsets, dim3((unsigned)ntile), dim3(kThreads), 0, st, n, ctile, pcnt, icnt, tsum, poff,
-                       ioff);
+    const bool scan = ntile > kTilesRead;
+    if (scan) ag_tile_scan(c, c->scan_tmp.as<int32_t>(), 2, ntile);
+    hipLaunchKernelGGL(k_node_offsets, dim3((unsigned)ntile), dim3(kThreads), 0, st, n, ctile, pcnt, icnt, tsum, scan,
+                       poff, ioff);
     // (the node counts are free after their scans: they hold the list of far
     // ends; the sort's histograms hold the per-workgroup rows)
     int32_t* blk_rows = c->sort_hist.as<int32_t>();

@@ -1976,10 +1976,11 @@ __global__ void __launch_bounds__(256) k_mark_flag(int64_t n_act, const int64_t*
 // offsets of the active positions (n + 1 of them) and their list
 __global__ void __launch_bounds__(256) k_mark_list(int64_t n_act, const int64_t* __restrict__ n_dev, int64_t n,
                                                    const int32_t* __restrict__ flag,
-                                                   const int32_t* __restrict__ tile_sum, int32_t* __restrict__ off,
-                                                   int32_t* __restrict__ out, int32_t* __restrict__ flags) {
+                                                   const int32_t* __restrict__ tile_sum, bool scanned,
+                                                   int32_t* __restrict__ off, int32_t* __restrict__ out,
+                                                   int32_t* __restrict__ flags) {
     __shared__ int s_tmp[4];
-    int run = ag_tiles_before256(tile_sum, (int)blockIdx.x, s_tmp);
+    int run = ag_tiles_before256(tile_sum, (int)blockIdx.x, scanned, s_tmp);
     for (int r = 0; r < kMarkTile / 256; ++r) {
         const int64_t p = (int64_t)blockIdx.x * kMarkTile + r * 256 + threadIdx.x;
         const int f = p < n ? flag[p] : 0;
@@ -2133,15 +2134,16 @@ __global__ void __launch_bounds__(256) k_group_count(GroupCtx C, const int64_t* 
 // The groups in node order, their number, and the walks' work queues reset.
 __global__ void __launch_bounds__(256) k_group_emit(GroupCtx C, const int64_t* __restrict__ hdr,
                                                     const int32_t* __restrict__ gcnt,
-                                                    const int32_t* __restrict__ tile_sum, int4* __restrict__ grp,
-                                                    int32_t* __restrict__ ord, int32_t* __restrict__ ghdr,
+                                                    const int32_t* __restrict__ tile_sum, bool scan,
+                                                    int4* __restrict__ grp, int32_t* __restrict__ ord, int32_t* __restrict__ ghdr,
                                                     int* __restrict__ qctr) {
     __shared__ int s_tmp[4];
     const int64_t nn = hdr[0];
+    const bool scanned = scan && (nn + kGroupTile - 1) / kGroupTile > kTilesRead;
     if (blockIdx.x == 0 && threadIdx.x < 2 * 8) qctr[threadIdx.x * kQueueStride] = 0;   // two walks' queues
     for (int64_t t = blockIdx.x; t * kGroupTile < nn; t += gridDim.x) {
         const int64_t id = t * kGroupTile + threadIdx.x;
-        const int before = ag_tiles_before256(tile_sum, (int)t, s_tmp);
+        const int before = ag_tiles_before256(tile_sum, (int)t, scanned, s_tmp);
         const int g = id < nn ? gcnt[id] : 0;
         int tot;
         const int e = before + ag_block_scan256(g, s_tmp, &tot);
@@ -2241,8 +2243,10 @@ int ag_prepare_groups(ag_ctx* c, const int32_t* idx, int64_t n_act, int64_t* max
                            c->rank.as<int32_t>(), stamp, flags, n_total);
         hipLaunchKernelGGL(k_mark_flag, dim3((unsigned)mtiles), dim3(256), 0, st, n_act, n_dev, idx, n,
                            c->perm.as<int32_t>(), stamp, flag, msum);
-        hipLaunchKernelGGL(k_mark_list, dim3((unsigned)mtiles), dim3(256), 0, st, n_act, n_dev, n, flag, msum, off,
-                           c->act_pos.as<int32_t>(), flags);
+        const bool scan = mtiles > kTilesRead;
+        if (scan) ag_tile_scan(c, msum, 1, mtiles);
+        hipLaunchKernelGGL(k_mark_list, dim3((unsigned)mtiles), dim3(256), 0, st, n_act, n_dev, n, flag, msum, scan,
+                           off, c->act_pos.as<int32_t>(), flags);
     }
     // with every particle active the flags, their scan and the position list
     // are the identity: the grouping and the walk use sorted positions directly
@@ -2254,7 +2258,11 @@ int ag_prepare_groups(ag_ctx* c, const int32_t* idx, int64_t n_act, int64_t* max
     int32_t* ghdr = c->grp_hdr.as<int32_t>();
     const unsigned gblocks = (unsigned)std::min<int64_t>(gtiles, 4096);
     hipLaunchKernelGGL(k_group_count, dim3(gblocks), dim3(256), 0, st, C, hdr, gcnt, gsum);
-    hipLaunchKernelGGL(k_group_emit, dim3(gblocks), dim3(256), 0, st, C, hdr, gcnt, gsum,
+    // (a tree has far fewer nodes than there is room for: of 2^22 particles a
+    // million, 4000 tiles, with room for nine)
+    const bool scan = gtiles > 4 * kTilesRead;
+    if (scan) ag_tile_scan(c, gsum, 1, gtiles, hdr, kGroupTile);
+    hipLaunchKernelGGL(k_group_emit, dim3(gblocks), dim3(256), 0, st, C, hdr, gcnt, gsum, scan,
                        c->grp.as<int4>(), c->grp_ord.as<int32_t>(), ghdr, ghdr + kQueueStride);
     *max_groups = mg;
     return AG_OK;
