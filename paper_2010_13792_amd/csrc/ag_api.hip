@@ -140,6 +140,7 @@ int read_flags(ag_ctx* c) {
         AG_HIP(hipStreamSynchronize(c->stream));
         if (f & AGF_NONFINITE) return ag_fail(AG_ENONFINITE, "non-finite particle position in tree build");
         if (f & AGF_INTERNAL) return ag_fail(AG_EHIP, "internal consistency check failed in a tree kernel");
+        if (f & AGF_PMOPEN) return ag_fail(AG_EHIP, "Price & Monaghan lengths did not settle");
         return ag_fail(AG_EDEVICE, "index list held an out-of-range or repeated entry");
     }
     return AG_OK;

@@ -38,7 +38,7 @@ struct DevBuf {
 };
 
 // device-side flag bits (ag_ctx::dflags)
-enum { AGF_BADINDEX = 1, AGF_NONFINITE = 2, AGF_INTERNAL = 4 };
+enum { AGF_BADINDEX = 1, AGF_NONFINITE = 2, AGF_INTERNAL = 4, AGF_PMOPEN = 8 };
 
 constexpr int AG_MAX_LEVEL = 21;   // Morton digits: 21 x 3 bits = 63-bit keys
 constexpr int AG_MAX_SYS = 512;    // batched systems: 3 octal digits of prefix

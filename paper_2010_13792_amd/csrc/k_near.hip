@@ -471,9 +471,12 @@ __device__ __forceinline__ void find_lengths(NearLds& S, const NearArgs& A, cons
 // h with S(h) = 1 + sum_j w(r_j / h) = 3 N / 32 (self counted as 1), by
 // pm_newton; Omega = -(32 / (9 N)) sum_j u_j w'(u_j) at h.
 
-// Solves for the n distances at L in the bracket [0, hi]; returns false if
-// S(hi) falls short.  sd: the sum of u w'(u) at the solution.
-__device__ __forceinline__ bool solve_list(const double* L, int n, int lane, double target, double hi, double& h,
+// Solves for the n distances at L in the bracket [0, hi].  kShort: S(hi) falls
+// short.  kOpenRoot: no step settled, as where so many particles coincide that S
+// passes the target at every h; h is then the smallest length known to pass.
+// sd: the sum of u w'(u) at the solution.
+enum { kShort, kSolved, kOpenRoot };
+__device__ __forceinline__ int solve_list(const double* L, int n, int lane, double target, double hi, double& h,
                                            double& sd) {
     auto sums = [&](double hh) {
         const double hinv = 1.0 / hh;
@@ -490,7 +493,7 @@ __device__ __forceinline__ bool solve_list(const double* L, int n, int lane, dou
     };
     const double shi = sums(hi);
     h = hi;
-    if (!(shi >= target)) return false;
+    if (!(shi >= target)) return kShort;
     double lo = 0.0;
     // start where S would meet the target if the neighbours filled the ball
     // uniformly (S - 1 growing as h^3)
@@ -498,10 +501,11 @@ __device__ __forceinline__ bool solve_list(const double* L, int n, int lane, dou
     for (int it = 0; it < 200; ++it) {
         const double s = sums(h);
         double hn;
-        if (!pm_newton(s, sd, target, h, lo, hi, hn)) break;
+        if (!pm_newton(s, sd, target, h, lo, hi, hn)) return kSolved;
         h = hn;
     }
-    return true;
+    h = hi;
+    return kOpenRoot;
 }
 
 // The targets' distances below R (or, all: any distance) into lists of `cap`,
@@ -536,7 +540,7 @@ __device__ __forceinline__ void density_pass(NearLds& S, const NearArgs& A, cons
             if (n + __popcll(m) > cap) {
                 double hs, ds;
                 const double hi = all && !(rj < DBL_MAX) ? A.hiscale * diag : rj;
-                if (!solve_list(L, n, lane, target, hi, hs, ds)) hs = hi;
+                if (solve_list(L, n, lane, target, hi, hs, ds) == kShort) hs = hi;
                 hs = fmin(rj, hs * (1.0 + 1e-12));
                 int kept = 0;
                 for (int e = 0; e < n; e += kW) {
@@ -567,11 +571,13 @@ __device__ __forceinline__ void density_pass(NearLds& S, const NearArgs& A, cons
         // (every particle a candidate: any length may be taken)
         const double rj = lane_f64(D.rmax, j), hi = all && !(rj < DBL_MAX) ? A.hiscale * diag : rj;
         double hj, ds;
-        const bool ok = solve_list(S.r + j * cap, __builtin_amdgcn_readlane(D.cnt, j), lane, target, hi, hj, ds);
+        const int how = solve_list(S.r + j * cap, __builtin_amdgcn_readlane(D.cnt, j), lane, target, hi, hj, ds);
         if (lane == j) {
             D.h = hj;
             D.sd = ds;
-            D.done = ok || all;
+            D.done = how != kShort || all;
+            // (with every particle listed the sum does not fall short)
+            if (how == kOpenRoot || (how == kShort && all)) atomicOr(A.flags, AGF_PMOPEN);
         }
     }
 }
@@ -631,7 +637,7 @@ __device__ __forceinline__ void solve_density(NearLds& S, const NearArgs& A, con
                 moving = pm_newton(1.0 + ag_wave_sum_f64(a), sd, target, hc, lo, hi, hn);
                 hc = hn;
                 if (it == 400 && moving) {
-                    if (lane == 0) atomicOr(A.flags, AGF_INTERNAL);
+                    if (lane == 0) atomicOr(A.flags, AGF_PMOPEN);
                     moving = false;
                 }
             }
