@@ -29,6 +29,7 @@ constexpr int kWords = 1024;            // 8-byte words of the targets' lists (1
 constexpr int kMaxRun = 16;             // targets of a run at most
 constexpr int kDenList = 128;           // list of one target in the density solve: 64 kept, 64 new
 constexpr int kSumList = 128;           // ... in the sums
+constexpr int kWalkRun = 8;             // targets of a run that take their Newton steps together
 
 struct NearArgs {
     const int4* __restrict__ link;
@@ -60,7 +61,7 @@ struct NearArgs {
     bool add;                    // correction: added to acc (else written)
 };
 
-enum { kLengths, kDensity, kFactors, kCorrect };
+enum { kLengths, kDensity, kDensityWalk, kFactors, kCorrect };
 
 struct NearLds {
     int stack[kSCap];
@@ -582,13 +583,60 @@ __device__ __forceinline__ void density_pass(NearLds& S, const NearArgs& A, cons
     }
 }
 
+// Newton steps of the run's targets (M at most) together, from the lanes' h on, a
+// traversal each: every lane adds its particles' terms for each target that still
+// moves.
+template <int M>
+__device__ __forceinline__ void walk_density(NearLds& S, const NearArgs& A, const Run& t, const NearBox& gb, int root,
+                                             double diag, double& h, double& sd) {
+    const int lane = t.lane;
+    const double target = 3.0 * A.ngb / 32.0;
+    double lo = 0.0, hi = A.hiscale * diag, hn = h;
+    bool moving = lane < t.n;
+    for (int it = 0; __ballot(moving) != 0; ++it) {
+        h = hn;
+        const double h2 = moving ? h * h : 0.0, hinv = 1.0 / h;
+        double a[M], b[M];
+#pragma unroll
+        for (int j = 0; j < M; ++j) a[j] = b[j] = 0.0;
+        each_near<false, false>(S, A, gb, ag_wave_max_f64(h2), root, lane, [&](int pk, const double4& p, bool valid) {
+#pragma unroll
+            for (int j = 0; j < M; ++j) {
+                const double hj2 = lane_f64(h2, j);
+                if (!(hj2 > 0.0)) continue;   // settled, or no target
+                const int tp = __builtin_amdgcn_readlane(t.p, j);
+                const double r2 = dist2<false>(p, lane_f64(t.x, j), lane_f64(t.y, j), lane_f64(t.z, j), 0.0);
+                if (valid && pk != tp && r2 < hj2) {
+                    const double u = sqrt(r2) * lane_f64(hinv, j);
+                    a[j] += m4_w(u);
+                    b[j] += u * m4_wp(u);
+                }
+            }
+        });
+        double s = 0.0, sn = 0.0;
+#pragma unroll
+        for (int j = 0; j < M; ++j) {
+            const double sa = ag_wave_sum_f64(a[j]), sb = ag_wave_sum_f64(b[j]);
+            s = lane == j ? 1.0 + sa : s;
+            sn = lane == j ? sb : sn;
+        }
+        if (moving) {
+            sd = sn;
+            moving = pm_newton(s, sd, target, h, lo, hi, hn);
+            if (moving && it == 400) {
+                atomicOr(A.flags, AGF_PMOPEN);
+                moving = false;
+            }
+        }
+    }
+}
+
 // Every target of the run in lists of 128; those that need more, one by one in
 // a list of all the words; those that need more than that take Newton steps
 // with a traversal each.
 __device__ __forceinline__ void solve_density(NearLds& S, const NearArgs& A, const Run& t, const NearBox& gb,
-                                              int root, double diag, double R) {
+                                              int root, double diag, double R, double& h_out, double& sd_out) {
     const int lane = t.lane;
-    const double target = 3.0 * A.ngb / 32.0;
     Density D;
     D.h = D.sd = 0.0;
     D.done = lane >= t.n;
@@ -619,38 +667,18 @@ __device__ __forceinline__ void solve_density(NearLds& S, const NearArgs& A, con
         }
         double h = lane_f64(E.h, 0), sd = lane_f64(E.sd, 0);
         if (__builtin_amdgcn_readlane((int)E.longer, 0)) {
-            double lo = 0.0, hi = A.hiscale * diag, hc = lane_f64(E.rmax, 0);
-            bool moving = true;
-            for (int it = 0; moving; ++it) {
-                double a = 0.0, b = 0.0;
-                each_near<false, false>(S, A, ob, hc * hc, root, lane, [&](int pk, const double4& p, bool valid) {
-                    const double r2 = dist2<false>(p, o.x, o.y, o.z, 0.0);
-                    if (valid && pk != o.p && r2 < hc * hc) {
-                        const double u = sqrt(r2) / hc;
-                        a += m4_w(u);
-                        b += u * m4_wp(u);
-                    }
-                });
-                h = hc;
-                sd = ag_wave_sum_f64(b);
-                double hn;
-                moving = pm_newton(1.0 + ag_wave_sum_f64(a), sd, target, hc, lo, hi, hn);
-                hc = hn;
-                if (it == 400 && moving) {
-                    if (lane == 0) atomicOr(A.flags, AGF_PMOPEN);
-                    moving = false;
-                }
-            }
+            double hw = lane_f64(E.rmax, 0), sw = 0.0;
+            walk_density<1>(S, A, o, ob, root, diag, hw, sw);
+            h = lane_f64(hw, 0);
+            sd = lane_f64(sw, 0);
         }
         if (lane == j) {
             D.h = h;
             D.sd = sd;
         }
     }
-    if (lane < t.n) {
-        A.out[t.row] = D.h;
-        A.omega[t.row] = -(32.0 / (9.0 * A.ngb)) * D.sd;
-    }
+    h_out = D.h;
+    sd_out = D.sd;
 }
 
 // ---- Price & Monaghan sums over the pairs inside a kernel support ----
@@ -779,8 +807,17 @@ __global__ void __launch_bounds__(kW, 4) k_near(NearArgs A, int run, int cuts) {
             const double diag = fmax(1.001 * sqrt(ex * ex + ey * ey + ez * ez), DBL_MIN);
             // (every particle is a target: positions are slots)
             const double R = first_radius<kPer>(A, first, t.n, lane, kMode == kLengths ? (double)A.k : A.ngb, diag);
-            if constexpr (kMode == kLengths) find_lengths<kPer>(S, A, t, gb, root, diag, R);
-            else solve_density(S, A, t, gb, root, diag, R);
+            if constexpr (kMode == kLengths) {
+                find_lengths<kPer>(S, A, t, gb, root, diag, R);
+            } else {
+                double h = R / 1.25, sd = 0.0;
+                if constexpr (kMode == kDensity) solve_density(S, A, t, gb, root, diag, R, h, sd);
+                else walk_density<kWalkRun>(S, A, t, gb, root, diag, h, sd);
+                if (lane < t.n) {
+                    A.out[t.row] = h;
+                    A.omega[t.row] = -(32.0 / (9.0 * A.ngb)) * sd;
+                }
+            }
         }
         wave_sync();
     }
@@ -862,7 +899,16 @@ int ag_launch_pm_lengths(ag_ctx* c, double n_ngb, double* h, double* omega) {
     // 1 - 6 u^2 for u < 1/2)
     const double f = 3.0 * n_ngb / 32.0 / (double)c->n;
     A.hiscale = 1.01 / fmin(0.5, sqrt((1.0 - f) / 6.0));
-    launch_near<kDensity, false>(c, A, mg, c->n, kWords / kDenList);
+    // Supports that the lists of 128 do not hold go one target at a time through a
+    // list of 1024, which is cut again and again where its first radius took in
+    // too much; Newton steps of eight targets together read them as often as there
+    // are steps but keep nothing (ms, lists and steps; n = 100 000, uniform and
+    // Plummer: n_ngb 100 1.76, 1.73 and 45, 14.6; 400 6.6, 3.8 and 143, 56; 2000 47,
+    // 11.8 and 299, 86).  A small set waits for its longest run, which is longer of
+    // eight targets than of one (5000 in clumps: 200 0.42, 0.56; 400 0.86, 0.77).
+    const double lists = c->n > 16384 ? 128.0 : 256.0;
+    if (n_ngb > lists) launch_near<kDensityWalk, false>(c, A, mg, c->n, kWalkRun);
+    else launch_near<kDensity, false>(c, A, mg, c->n, kWords / kDenList);
     return AG_OK;
 }
 
