@@ -154,7 +154,7 @@ struct ag_ctx {
     DevBuf soft_s;                // f32 the same in key order (rounded up)
     DevBuf rel_a;                 // f32 |a| of the previous evaluation, input order (rounded down)
     DevBuf ewald_tab;             // f32 Ewald correction table (5 float4 per point)
-    DevBuf grp_hdr;               // i32: [0] number of groups, then two walks' eight work-queue counters, kQueueStride apart
+    DevBuf grp_hdr;               // i32: [0] number of groups, [1] as the team rule counts them, then two walks' eight work-queue counters, kQueueStride apart
     DevBuf grp_cnt;               // i32 [max_nodes]: groups owned per node
     DevBuf grp_tile;              // i32: their totals per tile
     DevBuf grp_ord, grp_amin;     // i32: the groups in the order they are walked; f32: smallest |a_old| of each

@@ -25,6 +25,7 @@
 #include <float.h>
 
 #include <algorithm>
+#include <climits>
 
 #include "ag_internal.h"
 #include "pair.h"
@@ -73,7 +74,7 @@ struct Tree {
 struct Groups {
     const int32_t* __restrict__ act_pos;
     const int4* __restrict__ grp;      // start, count, system
-    const int32_t* __restrict__ hdr;   // [0] = number of groups
+    const int32_t* __restrict__ hdr;   // [0] = number of groups, [1] = targets in them
     const int32_t* __restrict__ ord;   // the order in which teams of kMinTeam walk them (open boundaries)
 };
 
@@ -1731,7 +1732,8 @@ __global__ void __launch_bounds__(W * kW, Pol::kWaves) k_walk_team(Tree T, Group
     constexpr size_t kBytes = W * sizeof(Solo) > kTeamBytes ? W * sizeof(Solo) : kTeamBytes;
     __shared__ __align__(16) char s_mem[kBytes];   // one or the other, never both
     __shared__ HelpLds<W> s_help;
-    const int n_groups = Gr.hdr[0];
+    const int2 hdr = *reinterpret_cast<const int2*>(Gr.hdr);   // (one load: the next would wait as long again)
+    const int n_groups = hdr.x;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     int q = 0;
     WalkCount C;
@@ -1750,7 +1752,7 @@ __global__ void __launch_bounds__(W * kW, Pol::kWaves) k_walk_team(Tree T, Group
         }
         if constexpr (can_help<Pol>()) help<Pol, kPer, kSoft, W>(all[wave], s_help, wave, T, Gr, O, eps2, h2, hinv);
     } else {
-        const int ts = n_groups > R.teams_above ? kMinTeam : W;
+        const int ts = hdr.y > R.teams_above ? kMinTeam : W;
         Team* teams = reinterpret_cast<Team*>(s_mem + W * sizeof(Tile));
         const int n_teams = W / ts, own = wave / ts;
         Tile& st = reinterpret_cast<Tile*>(s_mem)[wave];
@@ -2132,6 +2134,9 @@ __global__ void __launch_bounds__(256) k_group_count(GroupCtx C, const int64_t* 
 }
 
 // The groups in node order, their number, and the walks' work queues reset.
+// Where they hold fewer than kFew targets on average the team rule is given four
+// times their number (launch_walk).
+constexpr int kFew = 8;
 __global__ void __launch_bounds__(256) k_group_emit(GroupCtx C, const int64_t* __restrict__ hdr,
                                                     const int32_t* __restrict__ gcnt,
                                                     const int32_t* __restrict__ tile_sum, bool scan,
@@ -2139,6 +2144,7 @@ __global__ void __launch_bounds__(256) k_group_emit(GroupCtx C, const int64_t* _
                                                     int* __restrict__ qctr) {
     __shared__ int s_tmp[4];
     const int64_t nn = hdr[0];
+    const int n = C.link[0].z, targets = C.aoff ? C.aoff[n] : n;   // (the root holds every position)
     const bool scanned = scan && (nn + kGroupTile - 1) / kGroupTile > kTilesRead;
     if (blockIdx.x == 0 && threadIdx.x < 2 * 8) qctr[threadIdx.x * kQueueStride] = 0;   // two walks' queues
     for (int64_t t = blockIdx.x; t * kGroupTile < nn; t += gridDim.x) {
@@ -2151,7 +2157,11 @@ __global__ void __launch_bounds__(256) k_group_emit(GroupCtx C, const int64_t* _
             node_groups(C, (int)id, grp + e);
             for (int k = 0; k < g; ++k) ord[e + k] = e + k;   // (k_group_order may change it)
         }
-        if ((t + 1) * kGroupTile >= nn && threadIdx.x == 0) ghdr[0] = before + tot;
+        if ((t + 1) * kGroupTile >= nn && threadIdx.x == 0) {
+            const int ng = before + tot;
+            ghdr[0] = ng;
+            ghdr[1] = targets < (int64_t)kFew * ng ? (int)std::min<int64_t>(4 * (int64_t)ng, INT_MAX) : ng;
+        }
     }
 }
 
@@ -2451,7 +2461,11 @@ static int device_cus(ag_ctx* c) {
 //               whose waves help the others at the end (64 systems of 4000
 //               particles, 5900 groups: 1.25 ms per step, 2.2 by single waves,
 //               1.8 by whole workgroups; 180 000 with the relative opening
-//               test, whose longest groups set the time: 1.33, 4.2 and 1.6)
+//               test, whose longest groups set the time: 1.33, 4.2 and 1.6);
+//               of fewer than 8 targets a group on average above P/16: such a group has few tiles, and what it takes is its
+//               traversal (300 000 particles, 1000 active in 887 groups: 114 us,
+//               233 by whole workgroups, 4 one after another; 6 targets a group
+//               in 317 groups 72 and 93, but 17 in 353 197 and 145)
 //   else        the whole workgroup (3000 particles, 96 groups: 0.20 ms per
 //               step, 0.23 in teams of 8, 0.25 of 4, 0.63 by single waves;
 //               32^3 periodic ones, 704 groups: 0.90 ms, 0.93, 1.12 and 3.5)
