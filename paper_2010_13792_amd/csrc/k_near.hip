@@ -806,7 +806,12 @@ __global__ void __launch_bounds__(kW, 4) k_near(NearArgs A, int run, int cuts) {
             const double ex = (double)hi.x - lo.x, ey = (double)hi.y - lo.y, ez = (double)hi.z - lo.z;
             const double diag = fmax(1.001 * sqrt(ex * ex + ey * ey + ez * ez), DBL_MIN);
             // (every particle is a target: positions are slots)
-            const double R = first_radius<kPer>(A, first, t.n, lane, kMode == kLengths ? (double)A.k : A.ngb, diag);
+            // (few neighbours vary more: 14 % of the targets have none in the radius
+            // that holds two on average, and nearly every run of 15 took a second
+            // traversal for its one neighbour; 10^6 uniform ones, k = 1, 1.53 ms, now
+            // 1.23, k = 4 1.58 and 1.40; from k = 13 on twice k is more)
+            const double few = (A.k + 3.5 * sqrt((double)A.k)) / (1.25 * 1.25 * 1.25);
+            const double R = first_radius<kPer>(A, first, t.n, lane, kMode == kLengths ? fmax(A.k, few) : A.ngb, diag);
             if constexpr (kMode == kLengths) {
                 find_lengths<kPer>(S, A, t, gb, root, diag, R);
             } else {
