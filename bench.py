@@ -243,7 +243,7 @@ def main():
                               "group_pack": 0}, {}
     else:
         tuned, tune_table = autotune.tune(trial, autotune.grid(n_leaf=leaves, group_targets=[64, 32],
-                                                               waves_per_cu=[12, 16], group_split=[0, 42],
+                                                               waves_per_cu=[16], group_split=[0, 42],
                                                                group_pack=[0, 1]),
                                           f"tree|n={n}|theta={args.theta}", use_cache=False)
     # the library's defaults (where the stored walk counters were taken)

@@ -281,7 +281,7 @@ def run_batched(args):
             stream.synchronize()
             return e0.elapsed_time(e1) / 3
 
-        cands = autotune.grid(n_leaf=[8, 16, 32], waves_per_cu=[8, 12, 16], group_targets=[64, 32])
+        cands = autotune.grid(n_leaf=[8, 16, 32], waves_per_cu=[16], group_targets=[64, 32])
         best, table = autotune.tune(run, cands, f"batched256|n={n}|act={len(act)}", use_cache=False)
         log(f"batched: autotuner picked {best}")
         once(best)

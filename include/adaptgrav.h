@@ -92,8 +92,9 @@ const char *ag_last_error(void);
 /* Tunable launch options (picked by an autotuner; defaults in brackets):
  *   AG_OPT_WALK_WAVES_PER_CU   resident walk waves launched per CU [16]
  *                              (the gravity and adjoint walks run in workgroups
- *                              of 16 and 12 waves: as many whole ones as fit,
- *                              at least one)
+ *                              of 16 and 12 waves: as many whole ones per CU as
+ *                              fit; below that, workgroups on the share of the
+ *                              CUs that makes this number of waves on average)
  *   AG_OPT_SMALL_NODE          accepted nodes with at most this many particles
  *                              are summed pair by pair instead [2]
  *   AG_OPT_GROUP_SPAN          a target group never spans a cell holding more

@@ -2451,9 +2451,10 @@ static int device_cus(ag_ctx* c) {
     return cus;
 }
 
-// A walk by workgroups of Pol::kTeamWaves waves, one workgroup resident per CU
-// (AG_OPT_WALK_WAVES_PER_CU in whole workgroups, at least one).  How the groups are walked
-// goes by how many there are for the P waves launched, read on the device:
+// A walk by workgroups of Pol::kTeamWaves waves, one workgroup resident per CU:
+// AG_OPT_WALK_WAVES_PER_CU waves per CU in whole workgroups, where that is less
+// than one by workgroups on some of the CUs (as many for each XCD).  How the groups
+// are walked goes by how many there are for the P waves launched, read on the device:
 //   above 4 P   single waves: they keep every lane at interactions, and the
 //               last groups' tail is short (2^20 particles, 23 000 groups:
 //               2.64 ms per step, 2.79 in teams of 4)
@@ -2462,10 +2463,11 @@ static int device_cus(ag_ctx* c) {
 //               particles, 5900 groups: 1.25 ms per step, 2.2 by single waves,
 //               1.8 by whole workgroups; 180 000 with the relative opening
 //               test, whose longest groups set the time: 1.33, 4.2 and 1.6);
-//               of fewer than 8 targets a group on average above P/16: such a group has few tiles, and what it takes is its
-//               traversal (300 000 particles, 1000 active in 887 groups: 114 us,
-//               233 by whole workgroups, 4 one after another; 6 targets a group
-//               in 317 groups 72 and 93, but 17 in 353 197 and 145)
+//               of fewer than 8 targets a group on average above P/16: such a
+//               group has few tiles, and what it takes is its traversal (300 000
+//               particles, 1000 active in 887 groups: 114 us, 233 by whole
+//               workgroups, four rounds of them; 6 targets a group in 317 groups
+//               72 and 93, but 17 in 353 197 and 145)
 //   else        the whole workgroup (3000 particles, 96 groups: 0.20 ms per
 //               step, 0.23 in teams of 8, 0.25 of 4, 0.63 by single waves;
 //               32^3 periodic ones, 704 groups: 0.90 ms, 0.93, 1.12 and 3.5)
@@ -2473,7 +2475,9 @@ template <class Pol, int kPer, bool kSoft = false>
 static void launch_walk(ag_ctx* c, int64_t max_groups, const Groups& Gr, const WalkOut& O, int32_t* qctr,
                         float theta2, float eps2, float h2, float hinv) {
     constexpr int W = Pol::kTeamWaves;
-    int64_t blocks = (int64_t)device_cus(c) * std::max(1, c->walk_waves_per_cu / W);
+    const int64_t cus = device_cus(c);
+    int64_t blocks = c->walk_waves_per_cu >= W ? cus * (c->walk_waves_per_cu / W)
+                                               : (cus * c->walk_waves_per_cu / W + 7) / 8 * 8;
     const int waves = (int)(blocks * W);
     if (blocks > max_groups) blocks = (max_groups + 7) / 8 * 8;
     const TeamRule R{4 * waves, waves / 4};

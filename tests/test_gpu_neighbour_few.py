@@ -1,6 +1,6 @@
 """Lengths of few neighbours: the first radius holds them for every target of a run
 in one traversal.  Right against the oracle for 1 to 16 neighbours, and one neighbour takes
-clearly less time than eight (0.75 of it; 0.91 when nearly every run of targets
+clearly less time than eight (0.75 of it; 0.93 when nearly every run of targets
 had one that found none and the run was traversed twice)."""
 import numpy as np
 import pytest
