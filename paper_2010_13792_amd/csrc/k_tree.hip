@@ -356,6 +356,13 @@ __global__ void __launch_bounds__(kThreads) k_rs_rowscan(const int32_t* __restri
     if (threadIdx.x == 0) tot[blockIdx.x] = carry;
 }
 
+// orders a wave's LDS accesses around it
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Stable scatter of one tile of (key, value) pairs by one 8-bit digit.  Each
 // wave ranks its own contiguous run of the tile (kRsItems rows of 64) with no
 // workgroup barrier: lanes with equal digits are matched by ballots, and the
@@ -438,7 +445,9 @@ __global__ void __launch_bounds__(kThreads) k_rs_scatter(const uint64_t* __restr
         const int r = ag_prefix_count(peers);
         int before = 0;
         if (valid) before = cnt_w[d];   // every matched lane reads the count ...
+        wave_sync();
         if (valid && r == 0) cnt_w[d] = before + __popcll(peers);   // ... before the first one adds to it
+        wave_sync();                                                // ... and after the row before's has
         rk[k] = before + r;
     }
     __syncthreads();
@@ -527,8 +536,10 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_sort(int n, const doubl
             }
             const int r = ag_prefix_count(peers);
             int before = 0;
-            if (valid) before = cnt_w[d];
+            if (valid) before = cnt_w[d];   // (ordered as in k_rs_scatter)
+            wave_sync();
             if (valid && r == 0) cnt_w[d] = before + __popcll(peers);
+            wave_sync();
             rk[k] = before + r;
         }
         __syncthreads();
@@ -1064,13 +1075,6 @@ constexpr int kWaveWin = 64 + kWaveLook;   // 17 runs of 16
 constexpr int kWinRuns = kWaveWin / 16;
 constexpr int kFarWave = 256;        // far entries held per wave between flushes
 constexpr int kLevels = AG_MAX_LEVEL + 1;
-
-// orders a wave's LDS accesses around it (the wave's lanes share the window)
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // index of the first entry at or after j in one run of 16 window entries
 // (four 16-byte reads) that is below l, or INT_MAX
