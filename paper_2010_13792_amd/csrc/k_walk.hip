@@ -1768,7 +1768,12 @@ __global__ void __launch_bounds__(W * kW, Pol::kWaves) k_walk_team(Tree T, Group
             if (!guest) {
                 if (me == 0 && ag_lane() == 0) {
                     lds_put(&teams[own].state, kTeamClosed);
+                    // (closed before the queue is asked: a wave that finds the queues
+                    // empty after this must not find the team still open on the group
+                    // before the one it gets here)
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
                     const int g = pop_group(kPer == kOpen && ts < W ? Gr.ord : nullptr, qctr, n_groups, q);
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
                     lds_put(&teams[own].g, g);
                     if (g < 0) lds_put(&teams[own].state, kTeamDone);
                 }
