@@ -78,9 +78,16 @@ struct Groups {
     const int32_t* __restrict__ ord;   // the order in which teams of kMinTeam walk them (open boundaries)
 };
 
-// numbers of groups that are walked in an order of their own (k_group_order)
-constexpr int kOrderMin = 512, kOrderMax = 16384;
-__device__ __forceinline__ bool ordered(int n_groups) { return n_groups > kOrderMin && n_groups <= kOrderMax; }
+// Numbers of groups that are walked in an order of their own (k_group_order): above
+// `least`, the teams of a walk, which start that many at once in any order; up to
+// `most`, above which single waves walk them, and no more than kOrderMax, which one
+// workgroup orders in 9 us (a larger AG_OPT_WALK_WAVES_PER_CU has teams walk more:
+// those go in the list's order).
+constexpr int kOrderMax = 16384;
+struct OrderRange {
+    int least, most;
+    __device__ __forceinline__ bool holds(int n_groups) const { return n_groups > least && n_groups <= most; }
+};
 
 struct WalkOut {
     double* acc;
@@ -2176,10 +2183,10 @@ __global__ void __launch_bounds__(256) k_group_emit(GroupCtx C, const int64_t* _
 // steps), or with the relative opening test by its smallest |a_old|, to a
 // factor of sqrt(2): it sets how far the nodes are opened.  By one workgroup,
 // for as many groups as are walked in such teams.
-__global__ void __launch_bounds__(256) k_group_amin(Groups Gr, const int32_t* __restrict__ perm,
+__global__ void __launch_bounds__(256) k_group_amin(Groups Gr, OrderRange R, const int32_t* __restrict__ perm,
                                                     const float* __restrict__ rel_a, float* __restrict__ amin) {
     const int n = Gr.hdr[0], lane = ag_lane();
-    if (!ordered(n)) return;
+    if (!R.holds(n)) return;
     for (int g = (blockIdx.x * blockDim.x + threadIdx.x) >> 6; g < n; g += (gridDim.x * blockDim.x) >> 6) {
         const int4 gd = Gr.grp[g];
         float a = FLT_MAX;
@@ -2189,12 +2196,13 @@ __global__ void __launch_bounds__(256) k_group_amin(Groups Gr, const int32_t* __
     }
 }
 
-__global__ void __launch_bounds__(1024) k_group_order(const int32_t* __restrict__ ghdr, const int4* __restrict__ grp,
-                                                      const float* __restrict__ amin, int32_t* __restrict__ ord) {
+__global__ void __launch_bounds__(1024) k_group_order(const int32_t* __restrict__ ghdr, OrderRange R,
+                                                      const int4* __restrict__ grp, const float* __restrict__ amin,
+                                                      int32_t* __restrict__ ord) {
     constexpr int K = 512;   // classes: exponent and one bit of the fraction
     __shared__ int s_at[8 * K], s_w[16];
     const int n = ghdr[0], t = threadIdx.x;
-    if (!ordered(n)) return;
+    if (!R.holds(n)) return;
     auto key = [&](int g) {
         int q = (int)((int64_t)g * 8 / n);   // the work queue that holds g (pop_group)
         while (g >= (int)((int64_t)n * (q + 1) / 8)) ++q;
@@ -2476,13 +2484,17 @@ static int device_cus(ag_ctx* c) {
 //   else        the whole workgroup (3000 particles, 96 groups: 0.20 ms per
 //               step, 0.23 in teams of 8, 0.25 of 4, 0.63 by single waves;
 //               32^3 periodic ones, 704 groups: 0.90 ms, 0.93, 1.12 and 3.5)
+static int64_t walk_blocks(ag_ctx* c, int W) {
+    const int64_t cus = device_cus(c);
+    return c->walk_waves_per_cu >= W ? cus * (c->walk_waves_per_cu / W)
+                                     : (cus * c->walk_waves_per_cu / W + 7) / 8 * 8;
+}
+
 template <class Pol, int kPer, bool kSoft = false>
 static void launch_walk(ag_ctx* c, int64_t max_groups, const Groups& Gr, const WalkOut& O, int32_t* qctr,
                         float theta2, float eps2, float h2, float hinv) {
     constexpr int W = Pol::kTeamWaves;
-    const int64_t cus = device_cus(c);
-    int64_t blocks = c->walk_waves_per_cu >= W ? cus * (c->walk_waves_per_cu / W)
-                                               : (cus * c->walk_waves_per_cu / W + 7) / 8 * 8;
+    int64_t blocks = walk_blocks(c, W);
     const int waves = (int)(blocks * W);
     if (blocks > max_groups) blocks = (max_groups + 7) / 8 * 8;
     const TeamRule R{4 * waves, waves / 4};
@@ -2538,13 +2550,17 @@ static WalkOut make_out(ag_ctx* c, double G) {
 // Ewald sums, where a group's cost goes by its width, no better.
 static int order_groups(ag_ctx* c, int64_t n_act, bool rel, const Groups& Gr) {
     if (n_act < 40000 || n_act / 48 > kOrderMax) return AG_OK;
+    // for either walk: the adjoint's workgroups hold fewer teams, the others more waves
+    constexpr int Wa = AdjointPolicy::kTeamWaves, Wf = ForwardPolicy::kTeamWaves;
+    const OrderRange R{(int)(walk_blocks(c, Wa) * (Wa / kMinTeam)),
+                       (int)std::min<int64_t>(4 * walk_blocks(c, Wf) * Wf, kOrderMax)};
     PhaseScope phase(c, AG_PHASE_GROUPS);
     if (rel) {
         AG_TRY(ag_ensure(c, c->grp_amin, kOrderMax * sizeof(float)));
-        hipLaunchKernelGGL(k_group_amin, dim3(1024), dim3(256), 0, c->stream, Gr, c->perm.as<int32_t>(),
+        hipLaunchKernelGGL(k_group_amin, dim3(1024), dim3(256), 0, c->stream, Gr, R, c->perm.as<int32_t>(),
                            c->rel_a.as<float>(), c->grp_amin.as<float>());
     }
-    hipLaunchKernelGGL(k_group_order, dim3(1), dim3(1024), 0, c->stream, Gr.hdr, Gr.grp,
+    hipLaunchKernelGGL(k_group_order, dim3(1), dim3(1024), 0, c->stream, Gr.hdr, R, Gr.grp,
                        rel ? c->grp_amin.as<float>() : (const float*)nullptr, c->grp_ord.as<int32_t>());
     return AG_OK;
 }
