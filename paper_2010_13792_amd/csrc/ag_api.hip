@@ -197,12 +197,12 @@ extern "C" int ag_destroy(ag_ctx* c) {
     if (!c) return AG_OK;
     DeviceGuard g(c->device);
     (void)hipStreamSynchronize(c->stream);
-    DevBuf* bufs[] = {&c->keys[0], &c->keys[1], &c->vals[0], &c->vals[1], &c->box_part, &c->sort_hist, &c->perm,
+    DevBuf* bufs[] = {&c->keys[0], &c->keys[1], &c->vals[0], &c->vals[1], &c->lvl_rows, &c->perm,
                       &c->rank, &c->spos, &c->svf, &c->cdig, &c->cd_min, &c->pos_cnt, &c->pos_off,
-                      &c->scan_tmp, &c->nd_rec, &c->nd_slot, &c->nd_link, &c->nd_mp,
-                      &c->nd_64, &c->nd_w, &c->nd_wf, &c->in_list, &c->in_cnt, &c->in_off,
+                      &c->nd_rec, &c->nd_slot, &c->nd_link, &c->nd_mp,
+                      &c->nd_64, &c->nd_w, &c->nd_wf, &c->in_cnt, &c->in_off,
                       &c->tree_hdr, &c->lvl_list, &c->leaf_list, &c->leaf_pos, &c->child, &c->sys_off, &c->sys_root, &c->sys_box, &c->act_flag,
-                      &c->act_pos, &c->act_off, &c->grp, &c->grp_hdr, &c->ewald_tab, &c->soft_h, &c->soft_s, &c->rel_a, &c->grp_cnt, &c->grp_tile, &c->grp_ord, &c->grp_amin, &c->act_stamp, &c->sys_act, &c->wsorted,
+                      &c->act_pos, &c->act_off, &c->grp, &c->grp_hdr, &c->ewald_tab, &c->soft_h, &c->soft_s, &c->rel_a, &c->grp_cnt, &c->grp_tile, &c->grp_amin, &c->sys_act, &c->wsorted,
                       &c->direct_part, &c->tmp_tidal, &c->sel_flag, &c->sel_tile, &c->stats, &c->dflags};
     for (DevBuf* b : bufs) ag_release(*b);
     for (PhaseEvents& p : c->timing.pending) {

@@ -111,17 +111,17 @@ struct ag_ctx {
     int32_t sys_levels = 0;  // octal digits taken by the system prefix
     int64_t max_nodes = 0;
 
-    DevBuf keys[2], vals[2];      // radix-sort ping-pong (u64 keys, i32 values)
-    DevBuf box_part;              // u64 [6 per workgroup]: partial bounding boxes
-    DevBuf sort_hist;             // per-block digit counts (u32)
+    DevBuf keys[2], vals[2];      // radix-sort ping-pong (u64 keys, i32 values); after the sort vals[0] holds
+                                  // the tiles' totals of the node counts (int2), then of the active flags
+    DevBuf lvl_rows;              // i32: inner nodes per level and deepest level of k_write_nodes' workgroups
     DevBuf perm;                  // i32 [n]: sorted position -> input row
     DevBuf rank;                  // i32 [n]: input row -> sorted position
-    DevBuf spos;                  // double4 [n]: sorted x, y, z, m
+    DevBuf spos;                  // double4 [n]: sorted x, y, z, m (before: partial bounding boxes)
     DevBuf svf;                   // float4  [n]: sorted vx, vy, vz, m (FP32 copies)
     DevBuf cdig;                  // i32 [n]: octal digits shared with the previous key
     DevBuf cd_min;                // i32: their minima over runs of 16, 256, ... 2^24 positions
-    DevBuf pos_cnt, pos_off;      // i32 [n+1]: nodes starting at each position, offsets
-    DevBuf scan_tmp;              // int2: totals of the node counts per tile; i32: of the active flags
+    DevBuf pos_cnt, pos_off;      // i32 [n+1]: nodes starting at each position (before: the sort's digit
+                                  // counts), offsets
 
     // node arrays, depth-first (pre-order) numbering
     DevBuf nd_rec;                // NodeRec: what the opening test reads
@@ -131,8 +131,10 @@ struct ag_ctx {
     DevBuf nd_64;                 // double [25]: FP64 moments (M, c, u, Q, Qd, lo, hi)
     DevBuf nd_w;                  // double [12]: vector-charge moments W0 (3), W1 (9) for the adjoint
     DevBuf nd_wf;                 // float4 x3: W0, W1 in FP32 for the adjoint walk
-    DevBuf in_list;               // i32 [max_nodes]: inner nodes in pre-order
-    DevBuf in_cnt, in_off;        // i32 [n+1]: inner nodes starting at each position, offsets
+    DevBuf in_cnt, in_off;        // i32 [n+1], [n+n_sys+1]: inner nodes starting at each position, offsets.
+                                  // After the build in_cnt holds the last list entry that named each
+                                  // position, + 1 (stale where none does), and in_off the groups in the
+                                  // order they are walked
     DevBuf tree_hdr;              // i64 [8]: n_nodes, max_level, inner nodes; then the level table (kLvl*)
     DevBuf lvl_list;              // i32 [inner bound]: inner node ids grouped by level
     DevBuf leaf_list;             // i32 [n]: leaf node ids in pre-order
@@ -145,7 +147,6 @@ struct ag_ctx {
 
     // --- evaluation scratch ---
     bool all_active = false;      // the last grouping listed every particle (no flag, offset or position arrays)
-    DevBuf act_stamp;             // i32 [n]: last list entry that named the position, + 1 (stale where none does)
     DevBuf act_flag;              // i32 [n]
     DevBuf act_pos;               // i32 [n]: active sorted positions, ascending
     DevBuf act_off;               // i32 [n+1]: exclusive scan of act_flag
@@ -157,7 +158,7 @@ struct ag_ctx {
     DevBuf grp_hdr;               // i32: [0] number of groups, [1] as the team rule counts them, then two walks' eight work-queue counters, kQueueStride apart
     DevBuf grp_cnt;               // i32 [max_nodes]: groups owned per node
     DevBuf grp_tile;              // i32: their totals per tile
-    DevBuf grp_ord, grp_amin;     // i32: the groups in the order they are walked; f32: smallest |a_old| of each
+    DevBuf grp_amin;              // f32: smallest |a_old| of each group
     DevBuf sys_act;               // i32 [n_sys + 1]
     DevBuf wsorted;               // double4 [n]: adjoint weights in sorted order
     DevBuf direct_part;           // direct sum: FP64 per-split sums of a small target set

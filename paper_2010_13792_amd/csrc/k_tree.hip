@@ -1054,8 +1054,7 @@ __global__ void __launch_bounds__(kThreads) k_seg_sort(TopoParams P, const int32
     }
 }
 
-// Writes every node's link and lists the inner nodes (in pre-order) and the
-// leaves with their first positions.  The end of the cell of node (l, p) is
+// Writes every node's link and lists the leaves with their first positions.  The end of the cell of node (l, p) is
 // the first q > p with cd'[q] < l; ends do not decrease from the deepest node
 // at p (the leaf) to the shallowest, so each search continues from the end
 // below it.  Every wave works on its own run of 64 positions with its own LDS
@@ -1119,7 +1118,7 @@ __device__ __forceinline__ int win_first_below(const int* __restrict__ cdw, cons
 __global__ void __launch_bounds__(kThreads) k_write_nodes(TopoParams P, const int32_t* __restrict__ cd,
                                                           const int32_t* __restrict__ off,
                                                           const int32_t* __restrict__ ioff, int4* __restrict__ link,
-                                                          int32_t* __restrict__ ilist, int32_t* __restrict__ leaves,
+                                                          int32_t* __restrict__ leaves,
                                                           int32_t* __restrict__ leaf_pos,
                                                           int64_t* __restrict__ hdr, int32_t* __restrict__ blk,
                                                           int32_t* __restrict__ far_p, int32_t* __restrict__ far_t) {
@@ -1193,7 +1192,6 @@ __global__ void __launch_bounds__(kThreads) k_write_nodes(TopoParams P, const in
             const int skip = far ? 0 : offw[e - p0];   // off[n] = n_nodes past the end
             link[id] = make_int4(skip, (int)p, far ? 0 : (int)(e - p), l | (leaf ? 0x100 : 0));
             if (!leaf) {
-                ilist[iop + t] = (int32_t)id;
                 atomicAdd(&s_lc[l], 1);
             } else {
                 const int64_t lf = op - iop;   // leaves before p = nodes - inner nodes before p
@@ -1576,10 +1574,13 @@ template <int G> __device__ __forceinline__ void grp_reduce(MomentSums& S) {
 // id and, in the child rows, its children by octant (-1 where an octant is
 // empty), from the pre-order links (the first child follows the node, the
 // next follows the first child's subtree, ...).  A level's kernels then read
-// a node and its children from the same slot.
+// a node and its children from the same slot.  (The inner nodes are picked from
+// the links a thousand nodes at a time: a list of them would take as much room as
+// the slots do, and one pass over every node with a lane each, four in five of them
+// leaves, took a build of 2^20 from 356 to 385 us.)
+constexpr int kListNodes = 1024;   // nodes a workgroup looks through at a time
 struct ListArgs {
     int blocks;   // workgroups that make the lists (0: none)
-    const int32_t* ilist;
     const int4* link;
     const uint64_t* keys;
     int4* child;
@@ -1588,7 +1589,6 @@ struct ListArgs {
     int32_t* nslot;
 };
 __device__ __forceinline__ void level_lists(const ListArgs& Q, const int64_t* __restrict__ hdr) {
-    const int32_t* __restrict__ ilist = Q.ilist;
     const int4* __restrict__ link = Q.link;
     const uint64_t* __restrict__ keys = Q.keys;
     int4* __restrict__ child = Q.child;
@@ -1596,7 +1596,8 @@ __device__ __forceinline__ void level_lists(const ListArgs& Q, const int64_t* __
     int32_t* __restrict__ lvl_list = Q.lvl_list;
     int32_t* __restrict__ nslot = Q.nslot;
     __shared__ int s_off[AG_MAX_LEVEL + 2], s_cnt[AG_MAX_LEVEL + 1], s_base[AG_MAX_LEVEL + 1];
-    const int64_t ni = hdr[2];
+    __shared__ int s_node[kListNodes], s_n;
+    const int64_t nn = hdr[0];
     if (threadIdx.x == 0) {
         int a = 0;
         for (int l = 0; l <= AG_MAX_LEVEL; ++l) {
@@ -1608,36 +1609,56 @@ __device__ __forceinline__ void level_lists(const ListArgs& Q, const int64_t* __
     if (threadIdx.x <= AG_MAX_LEVEL) s_cnt[threadIdx.x] = 0;
     __syncthreads();
     if (blockIdx.x == 0 && threadIdx.x <= AG_MAX_LEVEL + 1) lvl[kLvlOff + threadIdx.x] = s_off[threadIdx.x];
-    for (int64_t t0 = (int64_t)blockIdx.x * kThreads; t0 < ni; t0 += (int64_t)Q.blocks * kThreads) {
-        const int64_t t = t0 + threadIdx.x;
-        int node = -1, l = 0, r = 0;
-        int c8[8] = {-1, -1, -1, -1, -1, -1, -1, -1};
-        if (t < ni) {
-            node = ilist[t];
-            const int4 L = link[node];
-            l = L.w & 0xff;
-            r = atomicAdd(&s_cnt[l], 1);
-            const int sh = 63 - 3 * (l + 1);   // the children's own octal digit
-            for (int ch = node + 1, k8 = 0; ch < L.x && k8 < 8; ++k8) {
-                const int4 C = link[ch];
-                c8[(int)((keys[C.y] >> sh) & 7)] = ch;
-                ch = C.x;
+    for (int64_t t0 = (int64_t)blockIdx.x * kListNodes; t0 < nn; t0 += (int64_t)Q.blocks * kListNodes) {
+        int4 own[kListNodes / kThreads];
+#pragma unroll
+        for (int k = 0; k < kListNodes / kThreads; ++k) {
+            const int64_t t = t0 + k * kThreads + threadIdx.x;
+            own[k] = t < nn ? link[t] : make_int4(0, 0, 0, 0x100);
+        }
+        if (threadIdx.x == 0) s_n = 0;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kListNodes / kThreads; ++k) {
+            const bool inner = (own[k].w & 0x100) == 0;
+            const uint64_t m = __ballot(inner);
+            int base = 0;
+            if (m != 0 && (threadIdx.x & 63) == 0) base = atomicAdd(&s_n, __popcll(m));
+            base = __builtin_amdgcn_readfirstlane(base);
+            if (inner) s_node[base + ag_prefix_count(m)] = (int)(t0 + k * kThreads + threadIdx.x);
+        }
+        __syncthreads();
+        const int ni = s_n;
+        for (int b = 0; b < ni; b += kThreads) {
+            int node = -1, l = 0, r = 0;
+            int c8[8] = {-1, -1, -1, -1, -1, -1, -1, -1};
+            if (b + (int)threadIdx.x < ni) {
+                node = s_node[b + threadIdx.x];
+                const int4 L = link[node];
+                l = L.w & 0xff;
+                r = atomicAdd(&s_cnt[l], 1);
+                const int sh = 63 - 3 * (l + 1);   // the children's own octal digit
+                for (int ch = node + 1, k8 = 0; ch < L.x && k8 < 8; ++k8) {
+                    const int4 C = link[ch];
+                    c8[(int)((keys[C.y] >> sh) & 7)] = ch;
+                    ch = C.x;
+                }
             }
+            __syncthreads();
+            if (threadIdx.x <= AG_MAX_LEVEL && s_cnt[threadIdx.x] > 0) {
+                s_base[threadIdx.x] = atomicAdd(&lvl[kLvlCur + threadIdx.x], s_cnt[threadIdx.x]);
+                s_cnt[threadIdx.x] = 0;
+            }
+            __syncthreads();
+            if (node >= 0) {
+                const int64_t slot = s_off[l] + s_base[l] + r;
+                lvl_list[slot] = node;
+                nslot[node] = (int32_t)slot;
+                child[2 * slot] = make_int4(c8[0], c8[1], c8[2], c8[3]);
+                child[2 * slot + 1] = make_int4(c8[4], c8[5], c8[6], c8[7]);
+            }
+            __syncthreads();
         }
-        __syncthreads();
-        if (threadIdx.x <= AG_MAX_LEVEL && s_cnt[threadIdx.x] > 0) {
-            s_base[threadIdx.x] = atomicAdd(&lvl[kLvlCur + threadIdx.x], s_cnt[threadIdx.x]);
-            s_cnt[threadIdx.x] = 0;
-        }
-        __syncthreads();
-        if (node >= 0) {
-            const int64_t slot = s_off[l] + s_base[l] + r;
-            lvl_list[slot] = node;
-            nslot[node] = (int32_t)slot;
-            child[2 * slot] = make_int4(c8[0], c8[1], c8[2], c8[3]);
-            child[2 * slot + 1] = make_int4(c8[4], c8[5], c8[6], c8[7]);
-        }
-        __syncthreads();
     }
 }
 
@@ -1784,9 +1805,9 @@ int moments_pass(ag_ctx* c, const double* v, bool lists) {
     const int64_t n = c->n;
     const int64_t inner_bound = c->max_nodes - n;
     int64_t* hdr = c->tree_hdr.as<int64_t>();
-    ListArgs Q{0, c->in_list.as<int32_t>(), c->nd_link.as<int4>(), c->keys[0].as<uint64_t>(), c->child.as<int4>(),
+    ListArgs Q{0, c->nd_link.as<int4>(), c->keys[0].as<uint64_t>(), c->child.as<int4>(),
                reinterpret_cast<int32_t*>(hdr + 8), c->lvl_list.as<int32_t>(), c->nd_slot.as<int32_t>()};
-    if (lists) Q.blocks = std::min(grid_for(inner_bound), 1024);
+    if (lists) Q.blocks = (int)std::min<int64_t>((c->max_nodes + kListNodes - 1) / kListNodes, 1024);
     hipLaunchKernelGGL(k_leaf_moments, dim3(Q.blocks + grid_for(kLeafLanes * n)), dim3(kThreads), 0, st, hdr,
                        c->leaf_list.as<int32_t>(), c->leaf_pos.as<int32_t>(), c->spos.as<double4>(),
                        c->perm.as<int32_t>(), v, c->svf.as<float4>(), O, Q);
@@ -1827,18 +1848,21 @@ int ag_launch_build(ag_ctx* c, int64_t n, const double* x, const double* v, cons
     const int64_t max_nodes = n + (int64_t)(AG_MAX_LEVEL + 1) * (n / (n_leaf + 1) + n_sys) + 1;
 
     AG_TRY(ag_ensure(c, c->keys[0], n * 8)); AG_TRY(ag_ensure(c, c->keys[1], n * 8));
-    AG_TRY(ag_ensure(c, c->vals[0], n * 4)); AG_TRY(ag_ensure(c, c->vals[1], n * 4));
+    // tiles of the node counts: enough workgroups for the device, few enough
+    // totals for each to add up
+    const int ctile = n <= ((int64_t)1 << 19) ? 512 : (n <= ((int64_t)1 << 21) ? 1024 : 2048);
+    const int64_t ntile = (n + ctile - 1) / ctile;
+    AG_TRY(ag_ensure(c, c->vals[0], std::max(n * 4, ntile * (int64_t)sizeof(int2))));
+    AG_TRY(ag_ensure(c, c->vals[1], n * 4));
     const int items = rs_items(n);
     const int nblocks = (int)((n + rs_tile(items) - 1) / rs_tile(items));
-    // (also k_write_nodes' per-workgroup rows after the sort)
     const int wblocks = std::min(grid_for(n), kWriteBlocks);
-    AG_TRY(ag_ensure(c, c->sort_hist, std::max({(size_t)(256 * nblocks + 256 + 1) * 4,
-                                                (size_t)wblocks * (kLevels + 1) * sizeof(int32_t)})));
-    AG_TRY(ag_ensure(c, c->box_part, (size_t)(n / kBoxChunk + n_sys + 1) * 6 * sizeof(uint64_t)));
+    AG_TRY(ag_ensure(c, c->lvl_rows, (size_t)wblocks * (kLevels + 1) * sizeof(int32_t)));
     AG_TRY(ag_ensure(c, c->pos_off, (size_t)(256 * (int64_t)nblocks + 1 > n + 1 ? 256 * (int64_t)nblocks + 1 : n + 1) * 4));
     AG_TRY(ag_ensure(c, c->perm, n * 4)); AG_TRY(ag_ensure(c, c->rank, n * 4));
-    AG_TRY(ag_ensure(c, c->spos, n * 32)); AG_TRY(ag_ensure(c, c->svf, n * 16));
-    AG_TRY(ag_ensure(c, c->cdig, n * 4)); AG_TRY(ag_ensure(c, c->pos_cnt, (n + 1) * 4));
+    const size_t box_bytes = (size_t)(n / kBoxChunk + n_sys + 1) * 6 * sizeof(uint64_t);
+    AG_TRY(ag_ensure(c, c->spos, std::max((size_t)n * 32, box_bytes))); AG_TRY(ag_ensure(c, c->svf, n * 16));
+    AG_TRY(ag_ensure(c, c->cdig, n * 4)); AG_TRY(ag_ensure(c, c->pos_cnt, std::max((size_t)n + 1, (size_t)256 * nblocks + 256) * 4));
     // minima of the shared-digit counts: level 0 per 16 positions (16 per run of
     // 256), levels k >= 1 per 16^(k+1)
     int64_t cd_cnt[kCdLevels], cd_tot = 0;
@@ -1855,8 +1879,8 @@ int ag_launch_build(ag_ctx* c, int64_t n, const double* x, const double* v, cons
     AG_TRY(ag_ensure(c, c->nd_rec, max_nodes * sizeof(NodeRec))); AG_TRY(ag_ensure(c, c->nd_link, max_nodes * 16));
     AG_TRY(ag_ensure(c, c->nd_slot, max_nodes * 4));
     AG_TRY(ag_ensure(c, c->nd_mp, max_nodes * 64)); AG_TRY(ag_ensure(c, c->nd_64, max_nodes * kM64 * 8));
-    AG_TRY(ag_ensure(c, c->in_list, max_nodes * 4)); AG_TRY(ag_ensure(c, c->in_cnt, (n + 1) * 4));
-    AG_TRY(ag_ensure(c, c->in_off, (n + 1) * 4));
+    AG_TRY(ag_ensure(c, c->in_cnt, (n + 1) * 4));
+    AG_TRY(ag_ensure(c, c->in_off, (n + n_sys + 1) * 4));
     AG_TRY(ag_ensure(c, c->sys_off, (n_sys + 1) * 8)); AG_TRY(ag_ensure(c, c->sys_root, (n_sys + 1) * 4));
     const int64_t inner_bound = max_nodes - n;   // inner nodes never exceed this
     AG_TRY(ag_ensure(c, c->lvl_list, (size_t)(inner_bound > 0 ? inner_bound : 1) * 4));
@@ -1864,11 +1888,6 @@ int ag_launch_build(ag_ctx* c, int64_t n, const double* x, const double* v, cons
     AG_TRY(ag_ensure(c, c->leaf_pos, (n + 1) * 4));
     AG_TRY(ag_ensure(c, c->child, (size_t)(inner_bound > 0 ? inner_bound : 1) * 32));
     AG_TRY(ag_ensure(c, c->sys_box, 6 * n_sys * 8 + 8 * (n_sys + 1)));
-    // tiles of the node counts: enough workgroups for the device, few enough
-    // totals for each to add up
-    const int ctile = n <= ((int64_t)1 << 19) ? 512 : (n <= ((int64_t)1 << 21) ? 1024 : 2048);
-    const int64_t ntile = (n + ctile - 1) / ctile;
-    AG_TRY(ag_ensure(c, c->scan_tmp, (size_t)ntile * sizeof(int2)));
     if (c->soft_n > 0) AG_TRY(ag_ensure(c, c->soft_s, (size_t)n * sizeof(float)));
 
     if (c->depth_host && !c->capturing) {
@@ -1898,7 +1917,7 @@ int ag_launch_build(ag_ctx* c, int64_t n, const double* x, const double* v, cons
         hipLaunchKernelGGL(k_build_init, dim3(1), dim3(512), 0, st, n_sys, n, sys_offsets, off, flags, box, blk_off,
                            hdr, (int)(kTreeHdrBytes / 8));
     const int64_t box_blocks = one ? (n + kBoxChunk - 1) / kBoxChunk : n / kBoxChunk + n_sys + 1;
-    uint64_t* box_part = c->box_part.as<uint64_t>();
+    uint64_t* box_part = reinterpret_cast<uint64_t*>(c->spos.p);   // free until the particles move
     hipLaunchKernelGGL(k_box, dim3((unsigned)box_blocks), dim3(kBoxThreads), 0, st, x, n, off, n_sys,
                        one ? nullptr : blk_off, box_part, flags, c->box, hdr, (int)(kTreeHdrBytes / 8));
     // one system's partial boxes are reduced by every workgroup of the keys
@@ -1913,7 +1932,7 @@ int ag_launch_build(ag_ctx* c, int64_t n, const double* x, const double* v, cons
     uint64_t* k1 = c->keys[1].as<uint64_t>();
     int32_t* v0 = c->vals[0].as<int32_t>();
     int32_t* v1 = c->vals[1].as<int32_t>();
-    int32_t* hist = c->sort_hist.as<int32_t>();
+    int32_t* hist = c->pos_cnt.as<int32_t>();   // free until the topology
     int32_t* tot = hist + (int64_t)256 * nblocks;
     int32_t* hoff = c->pos_off.as<int32_t>();
     int32_t* perm = c->perm.as<int32_t>();
@@ -1979,18 +1998,18 @@ int ag_launch_build(ag_ctx* c, int64_t n, const double* x, const double* v, cons
     int32_t* poff = c->pos_off.as<int32_t>();
     int32_t* icnt = c->in_cnt.as<int32_t>();
     int32_t* ioff = c->in_off.as<int32_t>();
-    int2* tsum = c->scan_tmp.as<int2>();
+    int2* tsum = c->vals[0].as<int2>();   // free after the sort
     hipLaunchKernelGGL(k_count_nodes, dim3((unsigned)(ntile + 1)), dim3(kThreads), 0, st, P, cd, ctile, pcnt, icnt,
                        tsum, M, C);
     const bool scan = ntile > kTilesRead;
-    if (scan) ag_tile_scan(c, c->scan_tmp.as<int32_t>(), 2, ntile);
+    if (scan) ag_tile_scan(c, c->vals[0].as<int32_t>(), 2, ntile);
     hipLaunchKernelGGL(k_node_offsets, dim3((unsigned)ntile), dim3(kThreads), 0, st, n, ctile, pcnt, icnt, tsum, scan,
                        poff, ioff);
     // (the node counts are free after their scans: they hold the list of far
-    // ends; the sort's histograms hold the per-workgroup rows)
-    int32_t* blk_rows = c->sort_hist.as<int32_t>();
+    // ends)
+    int32_t* blk_rows = c->lvl_rows.as<int32_t>();
     hipLaunchKernelGGL(k_write_nodes, dim3(wblocks), dim3(kThreads), 0, st, P, cd, poff, ioff,
-                       c->nd_link.as<int4>(), c->in_list.as<int32_t>(), c->leaf_list.as<int32_t>(),
+                       c->nd_link.as<int4>(), c->leaf_list.as<int32_t>(),
                        c->leaf_pos.as<int32_t>(), hdr, blk_rows,
                        pcnt, icnt);
     const CloseArgs Q{wblocks, blk_rows, c->leaf_pos.as<int32_t>(), n_sys, off, c->sys_root.as<int32_t>(),

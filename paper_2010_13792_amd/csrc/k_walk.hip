@@ -2243,24 +2243,21 @@ int ag_prepare_groups(ag_ctx* c, const int32_t* idx, int64_t n_act, int64_t* max
     const int64_t n = c->n;
     const int64_t mg = n_act + c->n_sys + 1;   // every group holds at least one target
     const int64_t mtiles = (n + kMarkTile - 1) / kMarkTile, gtiles = (c->max_nodes + kGroupTile - 1) / kGroupTile;
-    AG_TRY(ag_ensure(c, c->act_stamp, n * 4));
     AG_TRY(ag_ensure(c, c->act_flag, n * 4));
     AG_TRY(ag_ensure(c, c->act_off, (n + 1) * 4));
     AG_TRY(ag_ensure(c, c->act_pos, n * 4));
     AG_TRY(ag_ensure(c, c->grp, mg * 16));
-    AG_TRY(ag_ensure(c, c->grp_ord, mg * 4));
     AG_TRY(ag_ensure(c, c->grp_hdr, (1 + 2 * 8) * kQueueStride * sizeof(int32_t)));
     AG_TRY(ag_ensure(c, c->grp_cnt, c->max_nodes * 4));
     AG_TRY(ag_ensure(c, c->grp_tile, gtiles * 4));
-    AG_TRY(ag_ensure(c, c->scan_tmp, mtiles * 4));
     PhaseScope phase(c, AG_PHASE_GROUPS);
     hipStream_t st = c->stream;
     int32_t* off = c->act_off.as<int32_t>();
     c->all_active = idx == nullptr;
     if (idx) {
         int32_t* flag = c->act_flag.as<int32_t>();
-        int32_t* stamp = c->act_stamp.as<int32_t>();
-        int32_t* msum = c->scan_tmp.as<int32_t>();
+        int32_t* stamp = c->in_cnt.as<int32_t>();
+        int32_t* msum = c->vals[0].as<int32_t>();   // (as many as tiles at least)
         int32_t* flags = c->dflags.as<int32_t>();
         hipLaunchKernelGGL(k_mark_stamp, dim3(grid_for(n_act)), dim3(256), 0, st, n_act, n_dev, idx, n,
                            c->rank.as<int32_t>(), stamp, flags, n_total);
@@ -2286,7 +2283,7 @@ int ag_prepare_groups(ag_ctx* c, const int32_t* idx, int64_t n_act, int64_t* max
     const bool scan = gtiles > 4 * kTilesRead;
     if (scan) ag_tile_scan(c, gsum, 1, gtiles, hdr, kGroupTile);
     hipLaunchKernelGGL(k_group_emit, dim3(gblocks), dim3(256), 0, st, C, hdr, gcnt, gsum, scan,
-                       c->grp.as<int4>(), c->grp_ord.as<int32_t>(), ghdr, ghdr + kQueueStride);
+                       c->grp.as<int4>(), c->in_off.as<int32_t>(), ghdr, ghdr + kQueueStride);
     *max_groups = mg;
     return AG_OK;
 }
@@ -2561,7 +2558,7 @@ static int order_groups(ag_ctx* c, int64_t n_act, bool rel, const Groups& Gr) {
                            c->rel_a.as<float>(), c->grp_amin.as<float>());
     }
     hipLaunchKernelGGL(k_group_order, dim3(1), dim3(1024), 0, c->stream, Gr.hdr, R, Gr.grp,
-                       rel ? c->grp_amin.as<float>() : (const float*)nullptr, c->grp_ord.as<int32_t>());
+                       rel ? c->grp_amin.as<float>() : (const float*)nullptr, c->in_off.as<int32_t>());
     return AG_OK;
 }
 
@@ -2570,7 +2567,7 @@ int ag_launch_eval(ag_ctx* c, const int32_t* idx, int64_t n_act, double theta, d
     int64_t mg = 0;
     AG_TRY(ag_prepare_groups(c, idx, n_act, &mg, n_dev, n_total));
     Groups Gr{c->all_active ? (const int32_t*)nullptr : c->act_pos.as<int32_t>(), c->grp.as<int4>(),
-              c->grp_hdr.as<int32_t>(), c->grp_ord.as<int32_t>()};
+              c->grp_hdr.as<int32_t>(), c->in_off.as<int32_t>()};
     const bool ewald = c->box > 0.0 && c->ewald;
     if (c->box <= 0.0) AG_TRY(order_groups(c, idx ? n_act : c->n, c->rel_n > 0, Gr));
     if (ewald) AG_TRY(ewald_table(c));
@@ -2672,7 +2669,7 @@ int ag_launch_backward(ag_ctx* c, const int32_t* idx, int64_t n_act, const doubl
     const bool grouped = call != 0;
     if (!grouped) AG_TRY(ag_prepare_groups(c, nullptr, n, &mg, nullptr, nullptr));
     Groups Gr{c->all_active ? (const int32_t*)nullptr : c->act_pos.as<int32_t>(), c->grp.as<int4>(),
-              c->grp_hdr.as<int32_t>(), c->grp_ord.as<int32_t>()};
+              c->grp_hdr.as<int32_t>(), c->in_off.as<int32_t>()};
     AG_TRY(order_groups(c, n, false, Gr));
     WalkOut O = make_out(c, G);
     O.dldx = dLdx;
