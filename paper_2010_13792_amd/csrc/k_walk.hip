@@ -2663,14 +2663,14 @@ int ag_launch_backward(ag_ctx* c, const int32_t* idx, int64_t n_act, const doubl
             hipLaunchKernelGGL(k_inner_wlevel, dim3(g), dim3(256), 0, st, l, l, lvl, ll, ch, m64, w64, wf);
         hipLaunchKernelGGL(k_inner_wlevel, dim3(1), dim3(256), 0, st, kTop, 0, lvl, ll, ch, m64, w64, wf);
     }
-    // every particle is a target: the first walk's groups where it had all rows
-    // (and the second set of work queues), else groups of their own
+    // every particle is a target: the first walk's groups, in its order, where it
+    // had all rows (and the second set of work queues), else groups of their own
     int64_t mg = n + c->n_sys + 1;
     const bool grouped = call != 0;
     if (!grouped) AG_TRY(ag_prepare_groups(c, nullptr, n, &mg, nullptr, nullptr));
     Groups Gr{c->all_active ? (const int32_t*)nullptr : c->act_pos.as<int32_t>(), c->grp.as<int4>(),
               c->grp_hdr.as<int32_t>(), c->in_off.as<int32_t>()};
-    AG_TRY(order_groups(c, n, false, Gr));
+    if (!grouped) AG_TRY(order_groups(c, n, false, Gr));
     WalkOut O = make_out(c, G);
     O.dldx = dLdx;
     O.dldm = dLdm;
