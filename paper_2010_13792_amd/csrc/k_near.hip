@@ -773,7 +773,10 @@ __device__ __forceinline__ void sum_pairs(NearLds& S, const NearArgs& A, const R
 // Persistent waves.  Every group has `cuts` places; it is cut into as few runs
 // of at most `run` targets as hold them, of equal length, and its other places
 // are empty.  An eighth of the places (neighbouring groups) belongs to the
-// waves of one XCD, which take them in turn: with a queue, the pops of one
+// waves of one XCD, which take them in turn, each wave another place of its group
+// every time (where their number is a multiple of `cuts` it would be the same one,
+// and the waves of the last places idle: 10^6 particles with k = 32 in runs of 10,
+// five of seven places used, 3.01 ms, now 2.30): with a queue, the pops of one
 // counter, 0.2 us each, took longer than the runs (2^20 particles: 4.0 ms).
 template <int kMode, bool kPer>
 __global__ void __launch_bounds__(kW, 4) k_near(NearArgs A, int run, int cuts) {
@@ -782,8 +785,18 @@ __global__ void __launch_bounds__(kW, 4) k_near(NearArgs A, int run, int cuts) {
     const int lane = ag_lane();
     const int xcd = (int)(blockIdx.x & 7);
     const int g0 = (int)((int64_t)n_groups * xcd / 8), g1 = (int)((int64_t)n_groups * (xcd + 1) / 8);
-    for (int64_t i = blockIdx.x >> 3; i < (int64_t)(g1 - g0) * cuts; i += gridDim.x >> 3) {
-        const int g = g0 + (int)(i / cuts), c = (int)(i % cuts);
+    const int waves = (int)(gridDim.x >> 3), w = (int)(blockIdx.x >> 3);
+    // (the steps of all waves alike: a group's places stay one to a wave)
+    const int add_g = waves / cuts, add_c = waves % cuts != 0 ? waves % cuts : 1, carry = waves % cuts != 0;
+    int g = g0 + w / cuts - add_g, c = w % cuts - add_c;
+    for (;;) {
+        g += add_g;
+        c += add_c;
+        if (c >= cuts) {
+            c -= cuts;
+            g += carry;
+        }
+        if (g >= g1) break;
         const int4 gd = A.grp[g];
         const int count = gd.y, nc = (count + run - 1) / run;
         const int root = A.sys_root[gd.z];
