@@ -202,7 +202,7 @@ extern "C" int ag_destroy(ag_ctx* c) {
                       &c->nd_rec, &c->nd_slot, &c->nd_link, &c->nd_mp,
                       &c->nd_64, &c->nd_w, &c->nd_wf, &c->in_cnt, &c->in_off,
                       &c->tree_hdr, &c->lvl_list, &c->leaf_list, &c->leaf_pos, &c->child, &c->sys_off, &c->sys_root, &c->sys_box, &c->act_flag,
-                      &c->act_pos, &c->act_off, &c->grp, &c->grp_hdr, &c->ewald_tab, &c->soft_h, &c->soft_s, &c->rel_a, &c->grp_cnt, &c->grp_tile, &c->grp_amin, &c->sys_act, &c->wsorted,
+                      &c->act_pos, &c->act_off, &c->grp, &c->grp_hdr, &c->ewald_tab, &c->soft_h, &c->soft_s, &c->rel_a, &c->grp_cnt, &c->grp_tile, &c->grp_amin, &c->wsorted,
                       &c->direct_part, &c->tmp_tidal, &c->sel_flag, &c->sel_tile, &c->stats, &c->dflags};
     for (DevBuf* b : bufs) ag_release(*b);
     for (PhaseEvents& p : c->timing.pending) {

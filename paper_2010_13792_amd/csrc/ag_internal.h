@@ -159,7 +159,6 @@ struct ag_ctx {
     DevBuf grp_cnt;               // i32 [max_nodes]: groups owned per node
     DevBuf grp_tile;              // i32: their totals per tile
     DevBuf grp_amin;              // f32: smallest |a_old| of each group
-    DevBuf sys_act;               // i32 [n_sys + 1]
     DevBuf wsorted;               // double4 [n]: adjoint weights in sorted order
     DevBuf direct_part;           // direct sum: FP64 per-split sums of a small target set
     DevBuf tmp_tidal;             // double [n*6]

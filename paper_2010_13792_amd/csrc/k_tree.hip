@@ -1,8 +1,8 @@
 // k_tree.hip -- oct-tree construction on the GPU.
 //
 // Pipeline (all on the context's stream, no host synchronisation):
-//   1. bounding cube of each system (order-preserving integer atomics, one
-//      atomic per workgroup and axis), non-finite detection;
+//   1. bounding cube of each system (partial boxes per workgroup, reduced),
+//      non-finite detection;
 //   2. 63-bit Morton keys: 21 octal digits; with several systems the top
 //      digits hold the system number and the rest its own cube's Morton code;
 //   3. stable LSD radix sort of (key, row) pairs over the top 32 key bits,
@@ -58,31 +58,24 @@ __device__ __forceinline__ int sys_of(const int64_t* __restrict__ off, int n_sys
 // ---------------------------------------------------------------------------
 constexpr int64_t kBoxChunk = 2048;
 
-// One block opens a build over several systems: system offsets (checked; NULL = one system), the
-// empty bounding boxes, the first box workgroup of each system (exclusive
-// scan of their chunk counts) and a zeroed tree header.
+// One block opens a build over several systems: their offsets (checked, and kept
+// within the arrays), the first box workgroup of each system (exclusive scan of
+// their chunk counts) and a zeroed tree header.
 __global__ void k_build_init(int n_sys, int64_t n, const int64_t* __restrict__ in, int64_t* __restrict__ off,
-                             int32_t* __restrict__ flags, uint64_t* __restrict__ box, int32_t* __restrict__ blk_off,
+                             int32_t* __restrict__ flags, int32_t* __restrict__ blk_off,
                              int64_t* __restrict__ hdr, int hdr_words) {
     __shared__ int s_sum[AG_MAX_SYS + 1];
     for (int s = threadIdx.x; s <= n_sys; s += blockDim.x) {
-        const int64_t v = in ? in[s] : (s == 0 ? 0 : n);
-        if (in) {
-            const bool bad = (s == 0 && v != 0) || (s == n_sys && v != n) || v < 0 || v > n ||
-                             (s > 0 && in[s - 1] > v);
-            if (bad) atomicOr(flags, AGF_BADINDEX);
-        }
-        off[s] = v;
+        const int64_t v = in[s];
+        const bool bad = (s == 0 && v != 0) || (s == n_sys && v != n) || v < 0 || v > n || (s > 0 && in[s - 1] > v);
+        if (bad) atomicOr(flags, AGF_BADINDEX);
+        off[s] = v < 0 ? 0 : (v > n ? n : v);
     }
     for (int i = threadIdx.x; i < hdr_words; i += blockDim.x) hdr[i] = 0;
     __syncthreads();
     for (int s = threadIdx.x; s < n_sys; s += blockDim.x) {
-        for (int c = 0; c < 3; ++c) {
-            box[6 * s + c] = ~0ull;        // min slots start at the top
-            box[6 * s + 3 + c] = 0ull;     // max slots at the bottom
-        }
         const int64_t sz = off[s + 1] - off[s];
-        s_sum[s] = (int)((sz + kBoxChunk - 1) / kBoxChunk);
+        s_sum[s] = sz > 0 ? (int)((sz + kBoxChunk - 1) / kBoxChunk) : 0;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -724,36 +717,6 @@ __device__ void cd_min_top(const CdMin& M, const CdCounts& C) {
     }
 }
 
-// first position q' >= q with cd[q'] < l (n if none): finish q's run of 16,
-// then skip whole runs by their minima, climbing a level each time a run of
-// the level above is passed, and search the run found downwards
-__device__ int64_t next_below(int64_t n, const int32_t* __restrict__ cd, const CdMin& M, int64_t q, int l) {
-    if (q >= n) return n;
-    for (; q & 15; ++q) {
-        if (q >= n) return n;
-        if (cd[q] < l) return q;
-    }
-    int lev = 0;
-    int64_t idx = q >> 4;
-    for (;;) {
-        if ((idx << (4 * (lev + 1))) >= n) return n;
-        if (M.lev[lev][idx] < l) break;
-        ++idx;
-        if ((idx & 15) == 0 && lev < kCdLevels - 1) {
-            ++lev;
-            idx >>= 4;
-        }
-    }
-    while (lev > 0) {
-        --lev;
-        idx <<= 4;
-        while (M.lev[lev][idx] >= l) ++idx;
-    }
-    q = idx << 4;
-    while (cd[q] >= l) ++q;
-    return q;
-}
-
 struct TopoParams {
     int64_t n;
     int n_leaf;
@@ -1244,8 +1207,8 @@ __device__ __forceinline__ int cd_level(int64_t n, const int32_t* __restrict__ c
     return j < (n + span - 1) / span ? M.lev[k][j] : INT_MAX;
 }
 
-// next_below for a group of 16 lanes (lane s = 0..15 of the group; every
-// lane of the group takes the same path): climb from q, reading at each
+// First position q' >= q with cd[q'] < l (n if none), by a group of 16 lanes
+// (lane s = 0..15 of the group; every lane takes the same path): climb from q, reading at each
 // level the entries up to the next boundary of the level above (all of them
 // start at or after the positions already passed), until one holds a count
 // below l; then descend through its 16 children per level.  About two loads
@@ -1790,12 +1753,6 @@ __global__ void __launch_bounds__(1024) k_inner_level(int l_hi, int l_lo, const 
     }
 }
 
-__global__ void k_fill_i32(int32_t* __restrict__ p, int64_t n, int32_t v) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = v;
-}
-
 // Moments: the leaves, then the inner levels from the deepest up.  The
 // levels below the deepest of the last build whose depth the host has seen
 // (c->seen_max_level; 20 if none) take one single-workgroup launch (they are
@@ -1920,7 +1877,7 @@ int ag_launch_build(ag_ctx* c, int64_t n, const double* x, const double* v, cons
     }
     const bool one = sys_offsets == nullptr;
     if (!one)
-        hipLaunchKernelGGL(k_build_init, dim3(1), dim3(512), 0, st, n_sys, n, sys_offsets, off, flags, box, blk_off,
+        hipLaunchKernelGGL(k_build_init, dim3(1), dim3(512), 0, st, n_sys, n, sys_offsets, off, flags, blk_off,
                            hdr, (int)(kTreeHdrBytes / 8));
     const int64_t box_blocks = one ? (n + kBoxChunk - 1) / kBoxChunk : n / kBoxChunk + n_sys + 1;
     uint64_t* box_part = reinterpret_cast<uint64_t*>(c->spos.p);   // free until the particles move

@@ -242,7 +242,7 @@ __device__ __forceinline__ bool mac_accept(const GroupBox& g, const NodeRec& c, 
 //     = ca nu + cd d + cp P - ri5 V,  V = Q nu + Qd d,
 //       cd = e P.nu - beta d.nu + 2.5 ri7 (d.Qd.d),  cp = e d.nu,
 // with d.Qd.d = d.V - P.nu (Q is symmetric).  Accumulates g, j and S = -T
-// (same convention as pair_interact); the ca I part of S is summed into
+// (pair.h's convention); the ca I part of S is summed into
 // `sca` and added to the diagonal once per tile.
 template <bool kTidal>
 __device__ __forceinline__ void node_interact(float dx, float dy, float dz, float nx, float ny, float nz,
@@ -388,7 +388,7 @@ struct ForwardSums {
         S.tile[kW + lane] = make_float4(u.x, u.y, u.z, T.sh ? T.sh[pk] : u.w);   // .w: softening length
         S.tidx[lane] = pk;
     }
-    // The quantities of pair_interact, written as multiply-add chains into
+    // The pair terms of pair.h, written as multiply-add chains into
     // the accumulators, with the m f I part of S summed once per tile.  The
     // self pair has d = 0 exactly (both sides round the same FP64 position),
     // so it always takes the softened branch, where it is dropped.  Periodic:
