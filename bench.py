@@ -44,23 +44,23 @@ PEAK_FP32_PACKED_SPEC = 157.3                   # MI355X's published FP32 vector
 PEAK_HBM_GBS = 8000.0
 
 # HBM traffic of the walk kernel at the default workload, from two rocprofv3
-# --pmc passes (FETCH_SIZE, WRITE_SIZE; KiB per dispatch, mean of the 5
+# --pmc passes (FETCH_SIZE, WRITE_SIZE; KiB per dispatch, mean of the 4
 # walk dispatches of a --no-tune run, the configuration named below)
 # scaled by what the same counters read for a plain 1 GiB device copy
 # (FETCH_SIZE 524305 KiB -> x2.0, WRITE_SIZE 1048576 KiB -> x1.0).  Valid only
 # while the walk kernel's sources hash to `src_sha256`; reported as null
 # otherwise, or for another workload.
 WALK_COUNTERS = {
-    "src_sha256": "6345fe3711c5c4d790309e59532916a182d333fd410154eb2449c9a84cb2c731",
+    "src_sha256": "7e015dad0397149939ea1dc4313bf4e86c3e04863ff4ef5fbdf5635cacbfda49",
     "workload": {"n": 1 << 20, "theta": 0.7, "eps": 1e-3, "n_leaf": 16, "mac_offset": 1, "group_targets": 64,
                  "waves_per_cu": 16, "group_split": 42, "group_pack": 0},
-    "fetch_kib": 214446.2, "write_kib": 171078.4,
+    "fetch_kib": 216987.7, "write_kib": 171076.2,
     "fetch_factor": 1048576.0 / 524304.5, "write_factor": 1.0,
 }
 # FP32 flops the hardware executed in one walk launch at the same workload
 # (SQ_INSTS_VALU_FLOPS_FP32 + _TRANS, per wave instruction, times 64 lanes);
 # they include the repeated work of lanes left over in small groups
-WALK_EXECUTED_FP32_FLOPS = (2475455898.0 + 21293289.0) * 64
+WALK_EXECUTED_FP32_FLOPS = (2475456223.5 + 21293451.3) * 64
 WALK_SOURCES = ("paper_2010_13792_amd/csrc/k_walk.hip", "paper_2010_13792_amd/csrc/pair.h",
                 "paper_2010_13792_amd/csrc/ag_internal.h")
 # algorithmic bytes of one build: per particle, read x, v, m (56), write them
@@ -433,7 +433,7 @@ def main():
             "unit": "TFLOP/s", "frac": achieved_tflops / PEAK_FP32_TFLOPS, "traffic": traffic,
             "hbm_gbs": None if traffic is None else traffic / (walk_ms * 1e-3) / 1e9,
             "hbm_frac": None if traffic is None else traffic / (walk_ms * 1e-3) / 1e9 / PEAK_HBM_GBS,
-            "kernel": "k_walk", "kernel_ms": walk_ms,
+            "kernel": "k_walk_team", "kernel_ms": walk_ms,
             "flops_per_launch": walk_flops,
             "executed_fp32_tflops": (WALK_EXECUTED_FP32_FLOPS / (walk_ms * 1e-3) / 1e12
                                      if walk_counters_valid(args, tuned) else None),

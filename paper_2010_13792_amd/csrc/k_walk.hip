@@ -227,6 +227,9 @@ __device__ __forceinline__ bool mac_accept(const GroupBox& g, const NodeRec& c, 
         bz = fabsf((float)(0.5 * ((double)lo.z + (double)hi.z) - g.cz));
     }
     {
+        // (x with one rounding, y and z with two, written out: that is how the compiler
+        // contracted these sums when the test's results were first taken, and a target
+        // on the cube's face would change sides with another choice)
 #pragma clang fp contract(off)
         const float e = 0.6f * Ln;
         return !(bx < __builtin_fmaf(0.6f, Ln, g.hx) && by < e + g.hy && bz < e + g.hz);
@@ -1492,7 +1495,7 @@ __device__ __forceinline__ void walk_group(typename Pol::Lds* all, HelpLds<W>& H
 
 // ---- one group walked by a team of waves ----
 // With fewer groups than the device has waves, a walk by single waves lasts as
-// long as its longest group (3000 particles: 70 groups on 1024 SIMDs, 0.74 ms).
+// long as its longest group (3000 particles: 96 groups on 1024 SIMDs, 0.74 ms).
 // A team (of 4 waves or the whole workgroup) walks one group: its first wave traverses the tree and queues the
 // full tiles in LDS, the others (and the first when the queue is full or the
 // traversal done) take tiles from the queue, stage and evaluate them, and fold
