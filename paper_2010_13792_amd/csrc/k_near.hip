@@ -884,11 +884,15 @@ void launch_near(ag_ctx* c, const NearArgs& A, int64_t max_groups, int64_t targe
 }  // namespace
 
 // Measured (us; before: lists of k distances in registers, sums on one lane per
-// target): k = 32 on a uniform sphere of 2^17, 1130 -> 390, of 10^6, 3510 ->
-// 2500; lengths and Omega at n_ngb = 32, 2^16: 2510 -> 463, 10^6: 15 700 ->
-// 4900; Z, 2^16: 542 -> 140; correction, 2^16: 697 -> 177.  Bound by
-// instruction issue: of a run's time about a third each goes to the traversal
-// (16 steps), the distances and the lists.
+// target): k = 32 on a uniform sphere of 2^17, 1130 -> 364, of 10^6, 3510 ->
+// 2300 (k = 8 to 16 of 10^6 2 to 5% slower); lengths and Omega at n_ngb = 32,
+// 2^16: 2510 -> 418, 10^6: 15 700 -> 4400; Z, 2^16: 542 -> 142, 10^6: 1490 ->
+// 1390; correction, 2^16: 697 -> 175, 10^6: 2270 -> 1950.  With long supports
+// and many particles the sums are slower than one lane per target was (10^6,
+// n_ngb = 400: Z 4100 -> 5300, correction 8300 -> 12 100), the lengths faster by
+// more (lengths, Z and correction 53 500 -> 47 900).  Bound by instruction
+// issue: of a run's time about a third each goes to the traversal (16 steps),
+// the distances and the lists.
 
 // distance of every particle to its k-th nearest other particle
 int ag_launch_knn(ag_ctx* c, int32_t k, double scale, double* h_out) {
